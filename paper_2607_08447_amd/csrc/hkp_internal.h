@@ -206,8 +206,10 @@ hipError_t launch_scale(double* v, long long n, int batch, long long bstride,
 // ---------------------------------------------------------------------------
 // mode 0 (RR):   A Hermitian nb x nb -> eigenvalues theta (ascending) and
 //                eigenvectors Q (columns), written over A's buffer layout
-// mode 1 (SVQB): A = Gram S -> T = D U diag(lambda)^-1/2, D = diag(S)^-1/2
-// SVQB mode: again[b] (if given) is set to 1 when the Gram matrix is so ill
+// mode 1 (orthonormaliser): A = Gram matrix G -> T with X T orthonormal: D L^-H from
+//                the Cholesky factor of D G D where that is provably well conditioned
+//                (evals not written), else SVQB, T = D U diag(lambda)^-1/2; D = diag(G)^-1/2
+// mode 1: again[b] (if given) is set to 1 when the Gram matrix is so ill
 // conditioned that a second pass is needed (and the member is active)
 // C = op(A) B per member (op: A if adj = 0, A^H if adj = 1), nb x nb complex
 // row-major; herm: store the Hermitian part; C must not alias A or B
@@ -225,6 +227,12 @@ hipError_t launch_set_identity(double* C, int nb, int batch, long long mat_strid
 hipError_t launch_heev(double* A, int nb, int batch, long long mat_stride, double* evals,
                        double* out, int mode, int* status, const int* active, hipStream_t s,
                        int* again = nullptr);
+// Rayleigh-Ritz step on small matrices: eigenvalues theta (ascending) of the Hermitian
+// part of S^H M S and T = S Q, one launch, for the nb that rr_supported accepts; T must
+// not alias M or S
+bool rr_supported(int nb);
+hipError_t launch_rr(const double* M, const double* S, int nb, int batch, long long mat_stride,
+                     double* theta, double* T, const int* active, hipStream_t s);
 
 // first step of the scaled Chebyshev filter: damp [a_cut, b_up], value 1 at the
 // lowest Ritz value a0; Y1 = alpha (H - shift) X (the later steps' coefficients

@@ -538,11 +538,15 @@ void rayleigh_ritz(const Ctx& c, const int* active) {
   double* tmp = c.at<double>(c.L.mat4);
   apply_block(c, c.L.X, c.L.W, active);
   HKP_CHECK(launch_gram(X, W, 1, c.p.batch, c.at<double>(c.L.gram), M, active, c.s));
-  HKP_CHECK(launch_small_gemm(M, 0, S, tmp, c.p.nb, c.p.batch, ms, 0, active, c.s));
-  HKP_CHECK(launch_small_gemm(S, 1, tmp, M, c.p.nb, c.p.batch, ms, 1, active, c.s));
-  HKP_CHECK(launch_heev(M, c.p.nb, c.p.batch, ms, c.at<double>(c.L.theta), tmp, 0, nullptr,
-                        active, c.s));
-  HKP_CHECK(launch_small_gemm(S, 0, tmp, Q, c.p.nb, c.p.batch, ms, 0, active, c.s));
+  if (rr_supported(c.p.nb)) {
+    HKP_CHECK(launch_rr(M, S, c.p.nb, c.p.batch, ms, c.at<double>(c.L.theta), Q, active, c.s));
+  } else {
+    HKP_CHECK(launch_small_gemm(M, 0, S, tmp, c.p.nb, c.p.batch, ms, 0, active, c.s));
+    HKP_CHECK(launch_small_gemm(S, 1, tmp, M, c.p.nb, c.p.batch, ms, 1, active, c.s));
+    HKP_CHECK(launch_heev(M, c.p.nb, c.p.batch, ms, c.at<double>(c.L.theta), tmp, 0, nullptr,
+                          active, c.s));
+    HKP_CHECK(launch_small_gemm(S, 0, tmp, Q, c.p.nb, c.p.batch, ms, 0, active, c.s));
+  }
   HKP_CHECK(launch_ritz(X, W, c.p.nb, c.at<double>(c.L.mat2), c.at<double>(c.L.theta),
                         c.at<double>(c.L.bounds),
                         c.p.product ? c.at<double>(c.L.roots) : nullptr, c.at<int>(c.L.act32),
