@@ -304,7 +304,7 @@ int run_autotune(const hkp_grid& g, int nb, bool mixed, bool strain, int field, 
                  size_t ws_bytes, void* stream, hkp_tune* out) {
   const long long N = (long long)g.nx * g.ny * g.nz, n6 = 6 * N;
   const size_t esz = mixed ? 8 : 16;
-  size_t need = al(6 * N * 8) + al((size_t)g.nz * 16) + al((size_t)g.nz * g.nx * 16) +
+  size_t need = al(6 * N * 8) + al(phase_table_bytes(g.nz, 8)) + al((size_t)g.nx * 16) +
                 2 * al((size_t)nb * n6 * esz);
   if (ws_bytes < need) {
     set_error("autotune workspace too small: need " + std::to_string(need) + " bytes");
@@ -319,8 +319,8 @@ int run_autotune(const hkp_grid& g, int nb, bool mixed, bool strain, int field, 
     return q;
   };
   void* D = take(6 * N * 8);
-  void* wt = take((size_t)g.nz * 16);
-  void* vt = take((size_t)g.nz * g.nx * 16);
+  void* pt = take(phase_table_bytes(g.nz, 8));
+  void* ut = take((size_t)g.nx * 16);
   void* X = take((size_t)nb * n6 * esz);
   void* O = take((size_t)nb * n6 * esz);
   void* Y = O;   // the solver's filter writes over the block it reads as Y_old
@@ -358,8 +358,9 @@ int run_autotune(const hkp_grid& g, int nb, bool mixed, bool strain, int field, 
     a.out_fp64 = !mixed;
     a.D = D;
     a.strain = strain;
-    a.wtab = field ? wt : nullptr;
-    a.vtab = field ? vt : nullptr;
+    a.ptab = field ? pt : nullptr;
+    a.ptab64 = static_cast<const double*>(pt);
+    a.utab64 = static_cast<const double*>(ut);
     a.phase_general = field == 2;
     a.coef.alpha = 1.0;
     a.coef.shift = 0.5;
@@ -409,8 +410,7 @@ int run_autotune(const hkp_grid& g, int nb, bool mixed, bool strain, int field, 
         a.D = D;
         a.strain = strain;
         a.zero = X;   // the timing blocks are all zero
-        a.wtab = field ? wt : nullptr;
-        a.vtab = field ? vt : nullptr;
+        a.ptab = field ? pt : nullptr;
         a.host1[0] = a.host2[0] = 1.0;
         a.host1[1] = a.host2[1] = 0.5;
         a.host1[2] = a.host2[2] = -1.0;

@@ -89,31 +89,48 @@ __global__ void onsite_kernel(int nx, int ny, int nz, const double* V, long long
 }
 
 __global__ void phase_kernel(int nx, int nz, double h, double Bx, double By, double Bz,
-                             double* w64, double* v64, float* w32, float* v32) {
+                             StencilConsts<double> k, double* p64, double* u64, float* p32) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   const double kh = kEoverHbar * h;
-  if (t < nz) {
-    const double Z = (t - 0.5 * (nz - 1)) * h;
+  auto expi = [](double a) {
     double s, c;
-    sincos(kh * By * Z, &s, &c);
-    w64[2 * t] = c;
-    w64[2 * t + 1] = s;
-    if (w32) {
-      w32[2 * t] = (float)c;
-      w32[2 * t + 1] = (float)s;
+    sincos(a, &s, &c);
+    return make_double2(c, s);
+  };
+  auto mul = [](double2 a, double2 b) {
+    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+  };
+  if (t < nz) {
+    // x-links w, y-links v (their part along z) of planes z-1, z, z+1; e: the y-links'
+    // step from one column to the next
+    auto w = [&](int z) { return expi(kh * By * (z - 0.5 * (nz - 1)) * h); };
+    auto v = [&](int z) { return expi(-kh * Bx * (z - 0.5 * (nz - 1)) * h); };
+    const double2 w0 = w(t), v0 = v(t), wm = w(t - 1), wp = w(t + 1), vm = v(t - 1),
+                  vp = v(t + 1);
+    const double2 e = expi(kh * Bz * h);
+    const double2 ep = make_double2(1.0 + e.x, e.y), em = make_double2(1.0 + e.x, -e.y);
+    const double2 wv = mul(w0, v0), wvc = mul(w0, make_double2(v0.x, -v0.y));
+    const double cLMM = k.cLM + k.cM, n8 = k.cN8;
+    auto s = [](double a, double2 b) { return make_double2(a * b.x, a * b.y); };
+    auto add = [](double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); };
+    const double2 row[kFoldRow] = {
+        s(k.cM, w0), s(cLMM, w0), s(k.cM, v0), s(cLMM, v0),
+        s(n8, mul(wv, ep)), s(n8, mul(wv, em)), s(-n8, mul(wvc, em)), s(-n8, mul(wvc, ep)),
+        s(n8, add(wm, w0)), s(-n8, add(wp, w0)), s(n8, add(vm, v0)), s(-n8, add(vp, v0))};
+    for (int i = 0; i < kFoldRow; ++i) {
+      const size_t o = 2 * ((size_t)t * kFoldRow + i);
+      p64[o] = row[i].x;
+      p64[o + 1] = row[i].y;
+      if (p32) {
+        p32[o] = (float)row[i].x;
+        p32[o + 1] = (float)row[i].y;
+      }
     }
   }
-  if (t < nx * nz) {
-    const int x = t % nx, z = t / nx;
-    const double X = (x - 0.5 * (nx - 1)) * h, Z = (z - 0.5 * (nz - 1)) * h;
-    double s, c;
-    sincos(kh * (Bz * X - Bx * Z), &s, &c);
-    v64[2 * t] = c;
-    v64[2 * t + 1] = s;
-    if (v32) {
-      v32[2 * t] = (float)c;
-      v32[2 * t + 1] = (float)s;
-    }
+  if (t < nx) {
+    const double2 u = expi(kh * Bz * (t - 0.5 * (nx - 1)) * h);
+    u64[2 * t] = u.x;
+    u64[2 * t + 1] = u.y;
   }
 }
 
@@ -361,10 +378,11 @@ hipError_t launch_onsite(const hkp_material& m, int nx, int ny, int nz, int batc
   return hipGetLastError();
 }
 
-hipError_t launch_phase_tables(int nx, int nz, double h, const double B[3], double* w64,
-                               double* v64, float* w32, float* v32, hipStream_t s) {
-  const int n = nx * nz > nz ? nx * nz : nz;
-  phase_kernel<<<(n + 255) / 256, 256, 0, s>>>(nx, nz, h, B[0], B[1], B[2], w64, v64, w32, v32);
+hipError_t launch_phase_tables(int nx, int nz, double h, const double B[3],
+                               const StencilConsts<double>& c, double* p64, double* u64,
+                               float* p32, hipStream_t s) {
+  const int n = nx > nz ? nx : nz;
+  phase_kernel<<<(n + 255) / 256, 256, 0, s>>>(nx, nz, h, B[0], B[1], B[2], c, p64, u64, p32);
   return hipGetLastError();
 }
 

@@ -78,8 +78,9 @@ struct StencilLaunch {
   const void* D;         // onsite fields (kernel type)
   long long D_bstride;   // reals between Hamiltonians
   int strain;            // D holds 6 arrays
-  const void* wtab;      // [nz] complex, kernel type, or null (B = 0)
-  const void* vtab;      // [nz][nx] complex
+  const void* ptab;      // [nz][kFoldRow] complex, kernel type: folded phases, or null (B = 0)
+  const double* ptab64;  // Bz != 0: the folded phases in double,
+  const double* utab64;  // and [nx] complex the y-links' phase along x
   int phase_general;     // Bz != 0: y-link phases vary along x
   StepCoef coef;
   const int* active;     // [batch] 0 = skip, or null
@@ -88,10 +89,10 @@ struct StencilLaunch {
                          // (vector lock[b] + i of member b is virtual vector work[b] + i);
                          // the grid covers nvec * batch vectors and only the first
                          // work[batch] are live, spread evenly over the XCDs. Or null.
-  int tile_y;            // 1, 2, 4
+  int tile_y;            // 1, 2, 4: waves of a workgroup per spin
   int vgroup;            // vectors of one tile side by side (1 vector-major, nvec tile-major)
-  int dma;               // 1: rows staged global -> LDS directly (needs nx % 64 == 0)
-  int zsplit;            // z ranges per (vector, tile): 0 never, 1 for small launches, 2 always
+  int dma;               // 1: rows may be staged global -> LDS directly (where nx % 64 == 0)
+  int zsplit;            // z ranges per (vector, tile): 0 never, 1 for small launches, 2 always two
   int fp64;              // kernel type
   int ncomp = 6;         // components per vector: 6 (spinor) or 3 (spin-free orbital, no field)
 };
@@ -114,8 +115,7 @@ struct Stencil2Launch {
   long long D_bstride;
   int strain;
   const void* zero;      // >= 16 bytes of zeros in device memory
-  const void* wtab;      // float phase tables, or null (B = 0)
-  const void* vtab;
+  const void* ptab;      // float folded phases, or null (B = 0)
   int phase_general;     // Bz != 0: not supported by this kernel
   const double* coef1;   // [batch][...]: alpha, shift, beta of the first step, or null
   const double* coef2;   // of the second (both null: host1 / host2 below)
@@ -137,8 +137,14 @@ hipError_t launch_stencil2(const Stencil2Launch& a, const StencilConsts<double>&
 hipError_t launch_onsite(const hkp_material& m, int nx, int ny, int nz, int batch,
                          const double* V, long long V_bstride, const double* strain,
                          double* D64, float* D32, long long D_bstride, hipStream_t s);
-hipError_t launch_phase_tables(int nx, int nz, double h, const double B[3], double* w64,
-                               double* v64, float* w32, float* v32, hipStream_t s);
+// link phases folded with the stencil coefficients, kFoldRow complex entries per plane
+// (order of sten::Fold, without the y-links' phase along x), and that phase u [nx]
+// (1 where Bz = 0); p32 may be null
+constexpr int kFoldRow = 12;
+inline size_t phase_table_bytes(int nz, size_t real) { return (size_t)nz * kFoldRow * 2 * real; }
+hipError_t launch_phase_tables(int nx, int nz, double h, const double B[3],
+                               const StencilConsts<double>& c, double* p64, double* u64,
+                               float* p32, hipStream_t s);
 // ABI (J basis, symmetric gauge, [v][x][y][z][6]) <-> internal (LS, GPU gauge)
 hipError_t launch_abi_to_internal(int nx, int ny, int nz, double h, const double B[3],
                                   int nvec, const void* abi, void* internal, int to_fp32,

@@ -50,7 +50,7 @@ constexpr int kKmax = 200;       // largest Chebyshev degree
 constexpr int kDotParts = 256;
 
 struct Layout {
-  size_t D64, D32, w64, v64, w32, v32, X, W, A32, B32, C32, E32, gram, mat1, mat2, mat3, mat4,
+  size_t D64, D32, p64, u64, p32, X, W, A32, B32, C32, E32, gram, mat1, mat2, mat3, mat4,
       theta, lam,
       r2, rpart, coef, bounds, flags, active, act32, act64, lock, sw, work, again, status, lal,
       lnrm,
@@ -69,10 +69,9 @@ Layout make_layout(const Plan& p) {
   const size_t N = p.N, n6 = p.n6;
   L.D64 = take(B * 6 * N * 8);
   L.D32 = p.mixed ? take(B * 6 * N * 4) : 0;
-  L.w64 = take((size_t)p.nz * 16);
-  L.v64 = take((size_t)p.nz * p.nx * 16);
-  L.w32 = take((size_t)p.nz * 8);
-  L.v32 = take((size_t)p.nz * p.nx * 8);
+  L.p64 = take(phase_table_bytes(p.nz, 8));
+  L.u64 = take((size_t)p.nx * 16);
+  L.p32 = take(phase_table_bytes(p.nz, 4));
   L.X = take(B * p.nb * n6 * 16);
   L.W = take(B * p.nb * n6 * 16);
   if (p.mixed) {
@@ -289,8 +288,9 @@ StencilLaunch base_launch(const Ctx& c, bool fp64, int nvec) {
   a.D_bstride = 6LL * c.p.N;
   a.strain = c.strain;
   if (c.field) {
-    a.wtab = fp64 ? (const void*)c.at<double>(c.L.w64) : (const void*)c.at<float>(c.L.w32);
-    a.vtab = fp64 ? (const void*)c.at<double>(c.L.v64) : (const void*)c.at<float>(c.L.v32);
+    a.ptab = fp64 ? (const void*)c.at<double>(c.L.p64) : (const void*)c.at<float>(c.L.p32);
+    a.ptab64 = c.at<double>(c.L.p64);
+    a.utab64 = c.at<double>(c.L.u64);
     a.phase_general = c.field_z;
   }
   a.tile_y = c.p.st.tile_y;
@@ -407,8 +407,7 @@ void filter32(const Ctx& c, const int* active, int m) {
     t2.D_bstride = 6LL * c.p.N;
     t2.strain = c.strain;
     if (c.field) {
-      t2.wtab = c.at<float>(c.L.w32);
-      t2.vtab = c.at<float>(c.L.v32);
+      t2.ptab = c.at<float>(c.L.p32);
       t2.phase_general = c.field_z;
     }
     t2.coef_stride = kstride;
@@ -733,9 +732,8 @@ int run_solve(const SolveArgs& A, hkp_stats* stats) {
                           c.at<double>(c.L.D64), p.mixed ? c.at<float>(c.L.D32) : nullptr,
                           6LL * p.N, c.s));
   if (c.field)
-    HKP_CHECK(launch_phase_tables(p.nx, p.nz, p.h, A.B, c.at<double>(c.L.w64),
-                                  c.at<double>(c.L.v64), c.at<float>(c.L.w32),
-                                  c.at<float>(c.L.v32), c.s));
+    HKP_CHECK(launch_phase_tables(p.nx, p.nz, p.h, A.B, c.consts, c.at<double>(c.L.p64),
+                                  c.at<double>(c.L.u64), c.at<float>(c.L.p32), c.s));
   HKP_CHECK(launch_fill_int(c.at<int>(c.L.flags), 8 * p.batch, 0, c.s));
   HKP_CHECK(launch_fill_int(c.at<int>(c.L.zero), 64, 0, c.s));
   HKP_CHECK(launch_fill_int(c.at<int>(c.L.active), p.batch, 1, c.s));
@@ -1052,8 +1050,8 @@ size_t apply_bytes(const hkp_grid& g, int nvec) {
   const size_t n6 = 6 * N;
   size_t b = 0;
   b += align_up(6 * N * 8) + align_up(6 * N * 4);                     // D64, D32
-  b += align_up((size_t)g.nz * 16) + align_up((size_t)g.nz * g.nx * 16);
-  b += align_up((size_t)g.nz * 8) + align_up((size_t)g.nz * g.nx * 8);
+  b += align_up(phase_table_bytes(g.nz, 8)) + align_up((size_t)g.nx * 16);
+  b += align_up(phase_table_bytes(g.nz, 4));
   b += 3 * align_up((size_t)nvec * n6 * 16);                          // X, Old, Y (FP64)
   b += align_up((size_t)nvec * n6 * 8);                               // X (FP32)
   return b;
@@ -1072,10 +1070,9 @@ int run_filter_step(const FilterArgs& A) {
   };
   double* D64 = (double*)take(6 * N * 8);
   float* D32 = (float*)take(6 * N * 4);
-  double* w64 = (double*)take((size_t)g.nz * 16);
-  double* v64 = (double*)take((size_t)g.nz * g.nx * 16);
-  float* w32 = (float*)take((size_t)g.nz * 8);
-  float* v32 = (float*)take((size_t)g.nz * g.nx * 8);
+  double* p64 = (double*)take(phase_table_bytes(g.nz, 8));
+  double* u64 = (double*)take((size_t)g.nx * 16);
+  float* p32 = (float*)take(phase_table_bytes(g.nz, 4));
   double* Xi = (double*)take((size_t)A.nvec * n6 * 16);
   double* Oi = (double*)take((size_t)A.nvec * n6 * 16);
   double* Yi = (double*)take((size_t)A.nvec * n6 * 16);
@@ -1083,7 +1080,9 @@ int run_filter_step(const FilterArgs& A) {
   const bool fp64 = A.precision == HKP_PREC_FP64;
   const bool field = A.B[0] != 0.0 || A.B[1] != 0.0 || A.B[2] != 0.0;
   HKP_CHECK(launch_onsite(A.mat, g.nx, g.ny, g.nz, 1, A.V, 0, A.strain, D64, D32, 0, s));
-  if (field) HKP_CHECK(launch_phase_tables(g.nx, g.nz, g.h_nm, A.B, w64, v64, w32, v32, s));
+  const StencilConsts<double> consts = make_consts(A.mat, g.h_nm, A.B);
+  if (field)
+    HKP_CHECK(launch_phase_tables(g.nx, g.nz, g.h_nm, A.B, consts, p64, u64, p32, s));
   HKP_CHECK(launch_abi_to_internal(g.nx, g.ny, g.nz, g.h_nm, A.B, A.nvec, A.X,
                                    fp64 ? (void*)Xi : (void*)Xf, fp64 ? 0 : 1, s));
   const bool has_old = A.Y_old != nullptr && A.beta != 0.0;
@@ -1103,8 +1102,9 @@ int run_filter_step(const FilterArgs& A) {
   a.D = fp64 ? (const void*)D64 : (const void*)D32;
   a.strain = A.strain != nullptr;
   if (field) {
-    a.wtab = fp64 ? (const void*)w64 : (const void*)w32;
-    a.vtab = fp64 ? (const void*)v64 : (const void*)v32;
+    a.ptab = fp64 ? (const void*)p64 : (const void*)p32;
+    a.ptab64 = p64;
+    a.utab64 = u64;
     a.phase_general = A.B[2] != 0.0;
   }
   a.coef.alpha = A.alpha;
@@ -1115,7 +1115,7 @@ int run_filter_step(const FilterArgs& A) {
   a.dma = A.st.dma;
   a.zsplit = A.st.zsplit;
   a.fp64 = fp64;
-  HKP_CHECK(launch_stencil(a, make_consts(A.mat, g.h_nm, A.B), s));
+  HKP_CHECK(launch_stencil(a, consts, s));
   HKP_CHECK(launch_internal_to_abi(g.nx, g.ny, g.nz, g.h_nm, A.B, A.nvec, 1, Yi, 0, A.Y, 0, s));
   return HKP_OK;
 }
@@ -1126,8 +1126,8 @@ size_t apply2_bytes(const hkp_grid& g, int nvec) {
   const size_t n6 = 6 * N;
   size_t b = 0;
   b += align_up(6 * N * 8) + align_up(6 * N * 4);                     // D64, D32
-  b += align_up((size_t)g.nz * 16) + align_up((size_t)g.nz * g.nx * 16);
-  b += align_up((size_t)g.nz * 8) + align_up((size_t)g.nz * g.nx * 8);
+  b += align_up(phase_table_bytes(g.nz, 8)) + align_up((size_t)g.nx * 16);
+  b += align_up(phase_table_bytes(g.nz, 4));
   b += 4 * align_up((size_t)nvec * n6 * 8);                           // X, Old, Y1, Y2 (FP32)
   b += align_up((size_t)nvec * n6 * 16);                              // FP64 staging
   b += align_up(256);                                                 // zeros
@@ -1147,10 +1147,9 @@ int run_filter_step2(const Filter2Args& A, int* passes) {
   };
   double* D64 = (double*)take(6 * N * 8);
   float* D32 = (float*)take(6 * N * 4);
-  double* w64 = (double*)take((size_t)g.nz * 16);
-  double* v64 = (double*)take((size_t)g.nz * g.nx * 16);
-  float* w32 = (float*)take((size_t)g.nz * 8);
-  float* v32 = (float*)take((size_t)g.nz * g.nx * 8);
+  double* p64 = (double*)take(phase_table_bytes(g.nz, 8));
+  double* u64 = (double*)take((size_t)g.nx * 16);
+  float* p32 = (float*)take(phase_table_bytes(g.nz, 4));
   float* Xf = (float*)take((size_t)A.nvec * n6 * 8);
   float* Of = (float*)take((size_t)A.nvec * n6 * 8);
   float* Y1f = (float*)take((size_t)A.nvec * n6 * 8);
@@ -1161,7 +1160,8 @@ int run_filter_step2(const Filter2Args& A, int* passes) {
   HKP_CHECK(launch_fill_int(zero, 64, 0, s));
   const StencilConsts<double> consts = make_consts(A.mat, g.h_nm, A.B);
   HKP_CHECK(launch_onsite(A.mat, g.nx, g.ny, g.nz, 1, A.V, 0, A.strain, D64, D32, 0, s));
-  if (field) HKP_CHECK(launch_phase_tables(g.nx, g.nz, g.h_nm, A.B, w64, v64, w32, v32, s));
+  if (field)
+    HKP_CHECK(launch_phase_tables(g.nx, g.nz, g.h_nm, A.B, consts, p64, u64, p32, s));
   HKP_CHECK(launch_abi_to_internal(g.nx, g.ny, g.nz, g.h_nm, A.B, A.nvec, A.X, Xf, 1, s));
   const bool has_old = A.Y_old != nullptr && A.beta[0] != 0.0;
   if (has_old)
@@ -1183,8 +1183,7 @@ int run_filter_step2(const Filter2Args& A, int* passes) {
   t2.zero = zero;
   t2.strain = A.strain != nullptr;
   if (field) {
-    t2.wtab = w32;
-    t2.vtab = v32;
+    t2.ptab = p32;
     t2.phase_general = A.B[2] != 0.0;
   }
   for (int i = 0; i < 3; ++i) {
@@ -1208,8 +1207,9 @@ int run_filter_step2(const Filter2Args& A, int* passes) {
     a.D = D32;
     a.strain = A.strain != nullptr;
     if (field) {
-      a.wtab = w32;
-      a.vtab = v32;
+      a.ptab = p32;
+      a.ptab64 = p64;
+      a.utab64 = u64;
       a.phase_general = A.B[2] != 0.0;
     }
     a.tile_y = A.st.tile_y;

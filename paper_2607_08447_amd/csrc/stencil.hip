@@ -13,18 +13,17 @@
 //            and Zeeman (a constant 6x6, evaluated in closed form)
 // with L = g1+4g2, M = g1-2g2, N = 6 g3.
 //
-// Kernel design (gfx950): a workgroup owns a 64 x TY tile of (x, y) columns of
-// one vector and marches along z.  Each plane (with a one-point halo ring) is
-// staged through LDS once; every thread reads its 19-point neighbourhood from
-// LDS and "pushes" the plane's contributions into three register accumulators
-// for the output planes z-1, z and z+1.  The x-z and y-z edge couplings of a
-// plane therefore need only that plane's x/y neighbours, so one plane of LDS
-// per vector suffices.  Planes are double-buffered in LDS: the next plane is
-// loaded into the other buffer while the current one is read (one barrier
-// per plane), so HBM loads of one wave overlap the arithmetic of the others.  Output plane z-1
-// is complete after plane z has been pushed and is written straight to HBM
-// (alpha, beta and the old block fused in).  Workgroups are mapped to XCDs in
-// contiguous runs so that the vectors of one tile share an L2.
+// Kernel design (gfx950): a workgroup owns a tile of (x, y) columns of one vector
+// and marches along z.  Each plane (with a one-point halo ring) is staged through
+// LDS once; every thread reads its 19-point neighbourhood from LDS and "pushes" the
+// plane's contributions into three register accumulators for the output planes z-1,
+// z and z+1.  The x-z and y-z edge couplings of a plane therefore need only that
+// plane's x/y neighbours, so one plane of LDS per vector suffices.  Planes are
+// double-buffered in LDS (one barrier per plane).  Output plane z-1 is complete after
+// plane z has been pushed and is written straight to memory (alpha, beta and the old
+// block fused in).  Workgroups are mapped to XCDs in contiguous runs so that the
+// vectors of one tile share an L2.  Two ways of staging a plane: copies of whole rows
+// (stencil_kernel) and through registers (stencil_pipe_kernel); launch_t chooses.
 #include <map>
 #include <mutex>
 #include <type_traits>
@@ -48,8 +47,9 @@ struct KArgs {
   long long out_bstride;
   const T* D;
   long long D_bstride;
-  const T* wtab;
-  const T* vtab;
+  const T* ptab;   // [nz][kFoldRow] complex: folded phases per plane (field on)
+  const double* ptab64;   // the same in double, and [nx] complex the y-links' phase along x
+  const double* utab64;   // (Bz != 0)
   const double* coef;
   int coef_stride;
   double alpha, shift, beta;
@@ -57,35 +57,346 @@ struct KArgs {
   const int* lock;
   const int* work;
   int batch;
-  int zsplit, split_below;
+  int zsplit, split_below, fill;
   int nx, ny, nz, nvec;
   int tiles_x, tiles_y;
   int vgroup;   // vectors of one tile run side by side (1: vector-major)
   StencilConsts<T> k;
 };
 
-// DMA = true (tiles full along x): the 64 interior elements of every halo-tile
-// row go global -> LDS directly (global_load_lds, no registers), issued one
-// plane ahead and waited for at the end of the step; the two x-halo columns
-// use ordinary loads.
+// Which (member, vector, tile, z range) this workgroup works on; false: none.
+// Workgroup order: groups of vgroup vectors; inside a group the vectors of
+// one tile are adjacent (they share the tile's on-site fields in L2) and the
+// tiles follow each other (neighbouring tiles march z side by side on one XCD,
+// so the halo rows they share hit in L2).  vgroup = 1 is vector-major order,
+// vgroup = nvec tile-major order.  With a work table the order runs over the
+// live (virtual) vectors of all members and the rest of the grid exits.
+// Launches with few live workgroups (locked vectors, converged members,
+// small grids) split every (vector, tile) into zs z-ranges so that more
+// workgroups share the chip; a range recomputes one plane on each side.
+// The grid holds zsplit x the unsplit count; the split is decided from the
+// live count, uniformly for the whole launch: in two below split_below live
+// workgroups, and on in halves while the doubled count stays within `fill`.
+struct Place {
+  int b, vec, tile, zs, zc;
+};
+template <typename T>
+__device__ __forceinline__ bool find_place(const KArgs<T>& a, Place* p) {
+  const int ntiles = a.tiles_x * a.tiles_y;
+  const int nlw = a.work ? a.work[a.batch] * ntiles : (int)gridDim.x / a.zsplit;
+  int zs = 1;
+  if (a.zsplit > 1 && nlw < a.split_below && a.nz >= 8) {
+    zs = 2;
+    while (2 * zs <= a.zsplit && 2 * zs * nlw <= a.fill && a.nz >= 4 * zs) zs *= 2;
+  }
+  const int nlive = nlw * zs;
+  if ((int)blockIdx.x >= nlive) return false;
+  int logical = xcd_remap(blockIdx.x, nlive);
+  p->zs = zs;
+  p->zc = logical / nlw;   // z range outermost: one range of all tiles per XCD run
+  logical -= p->zc * nlw;
+  if (a.work) {
+    const int nv = a.work[a.batch];
+    const int g = logical / (a.vgroup * ntiles);
+    const int within = logical - g * a.vgroup * ntiles;
+    const int gsize = min(a.vgroup, nv - g * a.vgroup);
+    p->tile = within / gsize;
+    const int u = g * a.vgroup + (within - p->tile * gsize);
+    int b = 0;
+    while (a.work[b + 1] <= u) ++b;
+    p->b = b;
+    p->vec = (a.lock ? a.lock[b] : 0) + (u - a.work[b]);
+    return true;
+  }
+  const int per_b = ntiles * a.nvec;
+  p->b = logical / per_b;
+  const int r = logical - p->b * per_b;
+  const int g = r / (a.vgroup * ntiles);
+  const int within = r - g * a.vgroup * ntiles;
+  const int gsize = min(a.vgroup, a.nvec - g * a.vgroup);
+  p->tile = within / gsize;
+  p->vec = g * a.vgroup + (within - p->tile * gsize);
+  if (a.active && !a.active[p->b]) return false;
+  return !(a.lock && p->vec < a.lock[p->b]);   // converged vectors are not filtered
+}
+
+// (in scalar registers, so that everything derived from it is uniform to the compiler)
+template <typename T>
+__device__ __forceinline__ bool place_workgroup(const KArgs<T>& a, Place* p) {
+  if (!find_place(a, p)) return false;
+  p->b = __builtin_amdgcn_readfirstlane(p->b);
+  p->vec = __builtin_amdgcn_readfirstlane(p->vec);
+  p->tile = __builtin_amdgcn_readfirstlane(p->tile);
+  p->zs = __builtin_amdgcn_readfirstlane(p->zs);
+  p->zc = __builtin_amdgcn_readfirstlane(p->zc);
+  return true;
+}
+
+// the coefficients alpha, shift, beta of this launch's step for member b
+template <typename T>
+__device__ __forceinline__ void step_coef(const KArgs<T>& a, int b, T* alpha, T* shift, T* beta) {
+  if (a.coef) {
+    const double* c = a.coef + (long long)b * a.coef_stride;
+    *alpha = (T)c[0];
+    *shift = (T)c[1];
+    *beta = (T)c[2];
+  } else {
+    *alpha = (T)a.alpha;
+    *shift = (T)a.shift;
+    *beta = (T)a.beta;
+  }
+}
+
+// barrier for LDS traffic alone: global loads and stores stay in flight across it
+// (__syncthreads would wait for every store to reach memory)
+__device__ __forceinline__ void lds_barrier() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#endif
+}
+
+// waves per SIMD that the register budget is held to: FP32 four (128 registers; the
+// general phases' recurrence step would spill: three), FP64 two
+template <typename T>
+constexpr int pipe_waves(int ph, bool old, int ty) {
+  return sizeof(T) == 4 && ty > 1 ? (ph == 2 && old ? 3 : 4) : 2;
+}
+
+// Register-staged march.  A tile is TX x (64 / TX x TY) columns: a wave covers 64 / TX
+// rows of TX columns of one spin, so grids that 64-wide tiles would pad (nx = 96, 75)
+// keep their lanes busy.  Plane z + 2 is loaded into registers while plane z is
+// computed, and written to LDS one step later.  One wait per step, at its top, covers
+// every load issued a whole step before (that plane, the on-site fields, the old
+// block) and the stores of the step before it; then come this step's stores and
+// loads, then the arithmetic.  Nothing that was just issued is waited for, and the
+// barrier at the end waits for LDS alone.
+// A lane's offsets are 32-bit bytes from a uniform base; TY = 1 (nx beyond 2^22) takes
+// 64-bit ones.
+template <typename T, typename TO, typename TW, int PH, bool STR, int TX, int TY, int NC = 6>
+__global__ void __launch_bounds__(64 * TY * (NC / 3), pipe_waves<T>(PH, !std::is_same<TO, void>::value, TY))
+stencil_pipe_kernel(KArgs<T> a) {
+  static_assert(NC == 6 || (NC == 3 && PH == 0), "spin-free vectors carry no field terms");
+  constexpr bool kWide = TY == 1;
+  constexpr int RH = (64 / TX) * TY;        // rows of the tile
+  constexpr int W = TX + 2, ROWS = RH + 2;
+  constexpr int PLANE = W * ROWS;
+  constexpr int NT = 64 * TY * (NC / 3);
+  constexpr int NS = (PLANE + NT - 1) / NT;
+  constexpr int BUF = NC * PLANE;
+  constexpr bool kOld = !std::is_same<TO, void>::value;
+  using TOv = std::conditional_t<kOld, TO, T>;
+  __shared__ cx<T> lds[2 * BUF];
+
+  Place pl;
+  if (!place_workgroup(a, &pl)) return;
+  const int nx = a.nx, ny = a.ny, nz = a.nz;
+  const int tx0 = (pl.tile % a.tiles_x) * TX, ty0 = (pl.tile / a.tiles_x) * RH;
+  // output planes [o0, o1) of this range; input planes p0..p1 feed them
+  const int o0 = (pl.zc * nz) / pl.zs, o1 = ((pl.zc + 1) * nz) / pl.zs;
+  const int p0 = o0 > 0 ? o0 - 1 : 0, p1 = o1 < nz ? o1 : nz - 1;
+  const unsigned nxy = (unsigned)nx * (unsigned)ny;
+  const unsigned N = nxy * (unsigned)nz;   // 6 N < 2^31 (checked on the host)
+  const int lane = threadIdx.x;
+  const int lx = lane & (TX - 1), ly = threadIdx.y * (64 / TX) + lane / TX;
+  // the spin is uniform across a wave (64 consecutive threads share threadIdx.z)
+  const int sp = __builtin_amdgcn_readfirstlane(threadIdx.z);
+  const int tid = lane + 64 * ((int)threadIdx.y + TY * sp);
+  const int gx = tx0 + lx, gy = ty0 + ly;
+  const bool mine = gx < nx && gy < ny;
+  const int X = 3 * sp, F = 3 - X;      // own and flipped-spin component offsets
+
+  T alpha, shift, beta;
+  step_coef(a, pl.b, &alpha, &shift, &beta);
+  const bool has_old = kOld && a.old != nullptr && beta != (T)0;
+
+  // bases at this tile's first row (uniform); lane offsets in bytes from there
+  const size_t row0 = (size_t)ty0 * nx;
+  const long long vb = (long long)pl.vec * NC * N;
+  const T* in = a.in + 2 * ((long long)pl.b * a.in_bstride + vb);
+  // (without an old block its loads read the block's first entry and are not used)
+  const TOv* oldp = has_old ? reinterpret_cast<const TOv*>(a.old) +
+                                  2 * ((long long)pl.b * a.old_bstride + vb + (long long)X * N + row0)
+                            : reinterpret_cast<const TOv*>(a.in);
+  const unsigned oldN = has_old ? N : 0u, oldxy = has_old ? nxy : 0u;
+  TW* outp = reinterpret_cast<TW*>(a.out) +
+             2 * ((long long)pl.b * a.out_bstride + vb + (long long)X * N + row0);
+  const T* D = a.D + (long long)pl.b * a.D_bstride + row0;
+  using Off = std::conditional_t<kWide, size_t, unsigned>;
+  // base + a lane's offset; the empty statement keeps the offset's extension to 64 bits
+  // beside the access, where it folds into the instruction's address
+  auto ptr = [](auto* base, Off bytes) {
+    using P = std::conditional_t<std::is_const<std::remove_pointer_t<decltype(base)>>::value,
+                                 const char*, char*>;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(bytes));
+#endif
+    return reinterpret_cast<decltype(base)>(reinterpret_cast<P>(base) + bytes);
+  };
+  const StencilConsts<T> k = a.k;
+  const T dgs = sp == 0 ? k.dgU : k.dgD;
+  const T ax = sp == 0 ? k.aUx : k.aDx, ay = sp == 0 ? k.aUy : k.aDy,
+          az = sp == 0 ? k.aUz : k.aDz;
+  const T sd3 = sp == 0 ? -k.d3 : k.d3;   // sign of the d3 f_Z and f_X spin-flip terms
+  const T sby = sp == 0 ? -k.by : k.by;   // (bx -+ i by)
+
+  // halo-tile slots this thread stages (a slot outside the grid loads the tile's first
+  // column and stores zero); offsets are from the tile's first row or the row above it
+  const int up = ty0 > 0 ? 1 : 0;
+  const T* inr = in + 2 * (row0 - (size_t)(up * nx));
+  Off soff[NS];
+  int sidx[NS];
+  bool sval[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int slot = tid + s * NT;
+    const int row = slot / W, colx = slot - row * W;
+    const int x = tx0 + colx - 1, y = ty0 + row - 1;
+    sval[s] = slot < PLANE && x >= 0 && x < nx && y >= 0 && y < ny;
+    soff[s] = sval[s] ? (Off)((Off)(row - 1 + up) * (Off)nx + (Off)x) * (Off)sizeof(cx<T>)
+                      : (Off)tx0 * (Off)sizeof(cx<T>);
+    sidx[s] = slot < PLANE ? slot : -1;
+  }
+  const Off col = mine ? (Off)ly * (Off)nx + (Off)gx : (Off)tx0;
+  const Off colT = col * (Off)sizeof(T), colO = has_old ? col * (Off)sizeof(cx<TOv>) : (Off)0,
+            colW = col * (Off)sizeof(cx<TW>);
+  const int lb = (ly + 1) * W + (lx + 1);   // this thread's centre in an LDS plane
+  cx<double> ux = mk<double>(1, 0);
+  if constexpr (PH == 2) ux = ld(a.utab64 + 2 * (gx < nx ? gx : nx - 1));
+
+  constexpr int ND = STR ? 6 : 1;
+  struct Set {          // what a step needs besides the plane: loaded one step ahead
+    T d[ND];            // on-site fields of the plane (d00 d11 d22 d12 d02 d01, or V)
+    cx<TOv> old[3];     // old block of the plane before it
+  };
+  // a plane's offset, kept out of the compiler's induction variables so that every
+  // access stays a uniform base plus a 32-bit lane offset
+  auto plane = [&](int z, unsigned stride) -> size_t {
+    return (size_t)(unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)z * stride));
+  };
+  cx<T> R[NS][NC];
+  auto fetch = [&](int z) {
+    const T* q = inr + 2 * plane(z, nxy);
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) R[s][c] = ld(ptr(q + 2 * (size_t)((unsigned)c * N), soff[s]));
+  };
+  auto commit = [&](int z) {
+    cx<T>* dst = lds + (z & 1) * BUF;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      if (PLANE % NT != 0 && sidx[s] < 0) continue;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        dst[c * PLANE + sidx[s]] = sval[s] ? R[s][c] : mk<T>(0, 0);
+    }
+  };
+  auto load_fields = [&](int z, Set& t) {
+    const T* q = D + plane(z, nxy);
+#pragma unroll
+    for (int i = 0; i < ND; ++i) t.d[i] = *ptr(q + (size_t)i * N, colT);
+  };
+  auto load_old = [&](int z, Set& t) {
+    if constexpr (kOld) {
+      const TOv* q = oldp + 2 * plane(z, oldxy);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) t.old[i] = ld_stream(ptr(q + 2 * (size_t)(i * oldN), colO));
+    }
+  };
+  cx<T> acc0[3], acc1[3], res[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) acc0[i] = acc1[i] = res[i] = mk<T>(0, 0);
+  auto store = [&](int z) {
+    if (!mine) return;
+    TW* q = outp + 2 * plane(z, nxy);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) stg_stream<TW>(ptr(q + 2 * (size_t)i * N, colW), 0, res[i]);
+  };
+  auto finish = [&](const Set& t) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      res[i] = scl(alpha, acc0[i]);
+      if constexpr (kOld)
+        if (has_old) res[i] = fma_s(res[i], beta, mk<T>((T)t.old[i].r, (T)t.old[i].i));
+    }
+  };
+
+  // step z: plane z + 1 to LDS, the finished plane z - 2 to memory, then the loads for
+  // step z + 1 and beyond, then plane z (which completes plane z - 1)
+  auto step = [&](int z, const Set& cur, Set& nxt) {
+    commit(z + 1);
+    if (z - 2 >= o0) store(z - 2);
+    fetch(z + 2 < p1 ? z + 2 : p1);
+    load_fields(z + 1 < nz ? z + 1 : z, nxt);
+    load_old(z < o1 ? (z > o0 ? z : o0) : o1 - 1, nxt);
+    const Fold<T> f = load_fold<T, PH>(a.ptab, a.ptab64, z, ux);
+    const T d00 = cur.d[0], d11 = cur.d[STR ? 1 : 0], d22 = cur.d[STR ? 2 : 0];
+    const T d12 = STR ? cur.d[STR ? 3 : 0] : (T)0;
+    const T d02 = STR ? cur.d[STR ? 4 : 0] : (T)0;
+    const T d01 = STR ? cur.d[STR ? 5 : 0] : (T)0;
+    cx<T> acc2[3];
+    push_plane<T, PH, STR, NC, PLANE, W>(lds + (z & 1) * BUF + lb, X, F, k, dgs, ax, ay, az, sd3,
+                                         sby, shift, f, d00, d11, d22, d12, d02, d01, acc0, acc1,
+                                         acc2);
+    finish(cur);
+    settle(acc1);
+    settle(acc2);
+    settle(res);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      acc0[i] = acc1[i];
+      acc1[i] = acc2[i];
+    }
+    lds_barrier();
+  };
+
+  Set A, B;
+  fetch(p0);
+  load_fields(p0, A);
+  load_old(o0, A);
+  commit(p0);
+  fetch(p0 < p1 ? p0 + 1 : p1);
+  lds_barrier();
+  int z = p0;
+  for (; z + 1 <= p1; z += 2) {
+    step(z, A, B);
+    step(z + 1, B, A);
+  }
+  if (z <= p1) {
+    step(z, A, B);
+    A = B;
+    ++z;
+  }
+  // z = p1 + 1: plane z - 2 is in res; with p1 the grid's last plane (o1 = nz), plane
+  // z - 1 has no successor to complete it
+  if (z - 2 >= o0) store(z - 2);
+  if (o1 == nz) {
+    finish(A);
+    store(nz - 1);
+  }
+}
+
+// Row-copy march, for grids of whole 64-wide tiles: the 64 interior elements of every
+// halo-tile row go global -> LDS directly (global_load_lds, no registers), issued one
+// plane ahead and waited for at the end of the step; the two x-halo columns use
+// ordinary loads.
 // NC = 6: the full spinor (a wave per spin and row).  NC = 3: a spin-free orbital
 // vector (X, Y, Z of one spin; no spin-orbit or field terms, so nothing couples
 // it to the other spin): one wave per row and half the bytes.
 // (FP32 steps without an old block are held to 128 VGPRs: four waves per SIMD)
-template <typename T, typename TO, typename TW, int PH, bool STR, int TY, bool DMA, int NC = 6>
+template <typename T, typename TO, typename TW, int PH, bool STR, int TY, int NC = 6>
 __global__ void __launch_bounds__(64 * TY * (NC / 3),
                                   (sizeof(T) == 4 && std::is_same<TO, void>::value && TY >= 2) ? 4 : 1)
 stencil_kernel(KArgs<T> a) {
   static_assert(NC == 6 || (NC == 3 && PH == 0), "spin-free vectors carry no field terms");
-  // LDS row: [pad] left halo, 64 interior, right halo [pad]; with FP32 DMA the
-  // interior starts on a 16-byte boundary (column 2 of a 68-wide row)
-  constexpr int C0 = (DMA && sizeof(T) == 4) ? 2 : 1;   // column of x = tx0
-  constexpr int W = (DMA && sizeof(T) == 4) ? 68 : 66;
+  // LDS row: [pad] left halo, 64 interior, right halo [pad]; in FP32 the interior
+  // starts on a 16-byte boundary (column 2 of a 68-wide row)
+  constexpr int C0 = sizeof(T) == 4 ? 2 : 1;   // column of x = tx0
+  constexpr int W = sizeof(T) == 4 ? 68 : 66;
   constexpr int ROWS = TY + 2;
   constexpr int SLOTS = W * ROWS;
   constexpr int PLANE = SLOTS;        // elements per (buffer, component) plane
   constexpr int NT = 64 * TY * (NC / 3);   // (x, y, spin) threads
-  constexpr int NS = (SLOTS + NT - 1) / NT;
   // double-buffered plane: [component][row][col] each (two distinct arrays, so the
   // compiler can tell the buffer being read from the one being filled)
   __shared__ cx<T> lds0[NC * PLANE];
@@ -94,55 +405,9 @@ stencil_kernel(KArgs<T> a) {
     if constexpr (decltype(BUF)::value == 0) return lds0; else return lds1;
   };
 
-  const int ntiles = a.tiles_x * a.tiles_y;
-  // Workgroup order: groups of vgroup vectors; inside a group the vectors of
-  // one tile are adjacent (they share the tile's on-site fields in L2) and the
-  // tiles follow each other (neighbouring tiles march z side by side on one XCD,
-  // so the halo rows they share hit in L2).  vgroup = 1 is vector-major order,
-  // vgroup = nvec tile-major order.  With a work table the order runs over the
-  // live (virtual) vectors of all members and the rest of the grid exits.
-  // Launches with few live workgroups (locked vectors, converged members,
-  // small grids) split every (vector, tile) into zs z-ranges so that more
-  // workgroups share the chip; a range recomputes one plane on each side.
-  // The grid holds zsplit x the unsplit count; the split is decided from the
-  // live count, uniformly for the whole launch.
-  int b, vec, tile, zs = 1, zc = 0;
-  if (a.work) {
-    const int nv = a.work[a.batch];
-    const int nlw = nv * ntiles;
-    if (a.zsplit > 1 && nlw < a.split_below && a.nz >= 8) zs = a.zsplit;
-    const int nlive = nlw * zs;
-    if ((int)blockIdx.x >= nlive) return;
-    int logical = xcd_remap(blockIdx.x, nlive);
-    zc = logical / nlw;   // z range outermost: one range of all tiles per XCD run
-    logical -= zc * nlw;
-    const int g = logical / (a.vgroup * ntiles);
-    const int within = logical - g * a.vgroup * ntiles;
-    const int gsize = min(a.vgroup, nv - g * a.vgroup);
-    tile = within / gsize;
-    const int u = g * a.vgroup + (within - tile * gsize);
-    b = 0;
-    while (a.work[b + 1] <= u) ++b;
-    vec = (a.lock ? a.lock[b] : 0) + (u - a.work[b]);
-  } else {
-    const int nlw = (int)gridDim.x / a.zsplit;
-    if (a.zsplit > 1 && nlw < a.split_below && a.nz >= 8) zs = a.zsplit;
-    const int nlive = nlw * zs;
-    if ((int)blockIdx.x >= nlive) return;
-    int logical = xcd_remap(blockIdx.x, nlive);
-    zc = logical / nlw;
-    logical -= zc * nlw;
-    const int per_b = ntiles * a.nvec;
-    b = logical / per_b;
-    const int r = logical - b * per_b;
-    const int g = r / (a.vgroup * ntiles);
-    const int within = r - g * a.vgroup * ntiles;
-    const int gsize = min(a.vgroup, a.nvec - g * a.vgroup);
-    tile = within / gsize;
-    vec = g * a.vgroup + (within - tile * gsize);
-    if (a.active && !a.active[b]) return;
-    if (a.lock && vec < a.lock[b]) return;   // converged vectors are not filtered
-  }
+  Place pl;
+  if (!place_workgroup(a, &pl)) return;
+  const int b = pl.b, vec = pl.vec, tile = pl.tile, zs = pl.zs, zc = pl.zc;
   const int tx0 = (tile % a.tiles_x) * 64;
   const int ty0 = (tile / a.tiles_x) * TY;
 
@@ -161,16 +426,7 @@ stencil_kernel(KArgs<T> a) {
   const int X = 3 * sp, F = 3 - X;      // own and flipped-spin component offsets
 
   T alpha, shift, beta;
-  if (a.coef) {
-    const double* c = a.coef + (long long)b * a.coef_stride;
-    alpha = (T)c[0];
-    shift = (T)c[1];
-    beta = (T)c[2];
-  } else {
-    alpha = (T)a.alpha;
-    shift = (T)a.shift;
-    beta = (T)a.beta;
-  }
+  step_coef(a, b, &alpha, &shift, &beta);
   // TO = void: a launch without an old block (a step of the product-form filter,
   // or H X), compiled without its loads
   constexpr bool kOld = !std::is_same<TO, void>::value;
@@ -195,23 +451,6 @@ stencil_kernel(KArgs<T> a) {
   const T sd3 = sp == 0 ? -k.d3 : k.d3;   // sign of the d3 f_Z and f_X spin-flip terms
   const T sby = sp == 0 ? -k.by : k.by;   // (bx -+ i by)
 
-  // halo-tile slots this thread loads (clamped offset + mask; waves whose
-  // slots are all inside the grid skip the mask)
-  unsigned soff[NS];
-  int sidx[NS];
-  bool sval[NS], sin_[NS], wmask[NS];
-#pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    const int slot = tid + s * NT;
-    sin_[s] = slot < SLOTS;
-    const int row = slot / W, colx = slot % W;
-    const int x = tx0 + colx - C0, y = ty0 + row - 1;
-    sval[s] = sin_[s] && x >= 0 && x < nx && y >= 0 && y < ny;
-    soff[s] = sval[s] ? (unsigned)(y * nx + x) : 0u;
-    sidx[s] = sin_[s] ? slot : 0;
-    wmask[s] = !__all(sval[s] || !sin_[s]);
-  }
-
   const unsigned col = mine ? (unsigned)(gy * nx + gx) : 0u;
   const int gxc = gx < nx ? gx : nx - 1;
   const int lb = (ly + 1) * W + (lx + C0);   // this thread's centre in an LDS plane
@@ -220,32 +459,7 @@ stencil_kernel(KArgs<T> a) {
 #pragma unroll
   for (int i = 0; i < 3; ++i) acc0[i] = acc1[i] = oldv[i] = mk<T>(0, 0);
 
-  // next plane: loads issued before the current plane is computed, written to
-  // the other LDS buffer after it (the wave's own arithmetic hides the latency)
-  auto fetch = [&](int z, cx<T> (&v)[NS][NC]) {
-    const unsigned zo = (unsigned)z * nxy;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      if (NS * NT > SLOTS && !sin_[s]) continue;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) v[s][c] = ld(in + 2 * (size_t)((unsigned)c * N + zo + soff[s]));
-    }
-  };
-  auto commit = [&](cx<T> (&v)[NS][NC], auto BUF) {
-    cx<T>* dst = bufp(BUF);
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      if (NS * NT > SLOTS && !sin_[s]) continue;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        cx<T> x = v[s][c];
-        if (wmask[s] && !sval[s]) x = mk<T>(0, 0);
-        dst[c * PLANE + sidx[s]] = x;
-      }
-    }
-  };
-
-  // ---- DMA staging: row loads spread over the workgroup's waves
+  // row copies spread over the workgroup's waves
   constexpr int NW = TY * (NC / 3);
   const int wave = __builtin_amdgcn_readfirstlane(ly + TY * sp);
   auto dma_plane = [&](int z, auto BUF) {
@@ -299,26 +513,8 @@ stencil_kernel(KArgs<T> a) {
     }
   };
 
-  // link phases (GPU gauge) as a rolling window over planes z-1, z, z+1,
-  // loaded one plane ahead: x-links per plane (w), y-links per (plane, column)
-  // (v; with Bz = 0, PH == 1, uniform over the plane); PH == 2 also needs the
-  // y-links of the neighbouring columns in plane z (vx+, vx-)
-  const int xc = PH == 2 ? gxc : 0;
-  const int xcp = gxc + 1 < nx ? gxc + 1 : gxc, xcm = gxc > 0 ? gxc - 1 : 0;
-  cx<T> pw[3], pv[3], pvxp, pvxm;
-  if constexpr (PH != 0) {
-    const int zm = p0 > 0 ? p0 - 1 : 0, z1 = p0 + 1 < nz ? p0 + 1 : nz - 1;
-    pw[0] = ld(a.wtab + 2 * zm);
-    pw[1] = ld(a.wtab + 2 * p0);
-    pw[2] = ld(a.wtab + 2 * z1);
-    pv[0] = ld(a.vtab + 2 * (zm * nx + xc));
-    pv[1] = ld(a.vtab + 2 * (p0 * nx + xc));
-    pv[2] = ld(a.vtab + 2 * (z1 * nx + xc));
-    if constexpr (PH == 2) {
-      pvxp = ld(a.vtab + 2 * (p0 * nx + xcp));
-      pvxm = ld(a.vtab + 2 * (p0 * nx + xcm));
-    }
-  }
+  cx<double> ux = mk<double>(1, 0);
+  if constexpr (PH == 2) ux = ld(a.utab64 + 2 * gxc);
 
   // on-site fields of this column, loaded one plane ahead (d00 d11 d22 d12 d02 d01;
   // without strain only the first)
@@ -334,40 +530,17 @@ stencil_kernel(KArgs<T> a) {
   auto step = [&](int z, auto BUF) {
     constexpr int cur = decltype(BUF)::value;
     // loads in the order they are needed (the memory counter retires them in
-    // order): next plane's phases, this plane's on-site fields, the old block
-    // for the output plane, the next plane's halo, the next plane's rows
-    cx<T> nw, nv, nvxp, nvxm;
-    if constexpr (PH != 0) {
-      const int z2 = z + 2 < nz ? z + 2 : nz - 1, z1 = z + 1 < nz ? z + 1 : nz - 1;
-      nw = ld(a.wtab + 2 * z2);
-      nv = ld(a.vtab + 2 * (z2 * nx + xc));
-      if constexpr (PH == 2) {
-        nvxp = ld(a.vtab + 2 * (z1 * nx + xcp));
-        nvxm = ld(a.vtab + 2 * (z1 * nx + xcm));
-      }
-    }
-    // the next plane goes to the other buffer while this one is read; the
-    // barrier at the end of the step publishes it and retires this buffer
-    // FP32: loads of the next plane issued before the arithmetic and written to
-    // LDS after it (latency hidden by this wave's own work); FP64 writes them
-    // at once (its register budget is already exhausted by the arithmetic)
-    constexpr bool late = sizeof(T) == 4;
+    // order): the next plane's on-site fields, the old block for the output plane,
+    // the next plane's halo, the next plane's rows (into the buffer that is not being
+    // read; the barrier at the end of the step publishes it and retires this one)
     T nd[ND];
     load_d(z + 1 < nz ? z + 1 : z, nd);
     if (z - 1 >= o0) load_old(z - 1);
-    cx<T> nxt[DMA ? 1 : NS][NC];
     cx<T> hv = mk<T>(0, 0);
     const bool more = z + 1 <= p1;
-    if constexpr (!DMA) {
-      if (more) {
-        fetch(z + 1, nxt);
-        if constexpr (!late) commit(nxt, IC<1 - cur>{});
-      }
-    } else {
-      if (more) {
-        hv = halo_load(z + 1);
-        dma_plane(z + 1, IC<1 - cur>{});
-      }
+    if (more) {
+      hv = halo_load(z + 1);
+      dma_plane(z + 1, IC<1 - cur>{});
     }
     // (indices stay inside cd for ND = 1; the strain terms are then zero)
     const T d00 = cd[0], d11 = cd[STR ? 1 : 0], d22 = cd[STR ? 2 : 0];
@@ -376,9 +549,9 @@ stencil_kernel(KArgs<T> a) {
     const T d01 = STR ? cd[STR ? 5 : 0] : (T)0;
     const cx<T>* L = bufp(IC<cur>{}) + lb;
     cx<T> acc2[3];
-    push_plane<T, PH, STR, NC, PLANE, W>(L, X, F, k, dgs, ax, ay, az, sd3, sby, shift, pw, pv,
-                                         pvxp, pvxm, d00, d11, d22, d12, d02, d01, acc0, acc1,
-                                         acc2);
+    const Fold<T> f = load_fold<T, PH>(a.ptab, a.ptab64, z, ux);
+    push_plane<T, PH, STR, NC, PLANE, W>(L, X, F, k, dgs, ax, ay, az, sd3, sby, shift, f, d00,
+                                         d11, d22, d12, d02, d01, acc0, acc1, acc2);
 
     // the output plane's stores (and the wait for the old block, which the
     // compiler extends to every load in flight, the next plane's copy included)
@@ -386,11 +559,7 @@ stencil_kernel(KArgs<T> a) {
     settle(acc1);
     settle(acc2);
     if (z - 1 >= o0) finalize(z - 1);
-    if constexpr (DMA) {
-      if (more) halo_commit(hv, IC<1 - cur>{});
-    } else if constexpr (late) {
-      if (more) commit(nxt, IC<1 - cur>{});
-    }
+    if (more) halo_commit(hv, IC<1 - cur>{});
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
       acc0[i] = acc1[i];
@@ -398,35 +567,17 @@ stencil_kernel(KArgs<T> a) {
     }
 #pragma unroll
     for (int i = 0; i < ND; ++i) cd[i] = nd[i];
-    if constexpr (PH != 0) {
-      pw[0] = pw[1];
-      pw[1] = pw[2];
-      pw[2] = nw;
-      pv[0] = pv[1];
-      pv[1] = pv[2];
-      pv[2] = nv;
-      if constexpr (PH == 2) {
-        pvxp = nvxp;
-        pvxm = nvxm;
-      }
-    }
     __syncthreads();
   };
 
-  if constexpr (DMA) {
-    // rows outside the grid are never loaded: zero both buffers once
-    for (int i = tid; i < NC * PLANE; i += NT) {
-      lds0[i] = mk<T>(0, 0);
-      lds1[i] = mk<T>(0, 0);
-    }
-    __syncthreads();
-    halo_commit(halo_load(p0), IC<0>{});
-    dma_plane(p0, IC<0>{});
-  } else {
-    cx<T> first[NS][NC];
-    fetch(p0, first);
-    commit(first, IC<0>{});
+  // rows outside the grid are never loaded: zero both buffers once
+  for (int i = tid; i < NC * PLANE; i += NT) {
+    lds0[i] = mk<T>(0, 0);
+    lds1[i] = mk<T>(0, 0);
   }
+  __syncthreads();
+  halo_commit(halo_load(p0), IC<0>{});
+  dma_plane(p0, IC<0>{});
   __syncthreads();
   for (int z = p0; z <= p1; z += 2) {
     step(z, IC<0>{});
@@ -471,8 +622,9 @@ hipError_t launch_t(const StencilLaunch& L, const StencilConsts<double>& c, hipS
   a.out_bstride = L.out_bstride;
   a.D = reinterpret_cast<const T*>(L.D);
   a.D_bstride = L.D_bstride;
-  a.wtab = reinterpret_cast<const T*>(L.wtab);
-  a.vtab = reinterpret_cast<const T*>(L.vtab);
+  a.ptab = reinterpret_cast<const T*>(L.ptab);
+  a.ptab64 = L.ptab64;
+  a.utab64 = L.utab64;
   a.coef = L.coef.coef;
   a.coef_stride = L.coef.stride;
   a.alpha = L.coef.alpha;
@@ -489,43 +641,58 @@ hipError_t launch_t(const StencilLaunch& L, const StencilConsts<double>& c, hipS
   a.vgroup = L.vgroup < 1 ? 1 : (L.vgroup > L.nvec ? L.nvec : L.vgroup);
   a.k = cast_consts<T>(c);
   const int ty = L.tile_y;
-  a.tiles_x = (L.nx + 63) / 64;
-  a.tiles_y = (L.ny + ty - 1) / ty;
-  const long long nwg = (long long)a.tiles_x * a.tiles_y * L.nvec * L.batch;
-  if (nwg <= 0) return hipSuccess;
-  // z split: 0 never, 1 when fewer live workgroups than three resident waves,
-  // 2 always (tests)
-  a.zsplit = L.zsplit > 0 ? 2 : 1;
-  if (nwg * a.zsplit > 0x7fffffffLL) return hipErrorInvalidValue;
-  dim3 grid((unsigned)(nwg * a.zsplit));
-  auto go = [&](auto kernel, dim3 block) {
-    a.split_below = L.zsplit >= 2 ? 0x7fffffff
-                  : (L.zsplit == 1 ? 3 * resident_workgroups(kernel, (int)(block.x * block.y * block.z)) : 0);
-    kernel<<<grid, block, 0, s>>>(a);
-  };
   constexpr unsigned NSP = NC / 3;   // spin waves per row
-  if (L.dma && L.nx % 64 == 0) {
+  auto go = [&](auto kernel, int tx, int rows, int waves) {
+    a.tiles_x = (L.nx + tx - 1) / tx;
+    a.tiles_y = (L.ny + rows - 1) / rows;
+    const long long nwg = (long long)a.tiles_x * a.tiles_y * L.nvec * L.batch;
+    if (nwg <= 0) return hipSuccess;
+    // z split: 0 never, 1 when fewer live workgroups than three resident waves of
+    // them (further while they still fit at once), 2 always in two (tests)
+    const int threads = 64 * waves * (int)NSP;
+    const int resident = L.zsplit == 1 ? resident_workgroups(kernel, threads) : 0;
+    a.zsplit = L.zsplit > 0 ? 2 : 1;
+    while (L.zsplit == 1 && a.zsplit < 16 && 2 * a.zsplit * nwg <= resident) a.zsplit *= 2;
+    if (nwg * a.zsplit > 0x7fffffffLL) return hipErrorInvalidValue;
+    a.split_below = L.zsplit >= 2 ? 0x7fffffff : 3 * resident;
+    a.fill = resident;
+    kernel<<<dim3((unsigned)(nwg * a.zsplit)), dim3(64, waves, NSP), 0, s>>>(a);
+    return hipGetLastError();
+  };
+  // Row copies or register staging.  Whole 64-wide tiles with an old block copy rows
+  // (FP64 recurrence step, 40 vectors of 128 x 40 x 40: 475 us, staged 504; FP32 both
+  // 250-253).  Without an old block staging is at least as fast in FP32 (16 vectors of
+  // 256 x 48 x 48: 220 us, copied 227; 4 vectors 43 and 53); in FP64 and for spin-free
+  // vectors the copy stays ahead by 1-3% (1057 and 1081 us, 40 vectors).  Any other nx
+  // is staged: 32-wide tiles keep the lanes that 64-wide ones pad away (FP32 product
+  // step, 40 vectors of 96 x 32 x 32: 66 us, 64-wide staged 100; 75 x 31 x 29: 77 and
+  // 98), 16-wide ones only where a 32-wide tile would be half empty.
+  constexpr bool copy = !std::is_same<TO, void>::value || sizeof(T) == 8 || NC == 3;
+  if (copy && L.dma && L.nx % 64 == 0) {
     switch (ty) {
-      case 1: go(stencil_kernel<T, TO, TW, PH, STR, 1, true, NC>, dim3(64, 1, NSP)); break;
-      case 2: go(stencil_kernel<T, TO, TW, PH, STR, 2, true, NC>, dim3(64, 2, NSP)); break;
-      case 4: go(stencil_kernel<T, TO, TW, PH, STR, 4, true, NC>, dim3(64, 4, NSP)); break;
+      case 1: return go(stencil_kernel<T, TO, TW, PH, STR, 1, NC>, 64, 1, 1);
+      case 2: return go(stencil_kernel<T, TO, TW, PH, STR, 2, NC>, 64, 2, 2);
+      case 4: return go(stencil_kernel<T, TO, TW, PH, STR, 4, NC>, 64, 4, 4);
       default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
   }
-  switch (ty) {
-    case 1: go(stencil_kernel<T, TO, TW, PH, STR, 1, false, NC>, dim3(64, 1, NSP)); break;
-    case 2: go(stencil_kernel<T, TO, TW, PH, STR, 2, false, NC>, dim3(64, 2, NSP)); break;
-    case 4: go(stencil_kernel<T, TO, TW, PH, STR, 4, false, NC>, dim3(64, 4, NSP)); break;
+  // one row and 64-bit lane offsets where a lane's 32-bit byte offset could overflow
+  // (tile rows x nx x 16 bytes)
+  const int waves = L.nx > (1 << 22) ? 1 : ty;
+  switch (waves) {
+    case 1: return go(stencil_pipe_kernel<T, TO, TW, PH, STR, 64, 1, NC>, 64, 1, 1);
+    case 2:
+      return L.nx <= 16 ? go(stencil_pipe_kernel<T, TO, TW, PH, STR, 16, 2, NC>, 16, 8, 2)
+                        : go(stencil_pipe_kernel<T, TO, TW, PH, STR, 32, 2, NC>, 32, 4, 2);
+    case 4: return go(stencil_pipe_kernel<T, TO, TW, PH, STR, 32, 4, NC>, 32, 8, 4);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 template <typename T, typename TO, typename TW>
 hipError_t launch_ph(const StencilLaunch& L, const StencilConsts<double>& c, hipStream_t s) {
   // 0: no field; 1: Bz = 0 (all link phases uniform over a z-plane); 2: general
-  const int ph = L.wtab == nullptr ? 0 : (L.phase_general ? 2 : 1);
+  const int ph = L.ptab == nullptr ? 0 : (L.phase_general ? 2 : 1);
   if (L.ncomp == 3) {   // spin-free orbital vectors: zero field only
     if (ph != 0) return hipErrorInvalidValue;
     return L.strain ? launch_t<T, TO, TW, 0, true, 3>(L, c, s)

@@ -44,8 +44,7 @@ struct K2Args {
   const float* D;
   long long D_bstride;
   const float* zero;   // 16 bytes of zeros in device memory (the wall's values)
-  const float* wtab;   // [nz] x-link phases (complex)
-  const float* vtab;   // [nz][nx] y-link phases (complex; uniform over x here)
+  const float* ptab;   // [nz][kFoldRow] folded link phases (complex)
   const double* coef1;   // per member [alpha, shift, beta] of the first step, or null:
   const double* coef2;   // the host values below; and of the second
   int coef_stride;
@@ -212,22 +211,8 @@ stencil2_kernel(K2Args a) {
 #pragma unroll
     for (int i = 0; i < ND; ++i) d[i] = D[(unsigned)i * N + pz];
   };
-  auto wph = [&](int z) { return ld(a.wtab + 2 * (z < 0 ? 0 : (z >= nz ? nz - 1 : z))); };
-  auto vph = [&](int z) {
-    return ld(a.vtab + 2 * (size_t)((z < 0 ? 0 : (z >= nz ? nz - 1 : z)) * nx));
-  };
-  // step one pushes Y0 plane z, step two Y1 plane z - 2: windows of planes
-  // (z-1, z, z+1) and (z-3, z-2, z-1) at iteration z
-  cx<T> pw1[3], pv1[3], pw2[3], pv2[3];
   const cx<T> zero = mk<T>(0, 0);
-#pragma unroll
-  for (int i = 0; i < 3; ++i) pw1[i] = pv1[i] = pw2[i] = pv2[i] = zero;
-  if constexpr (PH != 0) {
-    pw1[0] = wph(-1); pw1[1] = wph(0); pw1[2] = wph(1);
-    pv1[0] = vph(-1); pv1[1] = vph(0); pv1[2] = vph(1);
-    pw2[0] = wph(-3); pw2[1] = wph(-2); pw2[2] = wph(-1);
-    pv2[0] = vph(-3); pv2[1] = vph(-2); pv2[2] = vph(-1);
-  }
+  const cx<double> one = mk<double>(1, 0);
 
   // accumulators of Y1 planes z-1, z, z+1 (acc) and of Y2 planes z-3, z-2,
   // z-1 (bcc); this column's Y0 of planes z-3, z-2, z-1 for the beta term of Y2
@@ -253,19 +238,12 @@ stencil2_kernel(K2Args a) {
     constexpr int cur = decltype(BUF)::value;
     // loads in the order they are needed (the memory counter retires them in
     // order, so a wait for an early load does not wait for the copy of the next
-    // plane): fields and phases for the next iteration, the old block for
+    // plane): fields for the next iteration, the old block for
     // Y1(z-1) (column 0 for threads off the grid: no branch), then the next
     // Y0 plane's rows into the other buffer
     T n1[ND], n2[ND];
     load_d(z + 1 < nz ? z + 1 : nz - 1, col1, n1);
     load_d(z - 1 < 0 ? 0 : (z - 1 < nz ? z - 1 : nz - 1), col2, n2);
-    cx<T> nw1 = zero, nv1 = zero, nw2 = zero, nv2 = zero;
-    if constexpr (PH != 0) {
-      nw1 = wph(z + 2);
-      nv1 = vph(z + 2);
-      nw2 = wph(z);
-      nv2 = vph(z);
-    }
     {   // read even when beta1 == 0 (a valid block; the value is then unused)
       const int zo = z - 1 < 0 ? 0 : (z - 1 < nz ? z - 1 : nz - 1);
       const unsigned o = (unsigned)zo * nxy + col1;
@@ -282,8 +260,8 @@ stencil2_kernel(K2Args a) {
       const T d12 = STR ? d1[STR ? 3 : 0] : (T)0;
       const T d02 = STR ? d1[STR ? 4 : 0] : (T)0;
       const T d01 = STR ? d1[STR ? 5 : 0] : (T)0;
-      push_plane<T, PH, STR, 6, IPL, IW>(L, X, F, k, dgs, ax, ay, az, sd3, sby, shift1, pw1,
-                                         pv1, zero, zero, d00, d11, d22, d12, d02, d01, acc0,
+      push_plane<T, PH, STR, 6, IPL, IW>(L, X, F, k, dgs, ax, ay, az, sd3, sby, shift1,
+                                         (load_fold<T, PH>(a.ptab, nullptr, z, one)), d00, d11, d22, d12, d02, d01, acc0,
                                          acc1, acc2);
     }
     // this thread's tile column of Y0 plane z (own spin), for Y2's beta term
@@ -301,8 +279,8 @@ stencil2_kernel(K2Args a) {
       const T d12 = STR ? d2[STR ? 3 : 0] : (T)0;
       const T d02 = STR ? d2[STR ? 4 : 0] : (T)0;
       const T d01 = STR ? d2[STR ? 5 : 0] : (T)0;
-      push_plane<T, PH, STR, 6, EPL, EW>(L, X, F, k, dgs, ax, ay, az, sd3, sby, shift2, pw2,
-                                         pv2, zero, zero, d00, d11, d22, d12, d02, d01, bcc0,
+      push_plane<T, PH, STR, 6, EPL, EW>(L, X, F, k, dgs, ax, ay, az, sd3, sby, shift2,
+                                         (load_fold<T, PH>(a.ptab, nullptr, z - 2, one)), d00, d11, d22, d12, d02, d01, bcc0,
                                          bcc1, bcc2);
     }
     // both steps' arithmetic is done before the stores below: their wait for the
@@ -361,12 +339,6 @@ stencil2_kernel(K2Args a) {
       d1[i] = n1[i];
       d2[i] = n2[i];
     }
-    if constexpr (PH != 0) {
-      pw1[0] = pw1[1]; pw1[1] = pw1[2]; pw1[2] = nw1;
-      pv1[0] = pv1[1]; pv1[1] = pv1[2]; pv1[2] = nv1;
-      pw2[0] = pw2[1]; pw2[1] = pw2[2]; pw2[2] = nw2;
-      pv2[0] = pv2[1]; pv2[1] = pv2[2]; pv2[2] = nv2;
-    }
     __syncthreads();   // next Y0 plane copied; Y1 plane z - 1 published; buffers retired
   };
 
@@ -415,8 +387,7 @@ hipError_t launch_stencil2(const Stencil2Launch& L, const StencilConsts<double>&
   a.D = static_cast<const float*>(L.D);
   a.D_bstride = L.D_bstride;
   a.zero = static_cast<const float*>(L.zero);
-  a.wtab = static_cast<const float*>(L.wtab);
-  a.vtab = static_cast<const float*>(L.vtab);
+  a.ptab = static_cast<const float*>(L.ptab);
   a.coef1 = L.coef1;
   a.coef2 = L.coef2;
   a.coef_stride = L.coef_stride;
@@ -432,7 +403,7 @@ hipError_t launch_stencil2(const Stencil2Launch& L, const StencilConsts<double>&
   a.tiles_y = (L.ny + L.tile_y - 1) / L.tile_y;
   a.vgroup = L.vgroup < 1 ? 1 : (L.vgroup > L.nvec ? L.nvec : L.vgroup);
   a.k = cast_consts<float>(c);
-  const bool field = L.wtab != nullptr;
+  const bool field = L.ptab != nullptr;
   if (field) return L.strain ? launch_ts<1, true>(a, L.tile_x, L.tile_y, s)
                              : launch_ts<1, false>(a, L.tile_x, L.tile_y, s);
   return L.strain ? launch_ts<0, true>(a, L.tile_x, L.tile_y, s)

@@ -117,43 +117,105 @@ struct IC {
   static constexpr int value = V;
 };
 
+// acc + c a, acc + conj(c) a
+template <typename T>
+__device__ __forceinline__ cx<T> mac(cx<T> acc, cx<T> c, cx<T> a) {
+  return {fma(-c.i, a.i, fma(c.r, a.r, acc.r)), fma(c.i, a.r, fma(c.r, a.i, acc.i))};
+}
+template <typename T>
+__device__ __forceinline__ cx<T> mac_conj(cx<T> acc, cx<T> c, cx<T> a) {
+  return {fma(c.i, a.i, fma(c.r, a.r, acc.r)), fma(-c.i, a.r, fma(c.r, a.i, acc.i))};
+}
+
+// The link phases of one plane folded with the stencil coefficients (w, v: x- and
+// y-link phases; m, 0, p: planes z-1, z, z+1):
+//   xo, xa   x faces of the other two orbitals and of |X>:  cM w0, (cLM + cM) w0
+//   yo, ya   y faces of the others and of |Y>:              cM v0, (cLM + cM) v0
+//   e0..e3   x-y corners: the sum is e0 f++ + conj(e1) f-- + e2 f+- + conj(e3) f-+
+//            (f by the signs of dx, dy); uniform phases have e1 = e0, e3 = e2
+//   cu, cd   x-z edges pushed to z-1 and z+1:  cN8 (wm + w0), -cN8 (wp + w0)
+//   du, dd   y-z edges:                        cN8 (vm + v0), -cN8 (vp + v0)
+template <typename T>
+struct Fold {
+  cx<T> xo, xa, yo, ya, e0, e1, e2, e3, cu, cd, du, dd;
+};
+
+template <typename T>
+using Const = const __attribute__((address_space(4))) T;   // uniform tables: scalar loads
+
+// The folded phases of plane z from the table (kFoldRow complex entries a plane, in
+// the order of Fold; see launch_phase_tables); where Bz != 0 this column's, with u its
+// phase along x: those products are formed in double from the double table, so an
+// FP32 constant is rounded once.  One scalar load per plane in place of about 40 vector operations
+// per wave and plane to fold them (a sixth of the plane's arithmetic).
+template <typename T, int PH>
+__device__ __forceinline__ Fold<T> load_fold(const T* ptab, const double* ptab64, int z,
+                                             cx<double> u) {
+  Fold<T> f;
+  if constexpr (PH != 0) {
+    Const<T>* t = (Const<T>*)ptab + 2 * kFoldRow * z;
+    auto at = [&](int i) { return mk<T>(t[2 * i], t[2 * i + 1]); };
+    f.xo = at(0);
+    f.xa = at(1);
+    f.yo = at(2);
+    f.ya = at(3);
+    f.e0 = at(4);
+    f.e1 = at(5);
+    f.e2 = at(6);
+    f.e3 = at(7);
+    f.cu = at(8);
+    f.cd = at(9);
+    f.du = at(10);
+    f.dd = at(11);
+    if constexpr (PH == 2) {
+      Const<double>* t64 = (Const<double>*)ptab64 + 2 * kFoldRow * z;
+      auto by = [&](cx<double> ph, int i) {
+        const cx<double> r = mul(ph, mk<double>(t64[2 * i], t64[2 * i + 1]));
+        return mk<T>((T)r.r, (T)r.i);
+      };
+      const cx<double> uc = conj(u);
+      f.yo = by(u, 2);
+      f.ya = by(u, 3);
+      f.e0 = by(u, 4);
+      f.e1 = by(u, 5);
+      f.e2 = by(uc, 6);
+      f.e3 = by(uc, 7);
+      f.du = by(u, 10);
+      f.dd = by(u, 11);
+    }
+  }
+  return f;
+}
+
 // Contributions of one input plane z of one spin's three orbital components
 // (this thread's column; the plane sits in LDS as [component][row][column] with
 // plane stride PLANE and row width W, L pointing at this column's centre) to
 // the output planes z-1 (added to acc0), z (added to acc1) and z+1 (written to
 // acc2).  X / F: component offsets of this thread's spin and of the other one.
-// pw, pv: x- and y-link phases of planes z-1, z, z+1; pvxp, pvxm: the y-links of
-// the neighbouring columns in plane z (PH == 2).  d..: the on-site orbital block
-// of this column at plane z.  In-plane terms (faces, x-y edges, on-site,
-// spin-orbit and Zeeman) go to plane z; the z faces and the x-z / y-z edges of
-// the plane are pushed to z-1 and z+1.
+// f: the plane's folded phases (PH != 0; this column's where Bz != 0, PH == 2).
+// d..: the on-site orbital block of this column at plane z.  In-plane terms (faces,
+// x-y edges, on-site, spin-orbit and Zeeman) go to plane z; the z faces and the
+// x-z / y-z edges of the plane are pushed to z-1 and z+1.
 template <typename T, int PH, bool STR, int NC, int PLANE, int W>
 __device__ __forceinline__ void push_plane(
     const cx<T>* L, int X, int F, const StencilConsts<T>& k, T dgs, T ax, T ay, T az, T sd3,
-    T sby, T shift, const cx<T> (&pw)[3], const cx<T> (&pv)[3], cx<T> pvxp, cx<T> pvxm,
+    T sby, T shift, const Fold<T>& f,
     T d00, T d11, T d22, T d12, T d02, T d01, cx<T> (&acc0)[3], cx<T> (&acc1)[3],
     cx<T> (&acc2)[3]) {
   auto at = [&](int c, int dy, int dx) { return L[c * PLANE + dy * W + dx]; };
-
-  // ---- phases (GPU gauge): x-links per plane, y-links per (plane, column);
-  // with Bz = 0 (PH == 1) every phase is uniform over the plane
-  const cx<T> wm = pw[0], w0 = pw[1], wp = pw[2], vm = pv[0], v0 = pv[1], vp = pv[2];
-  const cx<T> vxp = pvxp, vxm = pvxm;
 
   {
     // faces in the plane (this spin's three orbitals); the coefficient of the
     // x faces is (L-M) + M on |X> and M on |Y>, |Z> (y faces: on |Y> and the
     // others), folded with the link phase into one complex constant per plane
-    const T cLMM = k.cLM + k.cM;
     if constexpr (PH != 0) {
-      const cx<T> cx_o = scl(k.cM, w0), cx_a = scl(cLMM, w0);
-      const cx<T> cy_o = scl(k.cM, v0), cy_a = scl(cLMM, v0);
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
-        acc1[i] = wsum_acc(acc1[i], i == 0 ? cx_a : cx_o, at(X + i, 0, 1), at(X + i, 0, -1));
-        acc1[i] = wsum_acc(acc1[i], i == 1 ? cy_a : cy_o, at(X + i, 1, 0), at(X + i, -1, 0));
+        acc1[i] = wsum_acc(acc1[i], i == 0 ? f.xa : f.xo, at(X + i, 0, 1), at(X + i, 0, -1));
+        acc1[i] = wsum_acc(acc1[i], i == 1 ? f.ya : f.yo, at(X + i, 1, 0), at(X + i, -1, 0));
       }
     } else {
+      const T cLMM = k.cLM + k.cM;
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
         const cx<T> sx = add(at(X + i, 0, 1), at(X + i, 0, -1));
@@ -170,23 +232,13 @@ __device__ __forceinline__ void push_plane(
     const cx<T> fX_pp = at(X, 1, 1), fX_pm = at(X, -1, 1);
     const cx<T> fX_mp = at(X, 1, -1), fX_mm = at(X, -1, -1);
     if constexpr (PH == 2) {
-      // P(sx, sy) = w^sx [ v(x+sx)^sy + v(x)^sy ]
-      const cx<T> ppp = mul(w0, add(vxp, v0));
-      const cx<T> ppm = mul(w0, conj(add(vxp, v0)));
-      const cx<T> pmp = mul(conj(w0), add(vxm, v0));
-      const cx<T> pmm = mul(conj(w0), conj(add(vxm, v0)));
-      cx<T> eY = sub(add(mul(ppp, fY_pp), mul(pmm, fY_mm)), add(mul(ppm, fY_pm), mul(pmp, fY_mp)));
-      cx<T> eX = sub(add(mul(ppp, fX_pp), mul(pmm, fX_mm)), add(mul(ppm, fX_pm), mul(pmp, fX_mp)));
-      acc1[0] = fma_s(acc1[0], k.cN8, eY);
-      acc1[1] = fma_s(acc1[1], k.cN8, eX);
+      acc1[0] = mac_conj(mac(acc1[0], f.e0, fY_pp), f.e1, fY_mm);
+      acc1[0] = mac_conj(mac(acc1[0], f.e2, fY_pm), f.e3, fY_mp);
+      acc1[1] = mac_conj(mac(acc1[1], f.e0, fX_pp), f.e1, fX_mm);
+      acc1[1] = mac_conj(mac(acc1[1], f.e2, fX_pm), f.e3, fX_mp);
     } else if constexpr (PH == 1) {
-      // uniform phases: P(sx, sy) = 2 w^sx v^sy, so the corner sum is
-      // q f++ + conj(q) f-- - (p f+- + conj(p) f-+) with q = 2 cN8 w v and
-      // p = 2 cN8 w conj(v) (f indexed by the signs of dx, dy)
-      const T c2 = k.cN8 + k.cN8;
-      const cx<T> q = scl(c2, mul(w0, v0)), mp = scl(-c2, mul(w0, conj(v0)));
-      acc1[0] = wsum_acc(wsum_acc(acc1[0], q, fY_pp, fY_mm), mp, fY_pm, fY_mp);
-      acc1[1] = wsum_acc(wsum_acc(acc1[1], q, fX_pp, fX_mm), mp, fX_pm, fX_mp);
+      acc1[0] = wsum_acc(wsum_acc(acc1[0], f.e0, fY_pp, fY_mm), f.e2, fY_pm, fY_mp);
+      acc1[1] = wsum_acc(wsum_acc(acc1[1], f.e0, fX_pp, fX_mm), f.e2, fX_pm, fX_mp);
     } else {
       cx<T> eY = sub(add(fY_pp, fY_mm), add(fY_pm, fY_mp));
       cx<T> eX = sub(add(fX_pp, fX_mm), add(fX_pm, fX_mp));
@@ -210,15 +262,12 @@ __device__ __forceinline__ void push_plane(
     const cx<T> ypZ = at(X + 2, 1, 0), ymZ = at(X + 2, -1, 0);
     const cx<T> ypY = at(X + 1, 1, 0), ymY = at(X + 1, -1, 0);
     if constexpr (PH != 0) {
-      // path-averaged phases (x2) times +-cN8, one complex constant each
-      const cx<T> cu = scl(k.cN8, add(wm, w0)), cd = scl(-k.cN8, add(wp, w0));
-      const cx<T> du = scl(k.cN8, add(vm, v0)), dd = scl(-k.cN8, add(vp, v0));
-      acc0[0] = wdiff_acc(acc0[0], cu, xpZ, xmZ);
-      acc0[2] = wdiff_acc(wdiff_acc(acc0[2], cu, xpX, xmX), du, ypY, ymY);
-      acc0[1] = wdiff_acc(acc0[1], du, ypZ, ymZ);
-      acc2[0] = wdiff_acc(acc2[0], cd, xpZ, xmZ);
-      acc2[2] = wdiff_acc(wdiff_acc(acc2[2], cd, xpX, xmX), dd, ypY, ymY);
-      acc2[1] = wdiff_acc(acc2[1], dd, ypZ, ymZ);
+      acc0[0] = wdiff_acc(acc0[0], f.cu, xpZ, xmZ);
+      acc0[2] = wdiff_acc(wdiff_acc(acc0[2], f.cu, xpX, xmX), f.du, ypY, ymY);
+      acc0[1] = wdiff_acc(acc0[1], f.du, ypZ, ymZ);
+      acc2[0] = wdiff_acc(acc2[0], f.cd, xpZ, xmZ);
+      acc2[2] = wdiff_acc(wdiff_acc(acc2[2], f.cd, xpX, xmX), f.dd, ypY, ymY);
+      acc2[1] = wdiff_acc(acc2[1], f.dd, ypZ, ymZ);
     } else {
       const T c2 = k.cN8 + k.cN8;
       const cx<T> dxZ = sub(xpZ, xmZ), dxX = sub(xpX, xmX);
