@@ -110,12 +110,12 @@ __global__ void phase_kernel(int nx, int nz, double h, double Bx, double By, dou
     const double2 e = expi(kh * Bz * h);
     const double2 ep = make_double2(1.0 + e.x, e.y), em = make_double2(1.0 + e.x, -e.y);
     const double2 wv = mul(w0, v0), wvc = mul(w0, make_double2(v0.x, -v0.y));
-    const double cLMM = k.cLM + k.cM, n8 = k.cN8;
+    const double cLMM = k.cLM + k.cM, n8 = k.cN8, ne = Bz != 0.0 ? 1.0 : n8;
     auto s = [](double a, double2 b) { return make_double2(a * b.x, a * b.y); };
     auto add = [](double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); };
     const double2 row[kFoldRow] = {
         s(k.cM, w0), s(cLMM, w0), s(k.cM, v0), s(cLMM, v0),
-        s(n8, mul(wv, ep)), s(n8, mul(wv, em)), s(-n8, mul(wvc, em)), s(-n8, mul(wvc, ep)),
+        s(ne, mul(wv, ep)), s(ne, mul(wv, em)), s(-ne, mul(wvc, em)), s(-ne, mul(wvc, ep)),
         s(n8, add(wm, w0)), s(-n8, add(wp, w0)), s(n8, add(vm, v0)), s(-n8, add(vp, v0))};
     for (int i = 0; i < kFoldRow; ++i) {
       const size_t o = 2 * ((size_t)t * kFoldRow + i);

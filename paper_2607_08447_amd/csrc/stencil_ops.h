@@ -132,7 +132,9 @@ __device__ __forceinline__ cx<T> mac_conj(cx<T> acc, cx<T> c, cx<T> a) {
 //   xo, xa   x faces of the other two orbitals and of |X>:  cM w0, (cLM + cM) w0
 //   yo, ya   y faces of the others and of |Y>:              cM v0, (cLM + cM) v0
 //   e0..e3   x-y corners: the sum is e0 f++ + conj(e1) f-- + e2 f+- + conj(e3) f-+
-//            (f by the signs of dx, dy); uniform phases have e1 = e0, e3 = e2
+//            (f by the signs of dx, dy); uniform phases have e1 = e0, e3 = e2.  With
+//            Bz != 0 they are the bare phases and the sum is scaled by cN8: as numbers
+//            near 2 their FP32 roundings agree, and cancel between the corners
 //   cu, cd   x-z edges pushed to z-1 and z+1:  cN8 (wm + w0), -cN8 (wp + w0)
 //   du, dd   y-z edges:                        cN8 (vm + v0), -cN8 (vp + v0)
 template <typename T>
@@ -232,10 +234,12 @@ __device__ __forceinline__ void push_plane(
     const cx<T> fX_pp = at(X, 1, 1), fX_pm = at(X, -1, 1);
     const cx<T> fX_mp = at(X, 1, -1), fX_mm = at(X, -1, -1);
     if constexpr (PH == 2) {
-      acc1[0] = mac_conj(mac(acc1[0], f.e0, fY_pp), f.e1, fY_mm);
-      acc1[0] = mac_conj(mac(acc1[0], f.e2, fY_pm), f.e3, fY_mp);
-      acc1[1] = mac_conj(mac(acc1[1], f.e0, fX_pp), f.e1, fX_mm);
-      acc1[1] = mac_conj(mac(acc1[1], f.e2, fX_pm), f.e3, fX_mp);
+      const cx<T> eY = mac_conj(mac(mac_conj(mul(f.e0, fY_pp), f.e1, fY_mm), f.e2, fY_pm), f.e3,
+                                fY_mp);
+      const cx<T> eX = mac_conj(mac(mac_conj(mul(f.e0, fX_pp), f.e1, fX_mm), f.e2, fX_pm), f.e3,
+                                fX_mp);
+      acc1[0] = fma_s(acc1[0], k.cN8, eY);
+      acc1[1] = fma_s(acc1[1], k.cN8, eX);
     } else if constexpr (PH == 1) {
       acc1[0] = wsum_acc(wsum_acc(acc1[0], f.e0, fY_pp, fY_mm), f.e2, fY_pm, fY_mp);
       acc1[1] = wsum_acc(wsum_acc(acc1[1], f.e0, fX_pp, fX_mm), f.e2, fX_pm, fX_mp);
