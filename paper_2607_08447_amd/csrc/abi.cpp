@@ -230,7 +230,6 @@ int solve_common(const hkp_grid* grid, const hkp_material* mat, const hkp_opts* 
   a.flags = opts->flags;
   a.seed = opts->seed;
   a.st = autotuned(*grid, p.nb, p.mixed, stencil_variant(strain != nullptr, B));
-  a.graph_chunk = 4;
   return guarded([&]() { return run_solve(a, stats); });
 }
 

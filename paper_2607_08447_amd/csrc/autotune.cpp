@@ -103,7 +103,6 @@ int run_autotune_block(const hkp_grid& g, const hkp_material& mat, const hkp_opt
     a.flags = oc.flags;
     a.seed = oc.seed;
     a.st = autotuned(g, oc.nb, oc.precision == HKP_PREC_MIXED, stencil_variant(strain != nullptr, B));
-    a.graph_chunk = 4;
     const auto t0 = std::chrono::steady_clock::now();
     const int rc = run_solve(a, nullptr);
     const double s = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -323,7 +322,6 @@ int run_autotune(const hkp_grid& g, int nb, bool mixed, bool strain, int field, 
   void* ut = take((size_t)g.nx * 16);
   void* X = take((size_t)nb * n6 * esz);
   void* O = take((size_t)nb * n6 * esz);
-  void* Y = O;   // the solver's filter writes over the block it reads as Y_old
   // contents do not affect the timing; give them finite values
   if (hipMemsetAsync(p, 0, off, s) != hipSuccess) return HKP_E_HIP;
   hkp_material m;
@@ -337,6 +335,7 @@ int run_autotune(const hkp_grid& g, int nb, bool mixed, bool strain, int field, 
   StencilTune best;
   double best_us = 1e300;
   const char* dbg = std::getenv("HKP_TUNE_TRACE");
+  const int group = filter_group(nb, (size_t)n6 * esz);
   std::vector<int> groups;   // 1 (vector-major), 2, 4, nb (tile-major)
   for (int vg : {1, 2, 4, nb})
     if (vg <= nb && std::find(groups.begin(), groups.end(), vg) == groups.end()) groups.push_back(vg);
@@ -351,10 +350,7 @@ int run_autotune(const hkp_grid& g, int nb, bool mixed, bool strain, int field, 
     a.nz = g.nz;
     a.nvec = nb;
     a.batch = 1;
-    a.in = X;
-    a.old = O;
     a.old_fp64 = !mixed;
-    a.out = Y;
     a.out_fp64 = !mixed;
     a.D = D;
     a.strain = strain;
@@ -369,15 +365,31 @@ int run_autotune(const hkp_grid& g, int nb, bool mixed, bool strain, int field, 
     a.vgroup = vg;
     a.dma = dma;
     a.fp64 = !mixed;
-    if (launch_stencil(a, c, s) != hipSuccess) continue;   // warm-up
+    // as a filter runs: all steps on one group of vectors, its two blocks taking turns
     const int reps = 5;
-    (void)hipEventRecord(e0, s);
-    for (int r = 0; r < reps; ++r) (void)launch_stencil(a, c, s);
-    (void)hipEventRecord(e1, s);
-    (void)hipEventSynchronize(e1);
-    float ms = 0;
-    (void)hipEventElapsedTime(&ms, e0, e1);
-    const double us = 1e3 * ms / reps;
+    double us = 0;
+    bool ok = true;
+    for (int v0 = 0; v0 < nb && ok; v0 += group) {
+      const size_t off_v = (size_t)v0 * n6 * esz;
+      char *in = (char*)X + off_v, *out = (char*)O + off_v;
+      a.nvec = std::min(group, nb - v0);
+      auto step = [&]() {
+        a.in = in;
+        a.old = a.out = out;
+        std::swap(in, out);
+        return launch_stencil(a, c, s) == hipSuccess;
+      };
+      ok = step() && step();   // warm-up
+      if (!ok) break;
+      (void)hipEventRecord(e0, s);
+      for (int r = 0; r < reps; ++r) (void)step();
+      (void)hipEventRecord(e1, s);
+      (void)hipEventSynchronize(e1);
+      float ms = 0;
+      (void)hipEventElapsedTime(&ms, e0, e1);
+      us += 1e3 * ms / reps;
+    }
+    if (!ok) continue;
     if (dbg && dbg[0] == '1')
       std::fprintf(stderr, "[hkp tune] ty %d vgroup %d dma %d: %.1f us\n", ty, vg, dma, us);
     if (us < best_us) {

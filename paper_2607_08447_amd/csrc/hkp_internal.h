@@ -89,6 +89,8 @@ struct StencilLaunch {
                          // (vector lock[b] + i of member b is virtual vector work[b] + i);
                          // the grid covers nvec * batch vectors and only the first
                          // work[batch] are live, spread evenly over the XCDs. Or null.
+  int vfirst = 0;        // one Hamiltonian without a work table: only the vectors
+  int vcount = 0;        // [vfirst, vfirst + vcount) (0: all)
   int tile_y;            // 1, 2, 4: waves of a workgroup per spin
   int vgroup;            // vectors of one tile side by side (1 vector-major, nvec tile-major)
   int dma;               // 1: rows may be staged global -> LDS directly (where nx % 64 == 0)
@@ -99,6 +101,18 @@ struct StencilLaunch {
 
 hipError_t launch_stencil(const StencilLaunch& a, const StencilConsts<double>& c,
                           hipStream_t s);
+
+// The memory-side cache of an MI355X (256 MiB), less what the on-site fields and other
+// traffic take: blocks that a launch leaves within it are read back from it by the next.
+constexpr size_t kCacheBytes = (size_t)232 << 20;
+// Vectors per group of a filter: as many as keep the two blocks of vec_bytes per vector
+// that a filter works on within the cache, in groups of equal size.
+inline int filter_group(int vectors, size_t vec_bytes) {
+  const size_t fit = kCacheBytes / (2 * vec_bytes);
+  if (fit < 1 || vectors < 1) return vectors < 1 ? 1 : vectors;   // nothing to gain: all at once
+  const int groups = (int)((vectors + fit - 1) / fit);
+  return (vectors + groups - 1) / groups;
+}
 
 // Two Chebyshev steps in one pass (FP32): Y1 = alpha1 (H - shift1) Y0 + beta1 Y_old,
 // Y2 = alpha2 (H - shift2) Y1 + beta2 Y0, coefficients per member from the device

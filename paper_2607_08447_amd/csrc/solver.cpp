@@ -152,106 +152,78 @@ void tridiag_extremes(const std::vector<double>& a, const std::vector<double>& b
   *lo = l;
 }
 
-// per-launch accounting of the stencil kernel: algorithmic bytes always,
-// event-timed durations when requested (eager mode)
+// accounting of the stencil kernel: algorithmic bytes always, event-timed durations when
+// requested (eager mode).  A run is a sequence of launches timed together (the steps of
+// one filter): an event around every launch would cost small problems more than the
+// launches.  A step over the live vectors counts as one launch, however many groups of
+// vectors it is split into.
 struct StencilStats {
+  enum Kind { k32 = 0, k64 = 1, k32x2 = 2 };
   bool timed = false;
+  struct Run {
+    int kind;
+    long long n;
+    double bytes;
+  };
   std::vector<hipEvent_t> ev;   // start/stop pairs
-  std::vector<int> kind;        // 0: FP32 stencil, 1: FP64
-  std::vector<double> bytes;
-  size_t used = 0;
-  double hx_bytes = 0, t32 = 0, t64 = 0, b32 = 0, b64 = 0, t32x2 = 0, b32x2 = 0;
-  long long n32 = 0, n64 = 0, n32x2 = 0;
+  std::vector<Run> runs;        // of the pairs in use
+  double hx_bytes = 0, t[3] = {0, 0, 0}, b[3] = {0, 0, 0};
+  long long n[3] = {0, 0, 0};
   ~StencilStats() {
     for (auto e : ev) (void)hipEventDestroy(e);
   }
-  // nvec_done: vectors the launch processes summed over the active members
-  // (< 0: every vector of every active member)
-  void launch(const StencilLaunch& a, const StencilConsts<double>& c, hipStream_t s,
-              long long N, int active_members, double nvec_done = -1) {
-    const double sin = a.fp64 ? 16 : 8;
-    const double sold = a.old ? (a.old_fp64 ? 16 : 8) : 0;
-    const double sout = a.out_fp64 ? 16 : 8;
-    if (nvec_done < 0) nvec_done = (double)active_members * a.nvec;
-    const double b = (double)N * a.ncomp * nvec_done * (sin + sold + sout) +
-                     (double)active_members * N * (a.strain ? 6 : 1) * (a.fp64 ? 8 : 4);
-    hx_bytes += b;
-    if (!timed) {
-      HKP_CHECK(launch_stencil(a, c, s));
-      return;
-    }
-    if (2 * used + 2 > ev.size()) {
+  void begin(hipStream_t s) {
+    if (!timed) return;
+    if (2 * runs.size() + 2 > ev.size()) {
       hipEvent_t e0, e1;
       HKP_CHECK(hipEventCreate(&e0));
-      HKP_CHECK(hipEventCreate(&e1));
       ev.push_back(e0);
+      HKP_CHECK(hipEventCreate(&e1));
       ev.push_back(e1);
-      kind.push_back(0);
-      bytes.push_back(0);
     }
-    HKP_CHECK(hipEventRecord(ev[2 * used], s));
-    HKP_CHECK(launch_stencil(a, c, s));
-    HKP_CHECK(hipEventRecord(ev[2 * used + 1], s));
-    kind[used] = a.fp64 ? 1 : 0;
-    bytes[used] = b;
-    ++used;
+    HKP_CHECK(hipEventRecord(ev[2 * runs.size()], s));
   }
-  // a two-step pass: algorithmic bytes of the two recurrence steps it performs
-  // (each step: its blocks read and written plus the fields, as a one-step pass)
-  void launch2(const Stencil2Launch& a, const StencilConsts<double>& c, hipStream_t s,
-               long long N, int active_members, double nvec_done = -1) {
-    if (nvec_done < 0) nvec_done = (double)active_members * a.nvec;
-    const double b = 2.0 * ((double)N * 6 * nvec_done * 3 * 8 +
-                            (double)active_members * N * (a.strain ? 6 : 1) * 4);
-    hx_bytes += b;
-    if (!timed) {
-      HKP_CHECK(launch_stencil2(a, c, s));
-      return;
-    }
-    if (2 * used + 2 > ev.size()) {
-      hipEvent_t e0, e1;
-      HKP_CHECK(hipEventCreate(&e0));
-      HKP_CHECK(hipEventCreate(&e1));
-      ev.push_back(e0);
-      ev.push_back(e1);
-      kind.push_back(0);
-      bytes.push_back(0);
-    }
-    HKP_CHECK(hipEventRecord(ev[2 * used], s));
-    HKP_CHECK(launch_stencil2(a, c, s));
-    HKP_CHECK(hipEventRecord(ev[2 * used + 1], s));
-    kind[used] = 2;
-    bytes[used] = b;
-    ++used;
+  void end(hipStream_t s, Kind kind, long long launches, double bytes) {
+    hx_bytes += bytes;
+    if (!timed) return;
+    HKP_CHECK(hipEventRecord(ev[2 * runs.size() + 1], s));
+    runs.push_back({kind, launches, bytes});
   }
   void collect() {
-    if (!timed || used == 0) return;
-    HKP_CHECK(hipEventSynchronize(ev[2 * used - 1]));
-    for (size_t i = 0; i < used; ++i) {
+    if (runs.empty()) return;
+    HKP_CHECK(hipEventSynchronize(ev[2 * runs.size() - 1]));
+    for (size_t i = 0; i < runs.size(); ++i) {
       float ms = 0;
       HKP_CHECK(hipEventElapsedTime(&ms, ev[2 * i], ev[2 * i + 1]));
-      if (kind[i] == 2) {
-        t32x2 += ms * 1e-3;
-        b32x2 += bytes[i];
-        ++n32x2;
-      } else if (kind[i]) {
-        t64 += ms * 1e-3;
-        b64 += bytes[i];
-        ++n64;
-      } else {
-        t32 += ms * 1e-3;
-        b32 += bytes[i];
-        ++n32;
-      }
+      t[runs[i].kind] += ms * 1e-3;
+      b[runs[i].kind] += runs[i].bytes;
+      n[runs[i].kind] += runs[i].n;
     }
-    used = 0;
+    runs.clear();
   }
 };
+
+// algorithmic bytes of one step: its blocks over `vectors` vectors and the on-site fields
+// of every active member
+double step_bytes(const StencilLaunch& a, long long N, int active_members, double vectors) {
+  const double sin = a.fp64 ? 16 : 8;
+  const double sold = a.old ? (a.old_fp64 ? 16 : 8) : 0;
+  const double sout = a.out_fp64 ? 16 : 8;
+  return (double)N * a.ncomp * vectors * (sin + sold + sout) +
+         (double)active_members * N * (a.strain ? 6 : 1) * (a.fp64 ? 8 : 4);
+}
 
 struct Ctx {
   StencilStats* ss = nullptr;
   int active_members = 1;   // host view of unconverged Hamiltonians (byte accounting)
-  double filtered_vectors = -1;   // host view of the vectors the filter processes (-1: all)
+  // host view of the vectors that the FP32 and the FP64 filter process (-1: unknown, at
+  // most all)
+  int live32 = -1, live64 = -1;
+  // One Hamiltonian, launched as it goes: the host knows which vectors are live, [locked,
+  // nb), so launches need no work table (a workgroup's walk through it is 2-3 us of
+  // dependent loads before its first plane) and a filter can go through them in groups.
+  bool direct = false;
+  int locked = 0;
   Plan p;
   Layout L;
   char* ws;
@@ -314,9 +286,45 @@ void apply_block(const Ctx& c, size_t x_off, size_t w_off, const int* active) {
   a.out = c.at<double>(w_off);
   a.out_fp64 = 1;
   a.out_bstride = c.bstride();
-  a.active = active;
-  a.work = c.work(2);
-  c.ss->launch(a, c.consts, c.s, c.p.N, c.active_members);
+  if (!c.direct) {
+    a.active = active;
+    a.work = c.work(2);
+  }
+  c.ss->begin(c.s);
+  HKP_CHECK(launch_stencil(a, c.consts, c.s));
+  c.ss->end(c.s, StencilStats::k64, 1,
+            step_bytes(a, c.p.N, c.active_members, (double)c.active_members * c.p.nb));
+}
+
+// The filter's vectors in groups that the memory-side cache holds: f(first, count) for
+// each, all of a filter's steps on one group before the next.  A step's blocks then come
+// from the cache instead of HBM: per point and vector, FP32 recurrence 27 instead of 30
+// ps (40 vectors of 256 x 48 x 48), 25 instead of 30 (24 of 128 x 40 x 40); FP64 51
+// instead of 61.  Not with a work table, whose launches go over all members (count 0):
+// there the groups gained 5% at best (product form, 128 vectors of 96 x 32 x 32) and
+// their launches, in a graph 2 us apart, cost more (342 -> 374 ms a sweep).
+template <typename F>
+void for_groups(const Ctx& c, bool fp64, F f) {
+  if (!c.direct) return f(0, 0);
+  const int total = fp64 ? c.live64 : c.live32;
+  const int g = filter_group(total, (size_t)c.p.n6 * (fp64 ? 16 : 8));
+  for (int v0 = 0; v0 < total; v0 += g) f(v0, std::min(g, total - v0));
+}
+// which vectors a filter's launch covers (first, count as for_groups gives them)
+void cover(const Ctx& c, StencilLaunch& a, const int* active, const int* work, int v0, int vn) {
+  if (c.direct) {
+    a.vfirst = c.locked + v0;
+    a.vcount = vn;
+  } else {
+    a.active = active;
+    a.lock = c.at<int>(c.L.lock);
+    a.work = work;
+  }
+}
+// vectors counted in the byte accounting of a filter
+double counted_vectors(const Ctx& c, bool fp64) {
+  const int live = fp64 ? c.live64 : c.live32;
+  return live >= 0 ? live : (double)c.active_members * c.p.nb;
 }
 
 // The roots of the degree-m Chebyshev polynomial on [-1, 1], cos((2i - 1) pi / 2m),
@@ -365,25 +373,29 @@ void filter64(const Ctx& c, const int* active, int m) {
     a.lock = c.at<int>(c.L.lock);
     HKP_CHECK(launch_stencil(a, c.consts, c.s));
   }
-  size_t cur = c.L.W, oth = c.L.X;
-  for (int k = 1; k < m; ++k) {
-    StencilLaunch a = base_launch(c, true, c.p.nb);
-    a.in = c.at<double>(cur);
-    a.in_bstride = c.bstride();
-    a.old = c.p.product ? nullptr : c.at<double>(oth);
-    a.old_fp64 = 1;
-    a.old_bstride = c.bstride();
-    a.out = c.at<double>(oth);
-    a.out_fp64 = 1;
-    a.out_bstride = c.bstride();
-    a.coef.coef = c.at<double>(c.L.coef) + 4 * k;
-    a.coef.stride = kstride;
-    a.active = active;
-    a.lock = c.at<int>(c.L.lock);
-    a.work = c.work(1);
-    c.ss->launch(a, c.consts, c.s, c.p.N, c.active_members, c.filtered_vectors);
-    std::swap(cur, oth);
-  }
+  double bytes = 0;
+  c.ss->begin(c.s);
+  for_groups(c, true, [&](int v0, int vn) {
+    size_t cur = c.L.W, oth = c.L.X;
+    for (int k = 1; k < m; ++k) {
+      StencilLaunch a = base_launch(c, true, c.p.nb);
+      a.in = c.at<double>(cur);
+      a.in_bstride = c.bstride();
+      a.old = c.p.product ? nullptr : c.at<double>(oth);
+      a.old_fp64 = 1;
+      a.old_bstride = c.bstride();
+      a.out = c.at<double>(oth);
+      a.out_fp64 = 1;
+      a.out_bstride = c.bstride();
+      a.coef.coef = c.at<double>(c.L.coef) + 4 * k;
+      a.coef.stride = kstride;
+      cover(c, a, active, c.work(1), v0, vn);
+      HKP_CHECK(launch_stencil(a, c.consts, c.s));
+      if (v0 == 0) bytes += step_bytes(a, c.p.N, c.active_members, counted_vectors(c, true));
+      std::swap(cur, oth);
+    }
+  });
+  c.ss->end(c.s, StencilStats::k64, m - 1, bytes);
 }
 
 // Chebyshev filter in FP32 (mixed precision): the first step Y1 (FP32, written
@@ -420,81 +432,98 @@ void filter32(const Ctx& c, const int* active, int m) {
     t2.vgroup = c.p.st.vgroup;
     two = stencil2_supported(t2);
   }
+  const double vectors = counted_vectors(c, false);
+  double bytes = 0;
+  auto step = [&](StencilLaunch& a, int k, int v0, int vn) {
+    a.coef.coef = c.at<double>(c.L.coef) + 4 * k;
+    a.coef.stride = kstride;
+    a.in_bstride = a.old_bstride = a.out_bstride = c.bstride();
+    cover(c, a, active, c.work(0), v0, vn);
+    HKP_CHECK(launch_stencil(a, c.consts, c.s));
+    if (v0 == 0) bytes += step_bytes(a, c.p.N, c.active_members, vectors);
+  };
   if (c.p.product) {
     // product form: step k maps Y_k to Y_{k+1} (FP32 buffers in turn), the last
     // step writes FP64 into X
-    float* buf[2] = {A, Bf};
-    int cur = 0;
-    for (int k = 1; k < m; ++k) {
-      const bool last = k == m - 1;
-      StencilLaunch a = base_launch(c, false, c.p.nb);
-      a.in = buf[cur];
-      a.in_bstride = c.bstride();
-      a.out = last ? (void*)c.at<double>(c.L.X) : (void*)buf[1 - cur];
-      a.out_fp64 = last ? 1 : 0;
-      a.out_bstride = c.bstride();
-      a.coef.coef = c.at<double>(c.L.coef) + 4 * k;
-      a.coef.stride = kstride;
-      a.active = active;
-      a.lock = c.at<int>(c.L.lock);
-      a.work = c.work(0);
-      c.ss->launch(a, c.consts, c.s, c.p.N, c.active_members, c.filtered_vectors);
-      cur = 1 - cur;
-    }
+    c.ss->begin(c.s);
+    for_groups(c, false, [&](int v0, int vn) {
+      float* buf[2] = {A, Bf};
+      int cur = 0;
+      for (int k = 1; k < m; ++k) {
+        const bool last = k == m - 1;
+        StencilLaunch a = base_launch(c, false, c.p.nb);
+        a.in = buf[cur];
+        a.out = last ? (void*)c.at<double>(c.L.X) : (void*)buf[1 - cur];
+        a.out_fp64 = last ? 1 : 0;
+        step(a, k, v0, vn);
+        cur = 1 - cur;
+      }
+    });
+    c.ss->end(c.s, StencilStats::k32, m - 1, bytes);
     return;
   }
-  float* spare[2] = {two ? c.at<float>(c.L.C32) : nullptr, two ? c.at<float>(c.L.E32) : nullptr};
   // step k: in = Y_k (FP32), old = Y_{k-1} (X in FP64 for k = 1), out = Y_{k+1}
-  const void* in = A;
-  const void* old = c.at<double>(c.L.X);
-  int old64 = 1;
-  float* free32 = Bf;
-  auto one_step = [&](int k) {
+  struct March {
+    const void *in, *old;
+    int old64;
+  };
+  auto one_step = [&](March& h, int k, int v0, int vn) {
     const bool last = k == m - 1;
     StencilLaunch a = base_launch(c, false, c.p.nb);
-    a.in = in;
-    a.in_bstride = c.bstride();
-    a.old = old;
-    a.old_fp64 = old64;
-    a.old_bstride = c.bstride();
-    void* out = last ? (void*)c.at<double>(c.L.X) : (void*)(old64 ? free32 : (float*)old);
+    a.in = h.in;
+    a.old = h.old;
+    a.old_fp64 = h.old64;
+    void* out = last ? (void*)c.at<double>(c.L.X) : (void*)(h.old64 ? Bf : (float*)h.old);
     a.out = out;
     a.out_fp64 = last ? 1 : 0;
-    a.out_bstride = c.bstride();
-    a.coef.coef = c.at<double>(c.L.coef) + 4 * k;
-    a.coef.stride = kstride;
-    a.active = active;
-    a.lock = c.at<int>(c.L.lock);
-    a.work = c.work(0);
-    c.ss->launch(a, c.consts, c.s, c.p.N, c.active_members, c.filtered_vectors);
-    old = in;
-    old64 = 0;
-    in = out;
+    step(a, k, v0, vn);
+    h = March{out, h.in, 0};
   };
-  int k = 1;
-  if (k < m) one_step(k++);   // reads X (FP64) as Y_0
-  if (two) {
-    // steps 2 .. m-2 in pairs (one step first when their count is odd); a pair
-    // writes the two FP32 blocks it does not read
-    if (((m - 3) & 1) && k < m - 1) one_step(k++);
-    while (k + 1 < m - 1) {
-      t2.in = in;
-      t2.old = old;
-      t2.out1 = spare[0];
-      t2.out2 = spare[1];
-      t2.coef1 = c.at<double>(c.L.coef) + 4 * k;
-      t2.coef2 = c.at<double>(c.L.coef) + 4 * (k + 1);
-      c.ss->launch2(t2, c.consts, c.s, c.p.N, c.active_members, c.filtered_vectors);
-      float* was_in = (float*)in;
-      float* was_old = (float*)old;
-      old = spare[0];
-      in = spare[1];
-      spare[0] = was_in;
-      spare[1] = was_old;
-      k += 2;
-    }
+  const March start{A, c.at<double>(c.L.X), 1};
+  if (!two) {
+    c.ss->begin(c.s);
+    for_groups(c, false, [&](int v0, int vn) {
+      March h = start;
+      for (int k = 1; k < m; ++k) one_step(h, k, v0, vn);
+    });
+    c.ss->end(c.s, StencilStats::k32, m - 1, bytes);
+    return;
   }
-  while (k < m) one_step(k++);
+  // two-step passes over the whole block
+  float* spare[2] = {c.at<float>(c.L.C32), c.at<float>(c.L.E32)};
+  March h = start;
+  int k = 1;
+  auto single = [&]() {
+    bytes = 0;
+    c.ss->begin(c.s);
+    one_step(h, k++, 0, c.direct ? c.live32 : 0);
+    c.ss->end(c.s, StencilStats::k32, 1, bytes);
+  };
+  if (k < m) single();   // reads X (FP64) as Y_0
+  // steps 2 .. m-2 in pairs (one step first when their count is odd); a pair
+  // writes the two FP32 blocks it does not read
+  if (((m - 3) & 1) && k < m - 1) single();
+  while (k + 1 < m - 1) {
+    t2.in = h.in;
+    t2.old = h.old;
+    t2.out1 = spare[0];
+    t2.out2 = spare[1];
+    t2.coef1 = c.at<double>(c.L.coef) + 4 * k;
+    t2.coef2 = c.at<double>(c.L.coef) + 4 * (k + 1);
+    c.ss->begin(c.s);
+    HKP_CHECK(launch_stencil2(t2, c.consts, c.s));
+    // algorithmic bytes of the two steps (each as a one-step pass counts them)
+    c.ss->end(c.s, StencilStats::k32x2, 1,
+              2.0 * ((double)c.p.N * 6 * vectors * 3 * 8 +
+                     (double)c.active_members * c.p.N * (c.strain ? 6 : 1) * 4));
+    float* was_in = (float*)h.in;
+    float* was_old = (float*)h.old;
+    h = March{spare[1], spare[0], 0};
+    spare[0] = was_in;
+    spare[1] = was_old;
+    k += 2;
+  }
+  while (k < m) single();
 }
 
 // SVQB factor of X: S = D U diag(lambda)^-1/2 from X^H X (X S orthonormal) into
@@ -567,6 +596,7 @@ void lanczos_bounds(const Ctx& c, std::vector<double>& bup) {
   HKP_CHECK(launch_dots(v, v, n, B, bs, part, nrm, c.s));
   HKP_CHECK(launch_scale(v, n, B, bs, nrm, c.s));
   const int ksteps = (int)std::min<long long>(kLanczosSteps, std::max<long long>(2, n / 2));
+  double lanczos_bytes = 0;
   for (int j = 0; j < ksteps; ++j) {
     StencilLaunch a = base_launch(c, true, 1);
     a.in = v;
@@ -574,7 +604,8 @@ void lanczos_bounds(const Ctx& c, std::vector<double>& bup) {
     a.out = w;
     a.out_fp64 = 1;
     a.out_bstride = bs;
-    c.ss->launch(a, c.consts, c.s, c.p.N, B);
+    HKP_CHECK(launch_stencil(a, c.consts, c.s));
+    lanczos_bytes += step_bytes(a, c.p.N, B, B);
     double* alj = al + 2LL * j * B;
     HKP_CHECK(launch_dots(v, w, n, B, bs, part, alj, c.s));
     HKP_CHECK(launch_lanczos_update(w, v, j > 0 ? vp : nullptr, n, B, bs, alj,
@@ -587,6 +618,7 @@ void lanczos_bounds(const Ctx& c, std::vector<double>& bup) {
     v = w;
     w = t;
   }
+  c.ss->hx_bytes += lanczos_bytes;
   std::vector<double> hal(2 * (size_t)kLanczosSteps * B), hn(2 * (size_t)(kLanczosSteps + 1) * B);
   HKP_CHECK(hipMemcpyAsync(hal.data(), al, hal.size() * 8, hipMemcpyDeviceToHost, c.s));
   HKP_CHECK(hipMemcpyAsync(hn.data(), nrm, hn.size() * 8, hipMemcpyDeviceToHost, c.s));
@@ -793,6 +825,7 @@ int run_solve(const SolveArgs& A, hkp_stats* stats) {
     HKP_CHECK(launch_random_block(c.at<double>(c.L.X), p.n6, p.nb, p.batch, c.bstride(),
                                   A.seed, c.s));
   }
+  c.direct = p.batch == 1;   // until a recorded iteration begins
   const int* act = c.at<int>(c.L.active);
   // the product form's roots for the next filter's degree (set when it changes)
   int roots_m = 0;
@@ -870,13 +903,14 @@ int run_solve(const SolveArgs& A, hkp_stats* stats) {
   int m_cur = degree_at(1);
   auto count_work = [&]() {
     c.active_members = 0;
-    c.filtered_vectors = 0;
+    c.live32 = c.live64 = 0;
+    c.locked = hflags[6];
     for (int b = 0; b < p.batch; ++b) {
       if (hflags[8 * b]) continue;
       ++c.active_members;
       const int nf = p.nb - hflags[8 * b + 6];   // locked vectors are not filtered
-      c.filtered_vectors += nf;
       const bool f32 = p.mixed && !hflags[8 * b + 1];
+      (f32 ? c.live32 : c.live64) += nf;
       (f32 ? n_hx32 : n_hx64) += (long long)nf * m_cur;
       n_hx64 += p.nb;
     }
@@ -948,42 +982,52 @@ int run_solve(const SolveArgs& A, hkp_stats* stats) {
     }
   }
   if (!eager && iters < A.max_iter && !all_done() && !user_stop) {
-    // record a chunk of iterations once, replay until converged
+    // One iteration is recorded once per combination of filters that the unconverged
+    // members need (FP32, FP64 or both) and replayed until all have converged; the flags
+    // read back after each choose the next.  (Four iterations with both filters in one
+    // graph spent launches on filters no member used and on iterations past the last.)
     m_cur = p.degree;
-    const int chunk = std::max(1, std::min(A.graph_chunk > 0 ? A.graph_chunk : 4, A.max_iter));
     // destroyed on every exit, an error thrown by a replay included
     struct Recorded {
       hipGraph_t graph = nullptr;
       hipGraphExec_t exec = nullptr;
+      double bytes = 0;
       ~Recorded() {
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
       }
-    } rec;
-    // byte accounting of a replay: the recorded chunk with every member active
-    // and no vector locked (an upper estimate; the kernels skip on the device)
-    const double bytes_before = sst.hx_bytes;
-    c.active_members = p.batch;
-    c.filtered_vectors = -1;
-    HKP_CHECK(hipStreamBeginCapture(c.s, hipStreamCaptureModeThreadLocal));
-    try {
-      for (int k = 0; k < chunk; ++k) iteration(-1, false, false, p.degree);
-    } catch (...) {
-      hipGraph_t g2 = nullptr;
-      (void)hipStreamEndCapture(c.s, &g2);
-      if (g2) (void)hipGraphDestroy(g2);
-      throw;
-    }
-    HKP_CHECK(hipStreamEndCapture(c.s, &rec.graph));
-    const double chunk_bytes = sst.hx_bytes - bytes_before;
-    sst.hx_bytes = bytes_before;
-    HKP_CHECK(hipGraphInstantiate(&rec.exec, rec.graph, nullptr, nullptr, 0));
+    } rec[4];
+    auto record = [&](int need, Recorded& r) {
+      // byte accounting of a replay: every member active and no vector locked (an upper
+      // estimate; the kernels skip on the device)
+      const double bytes_before = sst.hx_bytes;
+      const int members = c.active_members;
+      c.active_members = p.batch;
+      c.live32 = c.live64 = -1;
+      c.direct = false;
+      HKP_CHECK(hipStreamBeginCapture(c.s, hipStreamCaptureModeThreadLocal));
+      try {
+        iteration(-1, need != 3, need == 1, p.degree);
+      } catch (...) {
+        hipGraph_t g2 = nullptr;
+        (void)hipStreamEndCapture(c.s, &g2);
+        if (g2) (void)hipGraphDestroy(g2);
+        throw;
+      }
+      HKP_CHECK(hipStreamEndCapture(c.s, &r.graph));
+      r.bytes = sst.hx_bytes - bytes_before;
+      sst.hx_bytes = bytes_before;
+      c.active_members = members;
+      HKP_CHECK(hipGraphInstantiate(&r.exec, r.graph, nullptr, nullptr, 0));
+    };
     while (iters < A.max_iter && !all_done() && !user_stop) {
-      for (int k = 0; k < chunk; ++k) count_work();   // upper estimate per replay
-      sst.hx_bytes += chunk_bytes;
-      HKP_CHECK(hipGraphLaunch(rec.exec, c.s));
+      count_work();
+      const int need = (c.live32 > 0 ? 1 : 0) | (c.live64 > 0 ? 2 : 0);
+      if (!rec[need].exec) record(need, rec[need]);
+      sst.hx_bytes += rec[need].bytes;
+      HKP_CHECK(hipGraphLaunch(rec[need].exec, c.s));
       ++n_graph;
-      iters += chunk;
+      ++iters;
       read_flags();
       report(iters);
     }
@@ -1025,15 +1069,15 @@ int run_solve(const SolveArgs& A, hkp_stats* stats) {
     stats->lambda_max_bound = bup.empty() ? 0.0 : bup[0];
     sst.collect();
     stats->hx_bytes = sst.hx_bytes;
-    stats->n_stencil32 = sst.n32;
-    stats->n_stencil64 = sst.n64;
-    stats->t_stencil32 = sst.t32;
-    stats->t_stencil64 = sst.t64;
-    stats->bytes_stencil32 = sst.b32;
-    stats->bytes_stencil64 = sst.b64;
-    stats->n_stencil32x2 = sst.n32x2;
-    stats->t_stencil32x2 = sst.t32x2;
-    stats->bytes_stencil32x2 = sst.b32x2;
+    stats->n_stencil32 = sst.n[StencilStats::k32];
+    stats->n_stencil64 = sst.n[StencilStats::k64];
+    stats->t_stencil32 = sst.t[StencilStats::k32];
+    stats->t_stencil64 = sst.t[StencilStats::k64];
+    stats->bytes_stencil32 = sst.b[StencilStats::k32];
+    stats->bytes_stencil64 = sst.b[StencilStats::k64];
+    stats->n_stencil32x2 = sst.n[StencilStats::k32x2];
+    stats->t_stencil32x2 = sst.t[StencilStats::k32x2];
+    stats->bytes_stencil32x2 = sst.b[StencilStats::k32x2];
     stats->n_graph_launches = n_graph;
     stats->n_host_syncs = n_sync;
     stats->seconds =

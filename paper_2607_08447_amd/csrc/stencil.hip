@@ -24,8 +24,7 @@
 // block fused in).  Workgroups are mapped to XCDs in contiguous runs so that the
 // vectors of one tile share an L2.  Two ways of staging a plane: copies of whole rows
 // (stencil_kernel) and through registers (stencil_pipe_kernel); launch_t chooses.
-#include <map>
-#include <mutex>
+#include <algorithm>
 #include <type_traits>
 
 #include "hkp_internal.h"
@@ -57,7 +56,11 @@ struct KArgs {
   const int* lock;
   const int* work;
   int batch;
-  int zsplit, split_below, fill;
+  int vfirst;
+  int zsplit;   // z-ranges that the grid leaves room for
+  int zfixed;   // z-ranges of the launch, or 0: from the live count
+  float c0;
+  int stream;   // blocks beyond the cache: the old block and the output pass it by
   int nx, ny, nz, nvec;
   int tiles_x, tiles_y;
   int vgroup;   // vectors of one tile run side by side (1: vector-major)
@@ -71,32 +74,57 @@ struct KArgs {
 // so the halo rows they share hit in L2).  vgroup = 1 is vector-major order,
 // vgroup = nvec tile-major order.  With a work table the order runs over the
 // live (virtual) vectors of all members and the rest of the grid exits.
-// Launches with few live workgroups (locked vectors, converged members,
-// small grids) split every (vector, tile) into zs z-ranges so that more
-// workgroups share the chip; a range recomputes one plane on each side.
-// The grid holds zsplit x the unsplit count; the split is decided from the
-// live count, uniformly for the whole launch: in two below split_below live
-// workgroups, and on in halves while the doubled count stays within `fill`.
+// Launches with few live workgroups (locked vectors, converged members, small grids
+// and groups) split every (vector, tile) into zs z-ranges so that more workgroups
+// share the chip evenly; a range recomputes one plane on each side.  The grid holds
+// zsplit x the unsplit count; the split is decided from the live count, uniformly
+// for the whole launch (z_ranges below).
 struct Place {
   int b, vec, tile, zs, zc;
 };
+
+// z-ranges for nlw workgroups of nz planes, at most zmax: the fewest planes marched on
+// the CU that gets the most workgroups.  A workgroup marches nz / zs + 2 planes, a CU
+// gets ceil(nlw zs / 256) of them, and c0 workgroups together take no longer per
+// plane than one alone (a plane's latency against its share of the CU).  Measured for
+// 480 FP32 recurrence workgroups (12 vectors of 128 x 40 x 40): 63 us in one range, 68
+// in two; 384 (4 vectors of 256 x 48 x 48): 81 in one, 64 in four; 144 FP64 product
+// ones (6 vectors of 96 x 32 x 32): 53 in one, 35 in two, 28 in three, 30 in four.
+constexpr int kCUs = 256, kMaxSplit = 12;
+__host__ __device__ inline int z_ranges(int nlw, int nz, int zmax, float c0) {
+  constexpr float inv[kMaxSplit] = {1.0f,     1.0f / 2, 1.0f / 3, 1.0f / 4,  1.0f / 5,  1.0f / 6,
+                                    1.0f / 7, 1.0f / 8, 1.0f / 9, 1.0f / 10, 1.0f / 11, 1.0f / 12};
+  int best = 1;
+  float cost = 1e30f;
+#pragma unroll
+  for (int zs = 1; zs <= kMaxSplit; ++zs) {
+    const float per_cu = (float)((nlw * zs + kCUs - 1) / kCUs);
+    const float c = (per_cu > c0 ? per_cu : c0) * ((float)nz * inv[zs - 1] + 2.0f);
+    if (c < cost && zs <= zmax && zs <= nz) {
+      best = zs;
+      cost = c;
+    }
+  }
+  return best;
+}
+
 template <typename T>
 __device__ __forceinline__ bool find_place(const KArgs<T>& a, Place* p) {
   const int ntiles = a.tiles_x * a.tiles_y;
-  const int nlw = a.work ? a.work[a.batch] * ntiles : (int)gridDim.x / a.zsplit;
+  const int nv = a.work ? a.work[a.batch] : 0;   // live vectors
+  const int nlw = a.work ? nv * ntiles : (int)gridDim.x / a.zsplit;
   int zs = 1;
-  if (a.zsplit > 1 && nlw < a.split_below && a.nz >= 8) {
-    zs = 2;
-    while (2 * zs <= a.zsplit && 2 * zs * nlw <= a.fill && a.nz >= 4 * zs) zs *= 2;
+  if (a.zsplit > 1) {
+    zs = a.zfixed;
+    if (zs == 0) zs = z_ranges(nlw, a.nz, a.zsplit, a.c0);
   }
   const int nlive = nlw * zs;
-  if ((int)blockIdx.x >= nlive) return false;
+  if (nlive <= 0 || (int)blockIdx.x >= nlive) return false;
   int logical = xcd_remap(blockIdx.x, nlive);
   p->zs = zs;
   p->zc = logical / nlw;   // z range outermost: one range of all tiles per XCD run
   logical -= p->zc * nlw;
   if (a.work) {
-    const int nv = a.work[a.batch];
     const int g = logical / (a.vgroup * ntiles);
     const int within = logical - g * a.vgroup * ntiles;
     const int gsize = min(a.vgroup, nv - g * a.vgroup);
@@ -115,7 +143,7 @@ __device__ __forceinline__ bool find_place(const KArgs<T>& a, Place* p) {
   const int within = r - g * a.vgroup * ntiles;
   const int gsize = min(a.vgroup, a.nvec - g * a.vgroup);
   p->tile = within / gsize;
-  p->vec = g * a.vgroup + (within - p->tile * gsize);
+  p->vec = a.vfirst + g * a.vgroup + (within - p->tile * gsize);
   if (a.active && !a.active[p->b]) return false;
   return !(a.lock && p->vec < a.lock[p->b]);   // converged vectors are not filtered
 }
@@ -263,6 +291,8 @@ stencil_pipe_kernel(KArgs<T> a) {
   cx<double> ux = mk<double>(1, 0);
   if constexpr (PH == 2) ux = ld(a.utab64 + 2 * (gx < nx ? gx : nx - 1));
 
+  const bool stream = a.stream != 0;
+
   constexpr int ND = STR ? 6 : 1;
   struct Set {          // what a step needs besides the plane: loaded one step ahead
     T d[ND];            // on-site fields of the plane (d00 d11 d22 d12 d02 d01, or V)
@@ -300,7 +330,10 @@ stencil_pipe_kernel(KArgs<T> a) {
     if constexpr (kOld) {
       const TOv* q = oldp + 2 * plane(z, oldxy);
 #pragma unroll
-      for (int i = 0; i < 3; ++i) t.old[i] = ld_stream(ptr(q + 2 * (size_t)(i * oldN), colO));
+      for (int i = 0; i < 3; ++i) {
+        const TOv* p = ptr(q + 2 * (size_t)(i * oldN), colO);
+        t.old[i] = stream ? ld_stream(p) : ld(p);
+      }
     }
   };
   cx<T> acc0[3], acc1[3], res[3];
@@ -310,7 +343,10 @@ stencil_pipe_kernel(KArgs<T> a) {
     if (!mine) return;
     TW* q = outp + 2 * plane(z, nxy);
 #pragma unroll
-    for (int i = 0; i < 3; ++i) stg_stream<TW>(ptr(q + 2 * (size_t)i * N, colW), 0, res[i]);
+    for (int i = 0; i < 3; ++i) {
+      TW* p = ptr(q + 2 * (size_t)i * N, colW);
+      if (stream) stg_stream<TW>(p, 0, res[i]); else stg<TW>(p, 0, res[i]);
+    }
   };
   auto finish = [&](const Set& t) {
 #pragma unroll
@@ -383,16 +419,13 @@ stencil_pipe_kernel(KArgs<T> a) {
 // NC = 6: the full spinor (a wave per spin and row).  NC = 3: a spin-free orbital
 // vector (X, Y, Z of one spin; no spin-orbit or field terms, so nothing couples
 // it to the other spin): one wave per row and half the bytes.
-// (FP32 steps without an old block are held to 128 VGPRs: four waves per SIMD)
 template <typename T, typename TO, typename TW, int PH, bool STR, int TY, int NC = 6>
-__global__ void __launch_bounds__(64 * TY * (NC / 3),
-                                  (sizeof(T) == 4 && std::is_same<TO, void>::value && TY >= 2) ? 4 : 1)
+__global__ void __launch_bounds__(64 * TY * (NC / 3))
 stencil_kernel(KArgs<T> a) {
   static_assert(NC == 6 || (NC == 3 && PH == 0), "spin-free vectors carry no field terms");
-  // LDS row: [pad] left halo, 64 interior, right halo [pad]; in FP32 the interior
-  // starts on a 16-byte boundary (column 2 of a 68-wide row)
-  constexpr int C0 = sizeof(T) == 4 ? 2 : 1;   // column of x = tx0
-  constexpr int W = sizeof(T) == 4 ? 68 : 66;
+  static_assert(sizeof(T) == 8, "a lane copies one complex entry of 16 bytes");
+  constexpr int C0 = 1;   // column of x = tx0 in an LDS row: left halo, 64 interior, right halo
+  constexpr int W = 66;
   constexpr int ROWS = TY + 2;
   constexpr int SLOTS = W * ROWS;
   constexpr int PLANE = SLOTS;        // elements per (buffer, component) plane
@@ -470,10 +503,8 @@ stencil_kernel(KArgs<T> a) {
       const int y = ty0 + r - 1;
       if (y < 0 || y >= ny) continue;
       const T* src = in + 2 * (size_t)((unsigned)c * N + zo + (unsigned)(y * nx + tx0)) +
-                     (sizeof(T) == 8 ? 2 : 4) * lx;
-      cx<T>* drow = dst + c * PLANE + r * W + C0;
-      if (sizeof(T) == 8 || lx < 32)
-        dma16(src, drow);
+                     2 * lx;
+      dma16(src, dst + c * PLANE + r * W + C0);
     }
   };
   // x-halo columns: element e of 12 ROWS per plane (side, component, row)
@@ -498,7 +529,8 @@ stencil_kernel(KArgs<T> a) {
     const unsigned o = (unsigned)z * nxy + col;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-      cx<TOv> q = ld_stream(oldp + 2 * (size_t)((unsigned)i * N + o));
+      const TOv* p = oldp + 2 * (size_t)((unsigned)i * N + o);
+      cx<TOv> q = a.stream ? ld_stream(p) : ld(p);
       oldv[i] = mk<T>((T)q.r, (T)q.i);
     }
   };
@@ -509,7 +541,8 @@ stencil_kernel(KArgs<T> a) {
     for (int i = 0; i < 3; ++i) {
       cx<T> r = scl(alpha, acc0[i]);
       if (kOld && has_old) r = fma_s(r, beta, oldv[i]);
-      stg_stream<TW>(outp, (long long)((unsigned)i * N + o), r);
+      const long long w = (long long)((unsigned)i * N + o);
+      if (a.stream) stg_stream<TW>(outp, w, r); else stg<TW>(outp, w, r);
     }
   };
 
@@ -589,28 +622,6 @@ stencil_kernel(KArgs<T> a) {
   }
 }
 
-// workgroups of this kernel resident on the whole device at once (occupancy
-// query, cached per kernel)
-template <typename K>
-int resident_workgroups(K kernel, int threads) {
-  static std::mutex mu;
-  static std::map<const void*, int> cache;
-  const void* key = reinterpret_cast<const void*>(kernel);
-  std::lock_guard<std::mutex> lk(mu);
-  auto it = cache.find(key);
-  if (it != cache.end()) return it->second;
-  int per_cu = 0, dev = 0, cus = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess ||
-      hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
-    (void)hipGetLastError();
-    return 0;   // unknown: never split
-  }
-  const int r = per_cu * cus;
-  cache[key] = r;
-  return r;
-}
-
 template <typename T, typename TO, typename TW, int PH, bool STR, int NC = 6>
 hipError_t launch_t(const StencilLaunch& L, const StencilConsts<double>& c, hipStream_t s) {
   KArgs<T> a;
@@ -637,43 +648,64 @@ hipError_t launch_t(const StencilLaunch& L, const StencilConsts<double>& c, hipS
   a.nx = L.nx;
   a.ny = L.ny;
   a.nz = L.nz;
-  a.nvec = L.nvec;
-  a.vgroup = L.vgroup < 1 ? 1 : (L.vgroup > L.nvec ? L.nvec : L.vgroup);
+  const bool part = L.vcount > 0;
+  if (part && (L.work || L.batch != 1)) return hipErrorInvalidValue;
+  a.nvec = part ? L.vcount : L.nvec;
+  a.vgroup = L.vgroup < 1 ? 1 : (L.vgroup > a.nvec ? a.nvec : L.vgroup);
+  a.vfirst = part ? L.vfirst : 0;
+  const long long vectors = (long long)a.nvec * L.batch;
+  // The old block (read for the last time) and the output pass the caches by where the
+  // launch's blocks exceed the memory-side cache: they would only push out what is
+  // read again (on-site fields, halo rows; a 40-vector FP32 step of 256 x 48 x 48: 711
+  // us, 763 cached).  Blocks that fit are kept, for the next step to read (4 vectors:
+  // 59 us, 72 streamed).
+  const size_t entries = (size_t)vectors * NC * L.nx * L.ny * L.nz;
+  a.stream = entries * (2 * sizeof(T) + 2 * sizeof(TW) +
+                        (L.old && L.old != L.out ? 2 * (L.old_fp64 ? 8 : 4) : 0)) > kCacheBytes;
   a.k = cast_consts<T>(c);
   const int ty = L.tile_y;
   constexpr unsigned NSP = NC / 3;   // spin waves per row
   auto go = [&](auto kernel, int tx, int rows, int waves) {
     a.tiles_x = (L.nx + tx - 1) / tx;
     a.tiles_y = (L.ny + rows - 1) / rows;
-    const long long nwg = (long long)a.tiles_x * a.tiles_y * L.nvec * L.batch;
+    const long long nwg = (long long)a.tiles_x * a.tiles_y * vectors;
     if (nwg <= 0) return hipSuccess;
-    // z split: 0 never, 1 when fewer live workgroups than three resident waves of
-    // them (further while they still fit at once), 2 always in two (tests)
-    const int threads = 64 * waves * (int)NSP;
-    const int resident = L.zsplit == 1 ? resident_workgroups(kernel, threads) : 0;
-    a.zsplit = L.zsplit > 0 ? 2 : 1;
-    while (L.zsplit == 1 && a.zsplit < 16 && 2 * a.zsplit * nwg <= resident) a.zsplit *= 2;
+    // z split: 0 never, 1 as balances the launch, 2 always in two (tests).  Where the
+    // live count is only known on the device the grid leaves room for twice the split
+    // that suits all vectors.
+    a.c0 = sizeof(T) == 8 ? 2.2f : (std::is_same<TO, void>::value ? 2.6f : 2.0f);
+    a.zsplit = a.zfixed = 1;
+    if (L.zsplit >= 2) {
+      a.zsplit = 2;
+      a.zfixed = L.nz >= 8 ? 2 : 1;
+    } else if (L.zsplit == 1 && nwg < 16 * kCUs) {
+      a.zfixed = a.zsplit = z_ranges((int)nwg, L.nz, 8, a.c0);
+      if (L.work) {
+        a.zsplit = std::min(kMaxSplit, 2 * a.zsplit);
+        a.zfixed = 0;
+      }
+    }
     if (nwg * a.zsplit > 0x7fffffffLL) return hipErrorInvalidValue;
-    a.split_below = L.zsplit >= 2 ? 0x7fffffff : 3 * resident;
-    a.fill = resident;
     kernel<<<dim3((unsigned)(nwg * a.zsplit)), dim3(64, waves, NSP), 0, s>>>(a);
     return hipGetLastError();
   };
-  // Row copies or register staging.  Whole 64-wide tiles with an old block copy rows
-  // (FP64 recurrence step, 40 vectors of 128 x 40 x 40: 475 us, staged 504; FP32 both
-  // 250-253).  Without an old block staging is at least as fast in FP32 (16 vectors of
-  // 256 x 48 x 48: 220 us, copied 227; 4 vectors 43 and 53); in FP64 and for spin-free
-  // vectors the copy stays ahead by 1-3% (1057 and 1081 us, 40 vectors).  Any other nx
-  // is staged: 32-wide tiles keep the lanes that 64-wide ones pad away (FP32 product
-  // step, 40 vectors of 96 x 32 x 32: 66 us, 64-wide staged 100; 75 x 31 x 29: 77 and
-  // 98), 16-wide ones only where a 32-wide tile would be half empty.
-  constexpr bool copy = !std::is_same<TO, void>::value || sizeof(T) == 8 || NC == 3;
-  if (copy && L.dma && L.nx % 64 == 0) {
-    switch (ty) {
-      case 1: return go(stencil_kernel<T, TO, TW, PH, STR, 1, NC>, 64, 1, 1);
-      case 2: return go(stencil_kernel<T, TO, TW, PH, STR, 2, NC>, 64, 2, 2);
-      case 4: return go(stencil_kernel<T, TO, TW, PH, STR, 4, NC>, 64, 4, 4);
-      default: return hipErrorInvalidValue;
+  // Row copies or register staging.  FP64 on whole 64-wide tiles copies rows (its step
+  // in cache-sized groups: 58 us copied, 61 staged, 2 vectors of 256 x 48 x 48; 14
+  // orbitals of 128 x 37 x 37 63 and 68; H X of 40 vectors 1057 and 1081).  FP32 is
+  // staged (12 vectors of 128 x 40 x 40: 63 us, 67 copied; 40 vectors of 256 x 48 x 48
+  // 718 and 722; without an old block 4 vectors 45 and 53), and so is any other nx:
+  // 32-wide tiles keep the lanes that 64-wide ones pad away (FP32 product step, 40
+  // vectors of 96 x 32 x 32: 66 us, 64-wide staged 100; 75 x 31 x 29: 77 and 98),
+  // 16-wide ones only where a 32-wide tile would be half empty.
+  constexpr bool copy = sizeof(T) == 8;
+  if constexpr (copy) {
+    if (L.dma && L.nx % 64 == 0) {
+      switch (ty) {
+        case 1: return go(stencil_kernel<T, TO, TW, PH, STR, 1, NC>, 64, 1, 1);
+        case 2: return go(stencil_kernel<T, TO, TW, PH, STR, 2, NC>, 64, 2, 2);
+        case 4: return go(stencil_kernel<T, TO, TW, PH, STR, 4, NC>, 64, 4, 4);
+        default: return hipErrorInvalidValue;
+      }
     }
   }
   // one row and 64-bit lane offsets where a lane's 32-bit byte offset could overflow
