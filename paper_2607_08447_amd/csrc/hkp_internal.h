@@ -33,6 +33,8 @@ __device__ __forceinline__ int xcd_remap(int wg, int nwg) {
   return x * per + (x < rem ? x : rem) + idx;
 }
 
+constexpr int kCUs = 256;   // compute units of the GPU
+
 // unit constants from CODATA 2018 (h, e exact; m0 = 9.1093837015e-31 kg),
 // ten significant digits
 constexpr double kE0 = 0.03809982116;         // hbar^2/(2 m0), eV nm^2

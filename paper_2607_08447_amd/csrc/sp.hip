@@ -11,13 +11,15 @@
 // would leave the box -- the field-free outer faces).  Electrode nodes keep
 // their potential; every CG vector is zero on them.
 //
-// All of these kernels stream through memory once per call: they are HBM-bound
-// and run one node per thread (grid-stride beyond kRedBlocks workgroups); the
+// All of these kernels stream through memory once per call, with one node per thread,
+// or two where the box allows it (grid-stride beyond kRedBlocks workgroups); the
 // stencil-shaped ones give every XCD a contiguous range of nodes, so that the
 // x- and y-neighbours a node reads are in the L2 its neighbours filled.
 // Per-workgroup partial sums are reduced in a fixed order by one workgroup
 // (the results do not depend on timing).
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "hkp_internal.h"
 
@@ -80,6 +82,24 @@ __device__ __forceinline__ void block_sums(double (&v)[NV], double* out) {
       for (int i = 0; i < NT / 64; ++i) s += sh[k][i];
       out[k] = s;
     }
+  }
+}
+
+// block sums of NV values for each of a group's NR systems (v[s * NV + k]), the rows
+// of the running ones written to partial[(system gridDim.x + blockIdx.x) NV + k]
+template <int NR, int NV>
+__device__ __forceinline__ void group_sums(double (&v)[NR * NV], const bool (&on)[NR],
+                                           double* partial) {
+  __shared__ double out[NR * NV];
+  block_sums<NR * NV>(v, out);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int s = 0; s < NR; ++s)
+      if (on[s])
+#pragma unroll
+        for (int k = 0; k < NV; ++k)
+          partial[((long long)(blockIdx.y * NR + s) * gridDim.x + blockIdx.x) * NV + k] =
+              out[s * NV + k];
   }
 }
 
@@ -158,46 +178,160 @@ __device__ __forceinline__ double link_sum(unsigned i, int x, int y, int z, cons
   return s;
 }
 
-// The six neighbours of node i at (x, y, z) in an nx x ny x nz box with strides
-// sx, sy (order +x, -x, +y, -y, +z, -z), for branch-free stencils: indices clamped
-// to i itself where the neighbour would lie outside the box, with that link's
-// weight set to zero.  Every load of such a stencil is issued unconditionally, so
-// a thread's loads go out back to back instead of one conditional round trip to
-// memory per link.
-struct Hood {
-  unsigned j[6];
-  bool in[6];
+// ---------------------------------------------------------------------------
+// Two nodes per thread.  A thread takes the nodes z, z + 1 (z even) of one z-row: 16-byte
+// loads of the pair and of its x- and y-neighbour pairs, while the two outer
+// z-neighbours come from the adjacent lanes, which hold the adjacent pairs.  A vector then takes 5 loads for two nodes instead of 14, which is
+// what these kernels are bound by otherwise: the address unit serves a wave's load in
+// at least 16 cycles, of 8 or of 16 bytes per lane, and was busy 80 % of their time.
+// Only the first and last lane of a run of RUN lanes fetch an outer z-neighbour
+// themselves (one masked load).  One system of 272 x 64 x 88, matvec / restriction with
+// the update / correction: 18.7 / 30.7 / 22.5 us with one node per thread, 14.4 / 20.7 /
+// 14.4 so; twenty systems 323 / 457 / 281 and 226 / 327 / 181 us.
+//
+// In a row of odd length the last pair has one node.  What its loads bring as the
+// second is the next row's or, at the end of an array, the workspace's next bytes (the
+// callers' phi and electrode mask are not read there); it reaches neither a stored
+// value nor a sum, nor the pair's first node.
+// ---------------------------------------------------------------------------
+typedef double d2 __attribute__((ext_vector_type(2)));
+// in memory: aligned as its elements are (a caller's array, a coarse level at an odd
+// offset); one 16-byte access all the same
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+
+__device__ __forceinline__ d2 ld2(const double* p, long long i) {
+  return *reinterpret_cast<const d2u*>(p + i);
+}
+__device__ __forceinline__ void st2(double* p, long long i, d2 v, bool two) {
+  if (two) *reinterpret_cast<d2u*>(p + i) = v;
+  else p[i] = v.x;
+}
+
+// v of the previous (UP) or next lane of the run; own value at the run's end
+template <int RUN, bool UP>
+__device__ __forceinline__ double lane_shift(double v) {
+  static_assert(RUN == 16 || RUN == 64, "a DPP row or the wave");
+  constexpr int ctrl = RUN == 16 ? (UP ? 0x111 : 0x101) : (UP ? 0x138 : 0x130);
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, ctrl, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(lo, lo, ctrl, 0xf, 0xf, false));
+}
+
+// the neighbour pairs of the pair at i = (x, y, z): +x, -x, +y, -y (i itself where
+// they would lie outside), whether the pair's second node and the outer z-neighbours
+// exist (two: i + 1, zp: i + 2, zm: i - 1), and the outer neighbour that this lane
+// fetches itself (ze, if edge)
+struct PairHood {
+  unsigned i, j[4], ze;
+  bool in[4], two, zp, zm, edge;
 };
-__device__ __forceinline__ Hood hood(unsigned i, int x, int y, int z, int nx, int ny, int nz,
-                                     unsigned sx, unsigned sy) {
-  Hood h;
+template <int RUN>
+__device__ __forceinline__ PairHood pair_hood(unsigned i, int x, int y, int z, int nx, int ny,
+                                              int nz) {
+  const unsigned sx = (unsigned)ny * nz, sy = (unsigned)nz;
+  PairHood h;
+  h.i = i;
   h.in[0] = x + 1 < nx;
   h.in[1] = x > 0;
   h.in[2] = y + 1 < ny;
   h.in[3] = y > 0;
-  h.in[4] = z + 1 < nz;
-  h.in[5] = z > 0;
   h.j[0] = h.in[0] ? i + sx : i;
   h.j[1] = h.in[1] ? i - sx : i;
   h.j[2] = h.in[2] ? i + sy : i;
   h.j[3] = h.in[3] ? i - sy : i;
-  h.j[4] = h.in[4] ? i + 1 : i;
-  h.j[5] = h.in[5] ? i - 1 : i;
+  h.two = z + 1 < nz;
+  h.zp = z + 2 < nz;
+  h.zm = z > 0;
+  const unsigned l = threadIdx.x & (RUN - 1);
+  const bool first = l == 0 && h.zm, last = l == RUN - 1 && h.zp;
+  h.edge = first || last;
+  h.ze = first ? i - 1 : last ? i + 2 : i;
   return h;
 }
-// weights of the six links from per-node +x, +y, +z link arrays (the link to the
-// lower neighbour is stored there), zero outside the box
-__device__ __forceinline__ void hood_weights(unsigned i, const Hood& h, const double* ax,
-                                             const double* ay, const double* az,
-                                             double (&c)[6]) {
-  const double v[6] = {ax[i], ax[h.j[1]], ay[i], ay[h.j[3]], az[i], az[h.j[5]]};
-#pragma unroll
-  for (int q = 0; q < 6; ++q) c[q] = h.in[q] ? v[q] : 0.0;
+
+// the pairs of a box, row after row
+struct PairGeo {
+  int nx, ny, nz;
+  unsigned row, pairs;   // pairs per z-row, in all
+  double iny, irow;      // 1 / ny, 1 / row (host-computed)
+};
+// first node of pair t, at (x, y, z)
+__device__ __forceinline__ unsigned pair_at(unsigned t, const PairGeo& g, int& x, int& y, int& z) {
+  const unsigned r = udiv(t, g.row, g.irow);   // x ny + y
+  z = (int)(2 * (t - r * g.row));
+  x = (int)udiv(r, (unsigned)g.ny, g.iny);
+  y = (int)(r - (unsigned)x * (unsigned)g.ny);
+  return r * (unsigned)g.nz + (unsigned)z;
 }
 
-// Every CG kernel solves blockIdx.y = 0 .. nrhs-1 systems at once (the same
-// operator, right-hand sides and vectors vs = NP apart, a CGState each); the
-// single-system solves are nrhs = 1.
+// a field on the pair, its neighbour pairs and the lane's own outer z-neighbour
+struct PairVals {
+  d2 o, n[4];
+  double e;
+};
+__device__ __forceinline__ PairVals pair_load(const double* p, const PairHood& h) {
+  PairVals v;
+  v.o = ld2(p, h.i);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v.n[k] = ld2(p, h.j[k]);
+  v.e = 0.0;
+  if (h.edge) v.e = p[h.ze];
+  return v;
+}
+// link weights of the pair: +x, -x, +y, -y, +z, -z (az is zero at a row's last node)
+__device__ __forceinline__ void pair_weights(const PairHood& h, const double* ax,
+                                             const double* ay, const double* az, d2 (&c)[6]) {
+  const d2 zero = {0.0, 0.0};
+  const d2 v[4] = {ld2(ax, h.i), ld2(ax, h.j[1]), ld2(ay, h.i), ld2(ay, h.j[3])};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) c[k] = h.in[k] ? v[k] : zero;
+  c[4] = ld2(az, h.i);
+  if (!h.zp) c[4].y = 0.0;
+  c[5].x = h.zm ? az[h.i - (h.zm ? 1 : 0)] : 0.0;
+  c[5].y = c[4].x;
+}
+// the z-neighbours of the pair's two nodes: +z, then -z
+template <int RUN>
+__device__ __forceinline__ void pair_z(const PairHood& h, const PairVals& u, d2& up, d2& um) {
+  const double a = lane_shift<RUN, false>(u.o.x), b = lane_shift<RUN, true>(u.o.y);
+  const unsigned l = threadIdx.x & (RUN - 1);
+  up.x = h.two ? u.o.y : u.o.x;
+  up.y = h.zp ? (l == RUN - 1 ? u.e : a) : u.o.y;
+  um.x = h.zm ? (l == 0 ? u.e : b) : u.o.x;
+  um.y = u.o.x;
+}
+
+// The CG kernels solve nrhs systems at once: the same operator, right-hand sides
+// and vectors NP apart, a CGState each; the single-system solves are nrhs = 1.  The
+// node-streaming kernels of an iteration take NR consecutive systems per workgroup
+// (blockIdx.y: the group), the others one system per blockIdx.y.
+//
+// Group: those NR systems.  A finished one (or one past the last) is read as the
+// first unfinished one instead, so that all loads stay unconditional, and stores
+// nothing.
+template <int NR>
+struct Group {
+  int sys[NR];
+  bool on[NR], any;
+};
+template <int NR>
+__device__ __forceinline__ Group<NR> group_of(const CGState* st, int nrhs) {
+  Group<NR> G;
+  const int first = blockIdx.y * NR;
+  int live = first;
+  G.any = false;
+#pragma unroll
+  for (int k = NR - 1; k >= 0; --k) {
+    const int s = first + k;
+    G.on[k] = s < nrhs && !st[s < nrhs ? s : first].done;
+    if (G.on[k]) live = s;
+    G.any = G.any || G.on[k];
+  }
+#pragma unroll
+  for (int k = 0; k < NR; ++k) G.sys[k] = G.on[k] ? first + k : live;
+  return G;
+}
+
 //
 // r = b - L phi on free nodes, b = (e/eps0) rho + electrode couplings; electrode
 // nodes take their fixed potential (0 when phi_fixed is null: grounded; free
@@ -270,46 +404,52 @@ cg_start_kernel(const double* partial, int nblk, double tol, CGState* st) {
 
 // p_new = z + beta p_old (at the node and its neighbours: the old direction is
 // not overwritten, p_new goes to the other buffer); q = L p_new; partial p.q
+template <int NR>
 __global__ void __launch_bounds__(kThreads)
-cg_matvec_kernel(unsigned NP, int px, int py, int pz, double ipy, double ipz,
-                 const double* __restrict__ cx,
+cg_matvec_kernel(long long NP, PairGeo g, const double* __restrict__ cx,
                  const double* __restrict__ cy, const double* __restrict__ cz,
-                 const uint8_t* __restrict__ dir, const double* __restrict__ zv,
-                 const double* __restrict__ p_old, double* __restrict__ p_new,
-                 double* __restrict__ q, double* partial, const CGState* st) {
-  st += blockIdx.y;
-  if (st->done) return;
-  const double beta = st->beta;
-  const Geo g = geo(px, py, pz, ipy, ipz);
-  const long long vo = (long long)blockIdx.y * NP;
-  zv += vo;
-  p_old += vo;
-  p_new += vo;
-  q += vo;
-  double acc[1] = {0.0};
-  for (unsigned i = xcd_remap(blockIdx.x, gridDim.x) * kThreads + threadIdx.x; i < NP;
-       i += gridDim.x * kThreads) {
+                  const uint8_t* __restrict__ dir, const double* __restrict__ zv,
+                  const double* __restrict__ p_old, double* __restrict__ p_new,
+                  double* __restrict__ q, double* partial, const CGState* st, int nrhs) {
+  const Group<NR> G = group_of<NR>(st, nrhs);
+  if (!G.any) return;
+  double acc[NR];
+#pragma unroll
+  for (int s = 0; s < NR; ++s) acc[s] = 0.0;
+  for (unsigned t = xcd_remap(blockIdx.x, gridDim.x) * kThreads + threadIdx.x; t < g.pairs;
+       t += gridDim.x * kThreads) {
     int x, y, z;
-    coords(i, g, x, y, z);
-    const Hood h = hood(i, x, y, z, g.px, g.py, g.pz, g.sx, g.sy);
-    const bool d = dir[i] != 0;
-    double c[6], zn[6], pn[6];
-    hood_weights(i, h, cx, cy, cz, c);
+    const unsigned i = pair_at(t, g, x, y, z);
+    const PairHood h = pair_hood<64>(i, x, y, z, g.nx, g.ny, g.nz);
+    const bool d0 = dir[i] != 0, d1 = dir[h.two ? i + 1 : i] != 0;
+    d2 c[6];
+    pair_weights(h, cx, cy, cz, c);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      zn[k] = zv[h.j[k]];
-      pn[k] = p_old[h.j[k]];
+    for (int s = 0; s < NR; ++s) {
+      const long long vo = (long long)G.sys[s] * NP;
+      const double beta = st[G.sys[s]].beta;
+      const PairVals zs = pair_load(zv + vo, h), ps = pair_load(p_old + vo, h);
+      PairVals u;   // p_new (0 at electrodes: z = p_old = 0 there)
+      u.o = zs.o + beta * ps.o;
+      u.e = zs.e + beta * ps.e;
+      d2 up, um;
+      pair_z<64>(h, u, up, um);
+      d2 qi = {0.0, 0.0};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) qi += c[k] * (u.o - (zs.n[k] + beta * ps.n[k]));
+      qi += c[4] * (u.o - up);
+      qi += c[5] * (u.o - um);
+      d2 pi = u.o;
+      if (d0) pi.x = qi.x = 0.0;
+      if (d1 || !h.two) pi.y = qi.y = 0.0;
+      if (G.on[s]) {
+        st2(p_new, vo + i, pi, h.two);
+        st2(q, vo + i, qi, h.two);
+      }
+      acc[s] += pi.x * qi.x + pi.y * qi.y;
     }
-    const double pi = zv[i] + beta * p_old[i];
-    // electrode neighbours hold z = p_old = 0, so their p_new is 0 as well
-    double qi = 0.0;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) qi += c[k] * (pi - (zn[k] + beta * pn[k]));
-    p_new[i] = d ? 0.0 : pi;
-    q[i] = d ? 0.0 : qi;
-    acc[0] += d ? 0.0 : pi * qi;
   }
-  block_sums<1>(acc, partial + (long long)blockIdx.y * gridDim.x + blockIdx.x);
+  group_sums<NR, 1>(acc, G.on, partial);
 }
 
 __global__ void __launch_bounds__(kRedThreads)
@@ -498,86 +638,86 @@ struct MGLevelArgs {
   const double *ax, *ay, *az, *diag, *dinv;
 };
 
-__device__ __forceinline__ Hood mg_hood(unsigned j, int x, int y, int z, const MGGeo& g) {
-  return hood(j, x, y, z, g.nx, g.ny, g.nz, (unsigned)g.ny * g.nz, (unsigned)g.nz);
-}
-
-// (A u)_j with u given by a functor of the neighbour's index and its direction
-// (0 .. 5 as in Hood); every load unconditional
-template <typename F>
-__device__ __forceinline__ double mg_apply(unsigned j, const Hood& h, const MGLevelArgs& L,
-                                           double uj, F u) {
-  double c[6], v[6];
-  hood_weights(j, h, L.ax, L.ay, L.az, c);
-#pragma unroll
-  for (int k = 0; k < 6; ++k) v[k] = u(h.j[k], k);
-  double s = L.diag[j] * uj;
-#pragma unroll
-  for (int k = 0; k < 6; ++k) s -= c[k] * v[k];
-  return s;
-}
-
 // b_c[I] = sum over the children j of I of (b - A u)_j, u = w D^-1 b (pre-smoothing).
-// Eight consecutive lanes take the eight children of one coarse node (lane bits
-// 2, 1, 0 = x, y, z offsets) and sum them by shuffles, so the fine level runs one
-// node per thread.  Like the other level kernels it gives every XCD a contiguous
-// run of nodes (the x- and y-neighbours a node reads are then in that XCD's L2).
+// Sixteen consecutive lanes take sixteen coarse nodes' z-pairs at one of the four (x, y)
+// children (lane bits 5, 4), summed by shuffles.  Like the other level kernels it gives
+// every XCD a contiguous run of nodes (the x- and y-neighbours a node reads are then in
+// that XCD's L2).
 //
 // UPD (the finest level inside a CG iteration): the CG update comes first, in the
 // same pass -- phi += alpha p and the new residual b - alpha q (b: the old residual),
 // formed wherever it is needed (at the node, and at its neighbours from their old b
 // and q) and stored to r_new, another buffer, with partial sums (0, r_new.r_new) per
 // workgroup -- and the restriction takes the new residual as its right-hand side.
-template <bool UPD>
+template <bool UPD, int NR>
 __global__ void __launch_bounds__(kThreads)
 mg_restrict_kernel(MGLevelArgs L, MGGeo c, double w, const double* __restrict__ b,
-                   long long b_stride, double* bc, long long bc_stride, const CGState* st,
-                   const double* __restrict__ p, const double* __restrict__ q,
-                   double* __restrict__ phi, double* __restrict__ r_new,
-                   double* __restrict__ partial) {
-  if (st[blockIdx.y].done) return;
-  const double alpha = UPD ? st[blockIdx.y].alpha : 0.0;
-  b += blockIdx.y * b_stride;
-  bc += blockIdx.y * bc_stride;
-  if (UPD) {
-    p += blockIdx.y * b_stride;
-    q += blockIdx.y * b_stride;
-    phi += blockIdx.y * b_stride;
-    r_new += blockIdx.y * b_stride;
-  }
+                    long long b_stride, double* bc, long long bc_stride, const CGState* st,
+                    int nrhs, const double* __restrict__ p, const double* __restrict__ q,
+                    double* __restrict__ phi, double* __restrict__ r_new,
+                    double* __restrict__ partial) {
+  const Group<NR> G = group_of<NR>(st, nrhs);
+  if (!G.any) return;
+  double acc[2 * NR];
+#pragma unroll
+  for (int s = 0; s < 2 * NR; ++s) acc[s] = 0.0;
   const unsigned NC = (unsigned)c.nx * c.ny * c.nz;
-  auto rhs = [&](unsigned j) { return UPD ? b[j] - alpha * q[j] : b[j]; };
-  auto u = [&](unsigned j, int) { return w * L.dinv[j] * rhs(j); };
-  const unsigned ch = threadIdx.x & 7;
-  double acc[2] = {0.0, 0.0};
-  // trip counts are equal within each group of eight lanes (8 NC and the stride are
-  // multiples of eight), so every shuffle below sees its whole group
-  for (unsigned t = xcd_remap(blockIdx.x, gridDim.x) * kThreads + threadIdx.x; t < 8 * NC; t += gridDim.x * kThreads) {
-    const unsigned I = t >> 3;
+  const unsigned lane = threadIdx.x & 63;
+  const unsigned cx = lane >> 5, cy = (lane >> 4) & 1;
+  // the four lanes of a coarse node run or leave together
+  for (unsigned t = xcd_remap(blockIdx.x, gridDim.x) * (kThreads / 4) + (threadIdx.x >> 6) * 16 +
+                    (lane & 15);
+       t < NC; t += gridDim.x * (kThreads / 4)) {
     int X, Y, Z;
-    mg_coords(I, c, X, Y, Z);
-    const int x = 2 * X + (int)(ch >> 2), y = 2 * Y + (int)((ch >> 1) & 1),
-              z = 2 * Z + (int)(ch & 1);
-    // a child past a ragged edge of the box stands in for the aggregate's first
-    // child (which always exists) and contributes nothing
-    const bool inb = x < L.g.nx && y < L.g.ny && z < L.g.nz;
-    const int xx = inb ? x : 2 * X, yy = inb ? y : 2 * Y, zz = inb ? z : 2 * Z;
-    const unsigned j = ((unsigned)xx * L.g.ny + yy) * L.g.nz + zz;
-    const double bj = rhs(j);
-    const double dj = L.dinv[j];
-    const double sj = bj - mg_apply(j, mg_hood(j, xx, yy, zz, L.g), L, w * dj * bj, u);
-    double s = (inb && dj != 0.0) ? sj : 0.0;   // active nodes only
-    if (UPD && inb) {
-      phi[j] += alpha * p[j];
-      r_new[j] = bj;
-      acc[1] += bj * bj;
+    mg_coords(t, c, X, Y, Z);
+    const int x = 2 * X + (int)cx, y = 2 * Y + (int)cy, z = 2 * Z;
+    // a child past a ragged edge stands in for the first one and contributes nothing
+    const bool inb = x < L.g.nx && y < L.g.ny;
+    const int xx = inb ? x : 2 * X, yy = inb ? y : 2 * Y;
+    const unsigned j = ((unsigned)xx * L.g.ny + yy) * L.g.nz + z;
+    const PairHood h = pair_hood<16>(j, xx, yy, z, L.g.nx, L.g.ny, L.g.nz);
+    d2 cw[6];
+    pair_weights(h, L.ax, L.ay, L.az, cw);
+    const PairVals dv = pair_load(L.dinv, h);
+    const d2 dg = ld2(L.diag, j);
+#pragma unroll
+    for (int s = 0; s < NR; ++s) {
+      const long long vo = G.sys[s] * b_stride;
+      PairVals r = pair_load(b + vo, h);
+      if (UPD) {
+        const double alpha = st[G.sys[s]].alpha;
+        const PairVals qs = pair_load(q + vo, h);
+        r.o -= alpha * qs.o;
+        r.e -= alpha * qs.e;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r.n[k] -= alpha * qs.n[k];
+        if (G.on[s] && inb) {
+          const d2 ps = ld2(p, vo + j);
+          if (h.two) st2(phi, vo + j, ld2(phi, vo + j) + alpha * ps, true);
+          else phi[vo + j] += alpha * ps.x;
+          st2(r_new, vo + j, r.o, h.two);
+          acc[2 * s + 1] += r.o.x * r.o.x + (h.two ? r.o.y * r.o.y : 0.0);
+        }
+      }
+      PairVals u;
+      u.o = w * dv.o * r.o;
+      u.e = w * dv.e * r.e;
+      d2 up, um;
+      pair_z<16>(h, u, up, um);
+      d2 au = dg * u.o;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) au -= cw[k] * (w * dv.n[k] * r.n[k]);
+      au -= cw[4] * up;
+      au -= cw[5] * um;
+      // active nodes only
+      double sum = ((inb && dv.o.x != 0.0) ? r.o.x - au.x : 0.0) +
+                   ((inb && h.two && dv.o.y != 0.0) ? r.o.y - au.y : 0.0);
+      sum += __shfl_xor(sum, 16, 64);
+      sum += __shfl_xor(sum, 32, 64);
+      if (lane < 16 && G.on[s]) bc[G.sys[s] * bc_stride + t] = sum;
     }
-    s += __shfl_xor(s, 1, 8);
-    s += __shfl_xor(s, 2, 8);
-    s += __shfl_xor(s, 4, 8);
-    if (ch == 0) bc[I] = s;
   }
-  if (UPD) block_sums<2>(acc, partial + 2LL * ((long long)blockIdx.y * gridDim.x + blockIdx.x));
+  if (UPD) group_sums<NR, 2>(acc, G.on, partial);
 }
 
 // The coarse tail of the V-cycle: levels t .. t + nt - 1 (the last one the
@@ -633,7 +773,7 @@ __device__ __forceinline__ MGRow mg_row(const MGLevelArgs& A, const MGGeo* c, un
   return r;
 }
 
-// (A u)_j, the row's order of terms as in mg_apply
+// (A u)_j, terms in the order of the per-level kernels
 __device__ __forceinline__ double mg_row_apply(const MGRow& r, const double* u, double uj) {
   double s = r.dg * uj;
 #pragma unroll
@@ -728,59 +868,68 @@ mg_tail_kernel(MGTailArgs T, double w, int sweeps, const double* __restrict__ bt
 
 // u' = w D^-1 b + alpha P e (the pre-smoothed u plus the prolonged correction),
 // then one damped-Jacobi sweep: out = u' + w D^-1 (b - A u').  On level 0, out is
-// the CG's z and the partial sums of r.z go to partial_rz.
-template <bool FINEST>
+// the CG's z and the partial sums of r.z go to partial_rz.  A pair's two nodes lie in one
+// aggregate, as do those of each neighbour pair.
+template <bool FINEST, int NR>
 __global__ void __launch_bounds__(kThreads)
-mg_correct_kernel(MGLevelArgs L, MGGeo c, double w, double alpha, const double* __restrict__ b,
-                  long long b_stride, const double* __restrict__ e, long long e_stride,
-                  double* out, long long out_stride, double* partial_rz, const CGState* st) {
-  if (st[blockIdx.y].done) return;
-  b += blockIdx.y * b_stride;
-  e += blockIdx.y * e_stride;
-  out += blockIdx.y * out_stride;
-  const unsigned N = (unsigned)L.g.nx * L.g.ny * L.g.nz;
-  const unsigned sxc = (unsigned)c.ny * c.nz;
-  auto parent = [&](int x, int y, int z) {
-    return (unsigned)(x >> 1) * sxc + (unsigned)(y >> 1) * c.nz + (unsigned)(z >> 1);
-  };
-  double acc[1] = {0.0};
-  for (unsigned j = xcd_remap(blockIdx.x, gridDim.x) * kThreads + threadIdx.x; j < N; j += gridDim.x * kThreads) {
+mg_correct_kernel(MGLevelArgs L, PairGeo g, MGGeo c, double w, double alpha,
+                  const double* __restrict__ b,
+                   long long b_stride, const double* __restrict__ e, long long e_stride,
+                   double* out, long long out_stride, double* partial_rz, const CGState* st,
+                   int nrhs) {
+  const Group<NR> G = group_of<NR>(st, nrhs);
+  if (!G.any) return;
+  double acc[NR];
+#pragma unroll
+  for (int s = 0; s < NR; ++s) acc[s] = 0.0;
+  const unsigned sxc = (unsigned)c.ny * c.nz, syc = (unsigned)c.nz;
+  for (unsigned t = xcd_remap(blockIdx.x, gridDim.x) * kThreads + threadIdx.x; t < g.pairs;
+       t += gridDim.x * kThreads) {
     int x, y, z;
-    mg_coords(j, L.g, x, y, z);
-    const Hood h = mg_hood(j, x, y, z, L.g);
-    // the node and its six neighbours (a clamped one is j itself, weight 0): D^-1, b
-    // and the coarse correction of the aggregate, all loaded before any is used
-    double dv[7], bv[7], ev[7], c[6];
-    {
-      unsigned m[7], P[7];
-      m[6] = j;
-      P[6] = parent(x, y, z);
+    const unsigned j = pair_at(t, g, x, y, z);
+    const PairHood h = pair_hood<64>(j, x, y, z, g.nx, g.ny, g.nz);
+    // aggregates: the pair's and its neighbour pairs'; along z the next pair is the
+    // next aggregate
+    const unsigned P = (unsigned)(x >> 1) * sxc + (unsigned)(y >> 1) * syc + (unsigned)(z >> 1);
+    const unsigned Pn[4] = {h.in[0] && (x & 1) ? P + sxc : P, h.in[1] && !(x & 1) ? P - sxc : P,
+                            h.in[2] && (y & 1) ? P + syc : P, h.in[3] && !(y & 1) ? P - syc : P};
+    const unsigned Pe = h.ze < j ? P - 1 : h.ze > j ? P + 1 : P;
+    d2 c6[6];
+    pair_weights(h, L.ax, L.ay, L.az, c6);
+    const PairVals dv = pair_load(L.dinv, h);
+    const d2 dg = ld2(L.diag, j);
 #pragma unroll
-      for (int k = 0; k < 6; ++k) {
-        const int dx = (k == 0) - (k == 1), dy = (k == 2) - (k == 3), dz = (k == 4) - (k == 5);
-        m[k] = h.j[k];
-        P[k] = h.in[k] ? parent(x + dx, y + dy, z + dz) : P[6];
-      }
-      hood_weights(j, h, L.ax, L.ay, L.az, c);
+    for (int s = 0; s < NR; ++s) {
+      const PairVals r = pair_load(b + G.sys[s] * b_stride, h);
+      const double* es = e + G.sys[s] * e_stride;
+      // u' = w D^-1 b + alpha P e on active nodes, 0 elsewhere
+      auto up1 = [&](double d, double bv, double ev) {
+        return d == 0.0 ? 0.0 : w * d * bv + alpha * ev;
+      };
+      auto up2 = [&](d2 d, d2 bv, double ev) {
+        return d2{up1(d.x, bv.x, ev), up1(d.y, bv.y, ev)};
+      };
+      PairVals u;
+      u.o = up2(dv.o, r.o, es[P]);
 #pragma unroll
-      for (int k = 0; k < 7; ++k) {
-        dv[k] = L.dinv[m[k]];
-        bv[k] = b[m[k]];
-        ev[k] = e[P[k]];
-      }
+      for (int k = 0; k < 4; ++k) u.n[k] = up2(dv.n[k], r.n[k], es[Pn[k]]);
+      u.e = 0.0;
+      if (h.edge) u.e = up1(dv.e, r.e, es[Pe]);
+      d2 up, um;
+      pair_z<64>(h, u, up, um);
+      d2 au = dg * u.o;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) au -= c6[k] * u.n[k];
+      au -= c6[4] * up;
+      au -= c6[5] * um;
+      d2 o = u.o + w * dv.o * (r.o - au);
+      if (dv.o.x == 0.0) o.x = 0.0;
+      if (dv.o.y == 0.0) o.y = 0.0;
+      if (G.on[s]) st2(out, G.sys[s] * out_stride + j, o, h.two);
+      if (FINEST) acc[s] += r.o.x * o.x + (h.two ? r.o.y * o.y : 0.0);
     }
-    // u' = w D^-1 b + alpha P e on active nodes, 0 elsewhere
-    double u[7];
-#pragma unroll
-    for (int k = 0; k < 7; ++k) u[k] = dv[k] == 0.0 ? 0.0 : w * dv[k] * bv[k] + alpha * ev[k];
-    double au = L.diag[j] * u[6];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) au -= c[k] * u[k];
-    const double o = dv[6] == 0.0 ? 0.0 : u[6] + w * dv[6] * (bv[6] - au);
-    out[j] = o;
-    if (FINEST) acc[0] += bv[6] * o;
   }
-  if (FINEST) block_sums<1>(acc, partial_rz + (long long)blockIdx.y * gridDim.x + blockIdx.x);
+  if (FINEST) group_sums<NR, 1>(acc, G.on, partial_rz);
 }
 
 // ---------------------------------------------------------------------------
@@ -1207,6 +1356,26 @@ hipError_t launch_cg_init(const PGeom& g, const double* cx, const double* cy, co
 }
 
 namespace {
+template <int NR>
+unsigned groups(int nrhs) {
+  return (unsigned)((nrhs + NR - 1) / NR);
+}
+// f(integral_constant NR) for a kernel of `threads` threads per system: NR systems per
+// workgroup.  Four share each load of the coefficients (20 systems of 272 x 64 x 88: 61.0
+// ms; 63.7 in twos), where that still leaves four workgroups for every CU; else one each,
+// so that small boxes keep their parallelism and two systems are not read as four (2 of
+// 114 x 26 x 69: 3.4 ms, in fours 4.5).
+template <typename F>
+void for_group(long long threads, int nrhs, F f) {
+  if (nrhs > 2 && threads * groups<4>(nrhs) >= 4LL * kCUs * kThreads)
+    f(std::integral_constant<int, 4>{});
+  else
+    f(std::integral_constant<int, 1>{});
+}
+PairGeo pair_geo(int nx, int ny, int nz) {
+  const unsigned row = (unsigned)(nz + 1) / 2;
+  return PairGeo{nx, ny, nz, row, (unsigned)nx * ny * row, 1.0 / ny, 1.0 / row};
+}
 MGGeo mg_geo(const MGLevel& L) { return MGGeo{L.nx, L.ny, L.nz, 1.0 / L.ny, 1.0 / L.nz}; }
 MGLevelArgs mg_args(const MGData& m, int k) {
   const MGLevel& L = m.plan.lv[k];
@@ -1223,12 +1392,16 @@ hipError_t launch_cg_iter(const PGeom& g, const double* cx, const double* cy, co
                           const double* p_old, double* p_new, double* q, double* phi,
                           double* r, double* partial, int max_iter, CGState* st,
                           hipStream_t s, int nrhs, const MGData* mg) {
-  const int nb = sp_blocks(g.NP);
-  cg_matvec_kernel<<<dim3(nb, nrhs), kThreads, 0, s>>>((unsigned)g.NP, g.px, g.py, g.pz, 1.0 / g.py,
-                                           1.0 / g.pz, cx, cy, cz, dir, z, p_old, p_new, q,
-                                           partial, st);
+  const PairGeo pg = pair_geo(g.px, g.py, g.pz);
+  const int nb = sp_blocks(pg.pairs);
+  for_group(pg.pairs, nrhs, [&](auto nr) {
+    constexpr int NR = decltype(nr)::value;
+    cg_matvec_kernel<NR><<<dim3(nb, groups<NR>(nrhs)), kThreads, 0, s>>>(
+        g.NP, pg, cx, cy, cz, dir, z, p_old, p_new, q, partial, st, nrhs);
+  });
   cg_alpha_kernel<<<dim3(1, nrhs), kRedThreads, 0, s>>>(partial, nb, st);
   if (!mg) {
+    const int nb = sp_blocks(g.NP);
     cg_update_kernel<<<dim3(nb, nrhs), kThreads, 0, s>>>(g.NP, dinv, p_new, q, phi, r, z,
                                                                partial, st);
     cg_beta_kernel<<<dim3(1, nrhs), kRedThreads, 0, s>>>(partial, nb, max_iter, st);
@@ -1238,10 +1411,13 @@ hipError_t launch_cg_iter(const PGeom& g, const double* cx, const double* cy, co
   // spent once p_new is formed) and the V-cycle's z to r's, so the caller swaps the
   // two buffers from one iteration to the next
   const MGPlan& P = mg->plan;
-  const unsigned nbu = (unsigned)sp_blocks(8 * P.lv[1].N);
-  mg_restrict_kernel<true><<<dim3(nbu, nrhs), kThreads, 0, s>>>(
-      mg_args(*mg, 0), mg_geo(P.lv[1]), kMGOmega, r, g.NP, mg->b + P.lv[1].voff, P.vtotal, st,
-      p_new, q, phi, z, partial);
+  const unsigned nbu = (unsigned)sp_blocks(4 * P.lv[1].N);
+  for_group(4 * P.lv[1].N, nrhs, [&](auto nr) {
+    constexpr int NR = decltype(nr)::value;
+    mg_restrict_kernel<true, NR><<<dim3(nbu, groups<NR>(nrhs)), kThreads, 0, s>>>(
+        mg_args(*mg, 0), mg_geo(P.lv[1]), kMGOmega, r, g.NP, mg->b + P.lv[1].voff, P.vtotal, st,
+        nrhs, p_new, q, phi, z, partial);
+  });
   const hipError_t e = launch_mg_vcycle(g, *mg, z, r, st, nrhs, s, false);
   if (e != hipSuccess) return e;
   cg_beta_mg_kernel<<<dim3(1, nrhs), kRedThreads, 0, s>>>(partial, (int)nbu, mg->partial_rz, nb,
@@ -1314,9 +1490,13 @@ hipError_t launch_mg_vcycle(const PGeom& g, const MGData& m, const double* r, do
   auto bvec = [&](int k) { return k == 0 ? r : m.b + P.lv[k].voff; };
   for (int k = restrict0 ? 0 : 1; k < t; ++k) {
     const MGLevel& C = P.lv[k + 1];
-    mg_restrict_kernel<false><<<dim3(mg_blocks(8 * C.N), nrhs), kThreads, 0, s>>>(
-        margs(m, k), mgeo(C), kMGOmega, bvec(k), k == 0 ? g.NP : vs, m.b + C.voff, vs, st,
-        nullptr, nullptr, nullptr, nullptr, nullptr);
+    for_group(4 * C.N, nrhs, [&](auto nr) {
+      constexpr int NR = decltype(nr)::value;
+      mg_restrict_kernel<false, NR>
+          <<<dim3(mg_blocks(4 * C.N), groups<NR>(nrhs)), kThreads, 0, s>>>(
+              margs(m, k), mgeo(C), kMGOmega, bvec(k), k == 0 ? g.NP : vs, m.b + C.voff, vs, st,
+              nrhs, nullptr, nullptr, nullptr, nullptr, nullptr);
+    });
   }
   MGTailArgs T{};
   T.t = t;
@@ -1328,14 +1508,22 @@ hipError_t launch_mg_vcycle(const PGeom& g, const MGData& m, const double* r, do
                                                          vs, st);
   for (int k = t - 1; k >= 1; --k) {
     const MGLevel &F = P.lv[k], &C = P.lv[k + 1];
-    mg_correct_kernel<false><<<dim3(mg_blocks(F.N), nrhs), kThreads, 0, s>>>(
-        margs(m, k), mgeo(C), kMGOmega, 1.0, m.b + F.voff, vs, m.u + C.voff, vs, m.u + F.voff,
-        vs, nullptr, st);
+    const PairGeo pg = pair_geo(F.nx, F.ny, F.nz);
+    for_group(pg.pairs, nrhs, [&](auto nr) {
+      constexpr int NR = decltype(nr)::value;
+      mg_correct_kernel<false, NR><<<dim3(mg_blocks(pg.pairs), groups<NR>(nrhs)), kThreads, 0, s>>>(
+          margs(m, k), pg, mgeo(C), kMGOmega, 1.0, m.b + F.voff, vs, m.u + C.voff, vs, m.u + F.voff,
+          vs, nullptr, st, nrhs);
+    });
   }
   const MGLevel& C1 = P.lv[1];
-  mg_correct_kernel<true><<<dim3(sp_blocks(g.NP), nrhs), kThreads, 0, s>>>(
-      margs(m, 0), mgeo(C1), kMGOmega, kMGAlpha, r, g.NP, m.u + C1.voff, vs, z, g.NP,
-      m.partial_rz, st);
+  const PairGeo pg = pair_geo(g.px, g.py, g.pz);
+  for_group(pg.pairs, nrhs, [&](auto nr) {
+    constexpr int NR = decltype(nr)::value;
+    mg_correct_kernel<true, NR><<<dim3(mg_blocks(pg.pairs), groups<NR>(nrhs)), kThreads, 0, s>>>(
+        margs(m, 0), pg, mgeo(C1), kMGOmega, kMGAlpha, r, g.NP, m.u + C1.voff, vs, z, g.NP,
+        m.partial_rz, st, nrhs);
+  });
   return hipGetLastError();
 }
 
@@ -1343,7 +1531,8 @@ hipError_t launch_mg_start(const PGeom& g, const MGData& m, const double* r, dou
                            CGState* st, int nrhs, hipStream_t s) {
   const hipError_t e = launch_mg_vcycle(g, m, r, z, st, nrhs, s, true);
   if (e != hipSuccess) return e;
-  cg_rz_kernel<<<dim3(1, nrhs), kRedThreads, 0, s>>>(m.partial_rz, sp_blocks(g.NP), st);
+  cg_rz_kernel<<<dim3(1, nrhs), kRedThreads, 0, s>>>(
+      m.partial_rz, sp_blocks(pair_geo(g.px, g.py, g.pz).pairs), st);
   return hipGetLastError();
 }
 

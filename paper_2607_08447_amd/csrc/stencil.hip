@@ -90,7 +90,7 @@ struct Place {
 // 480 FP32 recurrence workgroups (12 vectors of 128 x 40 x 40): 63 us in one range, 68
 // in two; 384 (4 vectors of 256 x 48 x 48): 81 in one, 64 in four; 144 FP64 product
 // ones (6 vectors of 96 x 32 x 32): 53 in one, 35 in two, 28 in three, 30 in four.
-constexpr int kCUs = 256, kMaxSplit = 12;
+constexpr int kMaxSplit = 12;
 __host__ __device__ inline int z_ranges(int nlw, int nz, int zmax, float c0) {
   constexpr float inv[kMaxSplit] = {1.0f,     1.0f / 2, 1.0f / 3, 1.0f / 4,  1.0f / 5,  1.0f / 6,
                                     1.0f / 7, 1.0f / 8, 1.0f / 9, 1.0f / 10, 1.0f / 11, 1.0f / 12};
