@@ -9,8 +9,9 @@
 //     dH/dB_b = Z_b + i (e / 2 hbar) eps_bcd (R - r0)_c H_0 (R - r0)_d,
 // Z_b the on-site Zeeman matrix per tesla and R the position.  So everything
 // needed for four states psi_i comes from one B = 0 stencil apply to the 16
-// vectors {psi_i, R_x psi_i, R_y psi_i, R_z psi_i} and one Gram product of those
-// 16 against themselves, their images under H_0 and Z_b psi_i (16 x 44).  The
+// vectors {psi_i, R_x psi_i, R_y psi_i, R_z psi_i}, formed from psi as they are read,
+// and one Gram product of those 16 against their images under H_0, psi_i and Z_b psi_i
+// (16 x 32), which reads psi and the images alone.  The
 // origin of each doublet's gauge is its own centre of charge, which enters the
 // small matrices only.  Everything after the Gram product is 4 x 4 algebra done
 // by a few threads of one workgroup.
@@ -21,8 +22,6 @@
 namespace hkp {
 
 namespace {
-
-constexpr int kT = 256;
 
 __device__ __forceinline__ double2 cadd(double2 a, double2 b) {
   return make_double2(a.x + b.x, a.y + b.y);
@@ -143,69 +142,133 @@ __device__ void qubit_frame(const double v[3], double R[3][3]) {
   rotation(u, atan2(s, c), R);
 }
 
-// [v][c][p] internal block (LS, p = (z ny + y) nx + x): slots 4 (a + 1) + v <- r_a psi_v,
-// r about the box centre
-__global__ void __launch_bounds__(kT)
-position_weight_kernel(int nx, int ny, int nz, double h, double2* buf) {
-  const long long N = (long long)nx * ny * nz;
-  const long long p = (long long)blockIdx.x * kT + threadIdx.x;
-  const int v = blockIdx.y;
-  if (p >= N) return;
-  const int x = (int)(p % nx), y = (int)((p / nx) % ny), z = (int)(p / ((long long)nx * ny));
-  const double r[3] = {(x - 0.5 * (nx - 1)) * h, (y - 0.5 * (ny - 1)) * h,
-                       (z - 0.5 * (nz - 1)) * h};
-  const long long n6 = 6 * N;
-  for (int c = 0; c < 6; ++c) {
-    const double2 val = buf[v * n6 + c * N + p];
-    for (int a = 0; a < 3; ++a) buf[(4 * (a + 1) + v) * n6 + c * N + p] = cscale(val, r[a]);
-  }
+typedef double d4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ d4 mfma(double a, double b, d4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// slots 32 + 4 b + v <- Z_b psi_v, Z_b = mu_B [(3 kappa - 1) 1 (x) L_b + sigma_b (x) 1]
-// in the |L S> basis (component 3 s + o), (L_b)_oo' = -i eps_boo'
-__global__ void __launch_bounds__(kT)
-zeeman_derivative_kernel(long long N, double g_orb, double2* buf) {
-  const long long p = (long long)blockIdx.x * kT + threadIdx.x;
-  const int v = blockIdx.y;
-  if (p >= N) return;
-  const long long n6 = 6 * N;
-  double2 ps[2][3];
-  for (int s = 0; s < 2; ++s)
-    for (int o = 0; o < 3; ++o) ps[s][o] = buf[v * n6 + (3 * s + o) * N + p];
-  for (int b = 0; b < 3; ++b) {
-    double2* out = buf + (32 + 4 * b + v) * n6 + p;
-    for (int s = 0; s < 2; ++s) {
-      for (int o = 0; o < 3; ++o) {
-        double2 orb = make_double2(0.0, 0.0);
-        for (int o2 = 0; o2 < 3; ++o2) {
-          const double e = levi(b, o, o2);
-          if (e != 0.0) orb = cadd(orb, cscale(ps[s][o2], e));
-        }
-        orb = cscale(times_i(orb), -g_orb);   // -i eps psi, times mu_B (3 kappa - 1)
-        double2 spin;
-        if (b == 0) {
-          spin = ps[1 - s][o];
-        } else if (b == 1) {
-          spin = s == 0 ? cscale(times_i(ps[1][o]), -1.0) : times_i(ps[0][o]);
-        } else {
-          spin = s == 0 ? ps[0][o] : cscale(ps[1][o], -1.0);
-        }
-        out[(3 * s + o) * N] = cadd(orb, cscale(spin, kMuB));
+constexpr int kGmChunks = 512;    // workgroups of the Gram product (two per CU)
+constexpr int kGmCols = 32;
+
+// Partial Gram products G = L^H [H_0 L, psi, Z psi] over a chunk of points, L = {psi, x psi,
+// y psi, z psi} (vector 4 c + i; coordinates about the box centre), Z_b = mu_B [(3 kappa -
+// 1) 1 (x) L_b + sigma_b (x) 1] in the |L S> basis (component 3 s + o), (L_b)_oo' = -i
+// eps_boo'.  Internal layout [v][c][p], p = (z ny + y) nx + x.
+//
+// A lane holds row and column r = 4 c + i (lane & 15) of the two 16 x 16 tiles at one of
+// four points (lane >> 4).  It loads psi_i's six components once per point and forms its
+// row r_c psi_i and its column psi_i or Z_(c-1) psi_i from them in registers (a column's
+// Zeeman matrix is lane-dependent coefficients on the same few terms), so 20 vectors are
+// read.  With the Zeeman vectors stored and the weighted ones read as well, 44 were: 711 us
+// and 146 to store, 256 x 48 x 48; 326 so.  Bound by the matrix unit (48 FP64 MFMAs of 64
+// cycles per four points are 184 us there) and by the loads' latency (two waves a SIMD).
+__global__ void __launch_bounds__(256, 2)
+gmatrix_gram_kernel(int nx, int ny, int nz, double inx, double iny, double h, double g_orb,
+                    const double2* __restrict__ psi, const double2* __restrict__ img,
+                    unsigned chunk, double2* __restrict__ partial) {
+  __shared__ double2 red[4][16][17];
+  const unsigned N = (unsigned)nx * ny * nz;
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int r = lane & 15, q = lane >> 4, kind = r >> 2;
+  const unsigned c0 = blockIdx.x * chunk, c1 = min(c0 + chunk, N);
+  const unsigned per = chunk / 4;   // a wave's share: a multiple of four points
+  const unsigned e0 = min(c0 + wv * per, c1), e1 = min(e0 + per, c1);
+  const double2* pp = psi + (size_t)(r & 3) * 6 * N;
+  const double2* pi = img + (size_t)r * 6 * N;
+  // column coefficients: on psi[s][o] (ks), on psi[1-s][o] (kx, and +-i ky), orbital (m)
+  const double ks[2] = {kind == 0 ? 1.0 : kind == 3 ? kMuB : 0.0,
+                        kind == 0 ? 1.0 : kind == 3 ? -kMuB : 0.0};
+  const double kx = kind == 1 ? kMuB : 0.0;
+  const double ky[2] = {kind == 2 ? -kMuB : 0.0, kind == 2 ? kMuB : 0.0};
+  const double m0 = kind == 1 ? g_orb : 0.0, m1 = kind == 2 ? g_orb : 0.0,
+               m2 = kind == 3 ? g_orb : 0.0;
+  d4 re[2], im[2];
+  re[0] = re[1] = im[0] = im[1] = d4{0, 0, 0, 0};
+  double2 P[6], H[6], Pn[6], Hn[6];
+  auto load = [&](unsigned p, double2 (&a)[6], double2 (&b)[6]) {
+    const unsigned e = p < e1 ? p : N - 1;   // past the end: read, and zeroed below
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      a[c] = pp[(size_t)c * N + e];
+      b[c] = pi[(size_t)c * N + e];
+    }
+  };
+  if (e0 < e1) load(e0 + q, P, H);
+  for (unsigned p0 = e0; p0 < e1; p0 += 4) {
+    const unsigned p = p0 + q;
+    load(p + 4, Pn, Hn);
+    if (p >= e1)
+#pragma unroll
+      for (int c = 0; c < 6; ++c) P[c] = H[c] = make_double2(0.0, 0.0);
+    const unsigned row = udiv(p, (unsigned)nx, inx), z = udiv(row, (unsigned)ny, iny);
+    const int x = (int)(p - row * (unsigned)nx), y = (int)(row - z * (unsigned)ny);
+    const double w = kind == 0   ? 1.0
+                     : kind == 1 ? (x - 0.5 * (nx - 1)) * h
+                     : kind == 2 ? (y - 0.5 * (ny - 1)) * h
+                                 : ((int)z - 0.5 * (nz - 1)) * h;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      const int s = c / 3, o = c % 3;
+      const double2 *u = P + 3 * s, f = P[3 * (1 - s) + o];
+      // (eps psi)_o of the lane's axis
+      const double2 l = o == 0   ? csub(cscale(u[1], m2), cscale(u[2], m1))
+                        : o == 1 ? csub(cscale(u[2], m0), cscale(u[0], m2))
+                                 : csub(cscale(u[0], m1), cscale(u[1], m0));
+      const double2 t = make_double2(ks[s] * u[o].x + kx * f.x - ky[s] * f.y + l.y,
+                                     ks[s] * u[o].y + kx * f.y + ky[s] * f.x - l.x);
+      const double2 a = cscale(u[o], w);
+      const double2 b[2] = {H[c], t};
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        re[k] = mfma(a.x, b[k].x, re[k]);
+        im[k] = mfma(a.x, b[k].y, im[k]);
+        re[k] = mfma(a.y, b[k].y, re[k]);
+        im[k] = mfma(-a.y, b[k].x, im[k]);
       }
     }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      P[c] = Pn[c];
+      H[c] = Hn[c];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) red[wv][4 * g + q][r] = make_double2(re[k][g], im[k][g]);
+    __syncthreads();
+    const int i = threadIdx.x >> 4, j = threadIdx.x & 15;
+    double2 sum = red[0][i][j];
+#pragma unroll
+    for (int v = 1; v < 4; ++v) sum = cadd(sum, red[v][i][j]);
+    partial[((size_t)blockIdx.x * 16 + i) * kGmCols + 16 * k + j] = sum;
+    __syncthreads();
   }
 }
 
-// 4 x 4 blocks of the Gram product G = L^H [L, H_0 L, Z psi] (16 x 44, row-major):
-// slot 4 c + i is r_c psi_i (c = 0: psi itself)
+// G[e] = sum of the chunks' partials: one wave per entry, in a fixed order
+__global__ void __launch_bounds__(256)
+gmatrix_reduce_kernel(int nchunks, const double2* __restrict__ partial, double2* G) {
+  const int e = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  double2 s = make_double2(0.0, 0.0);
+  for (int k = lane; k < nchunks; k += 64) s = cadd(s, partial[(size_t)k * 16 * kGmCols + e]);
+  for (int off = 32; off > 0; off >>= 1) {
+    s.x += __shfl_down(s.x, off, 64);
+    s.y += __shfl_down(s.y, off, 64);
+  }
+  if (lane == 0) G[e] = s;
+}
+
+// 4 x 4 blocks of the Gram product G = L^H [H_0 L, psi, Z psi] (16 x 32, row-major):
+// row 4 c + i is r_c psi_i (c = 0: psi itself)
 __device__ __forceinline__ double2 gW(const double2* G, int c, int i, int d, int j) {
-  return G[(4 * c + i) * 44 + 16 + 4 * d + j];   // <r_c psi_i | H_0 | r_d psi_j>
+  return G[(4 * c + i) * kGmCols + 4 * d + j];        // <r_c psi_i | H_0 | r_d psi_j>
 }
 __device__ __forceinline__ double2 gX(const double2* G, int a, int i, int j) {
-  return G[i * 44 + 4 * (a + 1) + j];            // <psi_i | r_a | psi_j>
+  return G[(4 * (a + 1) + i) * kGmCols + 16 + j];     // <psi_i | r_a | psi_j>
 }
 __device__ __forceinline__ double2 gZ(const double2* G, int b, int i, int j) {
-  return G[i * 44 + 32 + 4 * b + j];             // <psi_i | Z_b | psi_j>
+  return G[i * kGmCols + 16 + 4 * (b + 1) + j];       // <psi_i | Z_b | psi_j>
 }
 
 __device__ void sym_g(const double g[3][3], double out[3][3]) {
@@ -242,11 +305,11 @@ __device__ void doublet_basis(int k, const double2 (&C)[4][4], double2 (&U)[4][2
 // take the doublets' centres; twelve take one (doublet, field direction) column of
 // g each; four take the symmetric tensors.
 __global__ void gmatrix_post_kernel(const double2* __restrict__ Gg, hkp_gmatrix_result* out) {
-  __shared__ double2 G[16 * 44];   // the whole Gram block, staged once by the workgroup
+  __shared__ double2 G[16 * kGmCols];   // the whole Gram block, staged once by the workgroup
   __shared__ double2 sC[4][4];
   __shared__ double sR0[4][3], sg[4][3][3];
   const int t = threadIdx.x;
-  for (int i = t; i < 16 * 44; i += blockDim.x) G[i] = Gg[i];
+  for (int i = t; i < 16 * kGmCols; i += blockDim.x) G[i] = Gg[i];
   __syncthreads();
   if (t == 0) {   // the dots' doublets: eigenvectors of x within the span, lower x first
     double2 Xx[4][4], C[4][4];
@@ -416,20 +479,29 @@ __global__ void st_model_kernel(const hkp_gmatrix_result* __restrict__ gm,
   P.J_par_eV = P.Jtilde_eV[2][2];
 }
 
-unsigned blocks(long long n) { return (unsigned)((n + kT - 1) / kT); }
+// chunks of the Gram product: at least sixteen points each
+int gm_chunks(long long N) {
+  const long long c = (N + 15) / 16;
+  return (int)(c < kGmChunks ? c : kGmChunks);
+}
 
 }  // namespace
 
-hipError_t launch_position_weight(int nx, int ny, int nz, double h, double* buf, hipStream_t s) {
-  const long long N = (long long)nx * ny * nz;
-  position_weight_kernel<<<dim3(blocks(N), 4), kT, 0, s>>>(nx, ny, nz, h,
-                                                           reinterpret_cast<double2*>(buf));
-  return hipGetLastError();
+size_t gmatrix_partial_bytes(long long N) {
+  return (size_t)gm_chunks(N) * 16 * kGmCols * sizeof(double2);
 }
 
-hipError_t launch_zeeman_derivative(long long N, double kappa, double* buf, hipStream_t s) {
-  zeeman_derivative_kernel<<<dim3(blocks(N), 4), kT, 0, s>>>(
-      N, kMuB * (3.0 * kappa - 1.0), reinterpret_cast<double2*>(buf));
+hipError_t launch_gmatrix_gram(int nx, int ny, int nz, double h, double kappa, const double* psi,
+                               const double* img, double* partial, double* G, hipStream_t s) {
+  const long long N = (long long)nx * ny * nz;
+  const int nc = gm_chunks(N);
+  const unsigned chunk = (unsigned)((N + 16LL * nc - 1) / (16LL * nc) * 16);
+  gmatrix_gram_kernel<<<nc, 256, 0, s>>>(
+      nx, ny, nz, 1.0 / nx, 1.0 / ny, h, kMuB * (3.0 * kappa - 1.0),
+      reinterpret_cast<const double2*>(psi), reinterpret_cast<const double2*>(img), chunk,
+      reinterpret_cast<double2*>(partial));
+  gmatrix_reduce_kernel<<<16 * kGmCols / 4, 256, 0, s>>>(
+      nc, reinterpret_cast<const double2*>(partial), reinterpret_cast<double2*>(G));
   return hipGetLastError();
 }
 

@@ -33,6 +33,17 @@ __device__ __forceinline__ int xcd_remap(int wg, int nwg) {
   return x * per + (x < rem ? x : rem) + idx;
 }
 
+// n / d for n < 2^31 from a double reciprocal, corrected to the exact floor
+// (the product is within a tiny fraction of n / d, so one step either way
+// suffices); integer division by a runtime divisor costs far more
+__device__ __forceinline__ unsigned udiv(unsigned n, unsigned d, double inv) {
+  unsigned q = (unsigned)((double)n * inv);
+  const unsigned long long qd = (unsigned long long)q * d;
+  if (qd > n) --q;
+  else if (qd + d <= n) ++q;
+  return q;
+}
+
 constexpr int kCUs = 256;   // compute units of the GPU
 
 // unit constants from CODATA 2018 (h, e exact; m0 = 9.1093837015e-31 kg),
@@ -99,6 +110,9 @@ struct StencilLaunch {
   int zsplit;            // z ranges per (vector, tile): 0 never, 1 for small launches, 2 always two
   int fp64;              // kernel type
   int ncomp = 6;         // components per vector: 6 (spinor) or 3 (spin-free orbital, no field)
+  int weighted = 0;      // FP64, no field, no old block: input vector 4 c + i is vector i of
+                         // `in` times 1 (c = 0), or the x, y, z coordinate about the box
+  double h = 0.0;        // centre (c = 1, 2, 3; spacing h), nvec = 16
 };
 
 hipError_t launch_stencil(const StencilLaunch& a, const StencilConsts<double>& c,
@@ -448,8 +462,11 @@ hipError_t launch_anderson(const PGeom& g, int k, int m, int slot, double mixing
 // slots 32 + 4 b + v <- Z_b psi_v (Zeeman matrix per tesla); the post kernel turns
 // the 16 x 44 Gram product of slots 0-15 against 0-43 (slots 16-31 = H_0 of 0-15)
 // into an hkp_gmatrix_result
-hipError_t launch_position_weight(int nx, int ny, int nz, double h, double* buf, hipStream_t s);
-hipError_t launch_zeeman_derivative(long long N, double kappa, double* buf, hipStream_t s);
+// G [16][32] = {psi, r psi}^H [H_0 {psi, r psi}, psi, Z psi] from psi (4 vectors) and img = H_0
+// {psi, r psi} (16), internal layout; partial: gmatrix_partial_bytes(N)
+size_t gmatrix_partial_bytes(long long N);
+hipError_t launch_gmatrix_gram(int nx, int ny, int nz, double h, double kappa, const double* psi,
+                               const double* img, double* partial, double* G, hipStream_t s);
 hipError_t launch_gmatrix_post(const double* G, void* out, hipStream_t s);
 hipError_t launch_st_model(const void* gm, const double* J, const double n_so[3], double lambda,
                            double d, int nB, const double* B, void* pts, void* H, hipStream_t s);

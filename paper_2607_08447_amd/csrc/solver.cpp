@@ -1292,13 +1292,10 @@ int run_filter_step2(const Filter2Args& A, int* passes) {
 // L^H [L, H_0 L, Z psi] (16 x 44; L, the first 16 vectors of the block, is read twice
 // by the same workgroup, the second time from cache).
 // ---------------------------------------------------------------------------
-constexpr int kGmSlots = 44;
-
 size_t gmatrix_bytes(const hkp_grid& g) {
   const size_t N = (size_t)g.nx * g.ny * g.nz, n6 = 6 * N;
-  return align_up(6 * N * 8) + align_up((size_t)kGmSlots * n6 * 16) +
-         align_up(gram_partial_bytes(kGmSlots, (long long)n6, 1)) +
-         align_up((size_t)16 * kGmSlots * 16);
+  return align_up(6 * N * 8) + align_up(4 * n6 * 16) + align_up(16 * n6 * 16) +
+         align_up(gmatrix_partial_bytes((long long)N)) + align_up((size_t)16 * 32 * 16);
 }
 
 int run_gmatrix(const GMatrixArgs& A) {
@@ -1313,23 +1310,25 @@ int run_gmatrix(const GMatrixArgs& A) {
     return p;
   };
   double* D64 = (double*)take(6 * N * 8);
-  double* buf = (double*)take((size_t)kGmSlots * n6 * 16);
-  double* partial = (double*)take(gram_partial_bytes(kGmSlots, (long long)n6, 1));
-  double* G = (double*)take((size_t)16 * kGmSlots * 16);
+  double* psi = (double*)take(4 * n6 * 16);
+  double* img = (double*)take(16 * n6 * 16);
+  double* partial = (double*)take(gmatrix_partial_bytes((long long)N));
+  double* G = (double*)take((size_t)16 * 32 * 16);
   const double B0[3] = {0.0, 0.0, 0.0};
   HKP_CHECK(launch_onsite(A.mat, g.nx, g.ny, g.nz, 1, A.V, 0, A.strain, D64, nullptr, 0, s));
-  HKP_CHECK(launch_abi_to_internal(g.nx, g.ny, g.nz, g.h_nm, B0, 4, A.psi, buf, 0, s));
-  HKP_CHECK(launch_position_weight(g.nx, g.ny, g.nz, g.h_nm, buf, s));
+  HKP_CHECK(launch_abi_to_internal(g.nx, g.ny, g.nz, g.h_nm, B0, 4, A.psi, psi, 0, s));
   StencilLaunch a{};
   a.nx = g.nx;
   a.ny = g.ny;
   a.nz = g.nz;
   a.nvec = 16;
   a.batch = 1;
-  a.in = buf;
+  a.in = psi;
   a.old = nullptr;
   a.old_fp64 = 1;
-  a.out = buf + 2 * 16 * n6;   // slot 16 (two doubles per complex entry)
+  a.out = img;
+  a.weighted = 1;
+  a.h = g.h_nm;
   a.out_fp64 = 1;
   a.D = D64;
   a.strain = A.strain != nullptr;
@@ -1337,15 +1336,12 @@ int run_gmatrix(const GMatrixArgs& A) {
   a.coef.shift = 0.0;
   a.coef.beta = 0.0;
   a.tile_y = A.st.tile_y;
-  a.vgroup = A.st.vgroup;
+  a.vgroup = 16;   // a tile's sixteen inputs come from the same four vectors
   a.dma = A.st.dma;
   a.zsplit = A.st.zsplit;
   a.fp64 = 1;
   HKP_CHECK(launch_stencil(a, make_consts(A.mat, g.h_nm, B0), s));
-  HKP_CHECK(launch_zeeman_derivative((long long)N, A.mat.kappa, buf, s));
-  const BlockDesc L{buf, (long long)n6, 16, 0};
-  const BlockDesc R{buf, (long long)n6, kGmSlots, 0};
-  HKP_CHECK(launch_gram(L, R, 0, 1, partial, G, nullptr, s));
+  HKP_CHECK(launch_gmatrix_gram(g.nx, g.ny, g.nz, g.h_nm, A.mat.kappa, psi, img, partial, G, s));
   HKP_CHECK(launch_gmatrix_post(G, A.out, s));
   return HKP_OK;
 }

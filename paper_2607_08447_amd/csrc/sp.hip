@@ -40,17 +40,6 @@ __device__ __forceinline__ Geo geo(int px, int py, int pz, double ipy, double ip
   return Geo{px, py, pz, (unsigned)py * (unsigned)pz, (unsigned)pz, ipy, ipz};
 }
 
-// n / d for n < 2^31 from a double reciprocal, corrected to the exact floor
-// (the product is within a tiny fraction of n / d, so one step either way
-// suffices); integer division by a runtime divisor costs far more
-__device__ __forceinline__ unsigned udiv(unsigned n, unsigned d, double inv) {
-  unsigned q = (unsigned)((double)n * inv);
-  const unsigned long long qd = (unsigned long long)q * d;
-  if (qd > n) --q;
-  else if (qd + d <= n) ++q;
-  return q;
-}
-
 // (x, y, z) of box node i
 __device__ __forceinline__ void coords(unsigned i, const Geo& g, int& x, int& y, int& z) {
   const unsigned q = udiv(i, g.sy, g.ipz);   // x * py + y

@@ -64,6 +64,7 @@ struct KArgs {
   int nx, ny, nz, nvec;
   int tiles_x, tiles_y;
   int vgroup;   // vectors of one tile run side by side (1: vector-major)
+  double h;     // weighted inputs: the grid spacing
   StencilConsts<T> k;
 };
 
@@ -200,7 +201,12 @@ constexpr int pipe_waves(int ph, bool old, int ty) {
 // barrier at the end waits for LDS alone.
 // A lane's offsets are 32-bit bytes from a uniform base; TY = 1 (nx beyond 2^22) takes
 // 64-bit ones.
-template <typename T, typename TO, typename TW, int PH, bool STR, int TX, int TY, int NC = 6>
+// WGT: the input is formed on its way to LDS, vector 4 c + i from vector i times 1 or a
+// coordinate about the box centre (the g-matrices' twelve weighted vectors are never
+// stored: of 256 x 48 x 48 429 us for the sixteen, 441 from stored ones and 161 to store
+// them; the four that share their inputs run side by side).
+template <typename T, typename TO, typename TW, int PH, bool STR, int TX, int TY, int NC = 6,
+          bool WGT = false>
 __global__ void __launch_bounds__(64 * TY * (NC / 3), pipe_waves<T>(PH, !std::is_same<TO, void>::value, TY))
 stencil_pipe_kernel(KArgs<T> a) {
   static_assert(NC == 6 || (NC == 3 && PH == 0), "spin-free vectors carry no field terms");
@@ -240,7 +246,8 @@ stencil_pipe_kernel(KArgs<T> a) {
   // bases at this tile's first row (uniform); lane offsets in bytes from there
   const size_t row0 = (size_t)ty0 * nx;
   const long long vb = (long long)pl.vec * NC * N;
-  const T* in = a.in + 2 * ((long long)pl.b * a.in_bstride + vb);
+  const T* in = a.in + 2 * ((long long)pl.b * a.in_bstride +
+                            (WGT ? (long long)(pl.vec & 3) * NC * N : vb));
   // (without an old block its loads read the block's first entry and are not used)
   const TOv* oldp = has_old ? reinterpret_cast<const TOv*>(a.old) +
                                   2 * ((long long)pl.b * a.old_bstride + vb + (long long)X * N + row0)
@@ -274,11 +281,16 @@ stencil_pipe_kernel(KArgs<T> a) {
   Off soff[NS];
   int sidx[NS];
   bool sval[NS];
+  T wgt[WGT ? NS : 1];   // a slot's weight (x, y), and the plane's (z)
+  const int waxis = WGT ? pl.vec >> 2 : 0;
+  auto centred = [&](int i, int n) { return (T)((i - 0.5 * (n - 1)) * a.h); };
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
     const int slot = tid + s * NT;
     const int row = slot / W, colx = slot - row * W;
     const int x = tx0 + colx - 1, y = ty0 + row - 1;
+    if constexpr (WGT)
+      wgt[s] = waxis == 1 ? centred(x, nx) : waxis == 2 ? centred(y, ny) : (T)1;
     sval[s] = slot < PLANE && x >= 0 && x < nx && y >= 0 && y < ny;
     soff[s] = sval[s] ? (Off)((Off)(row - 1 + up) * (Off)nx + (Off)x) * (Off)sizeof(cx<T>)
                       : (Off)tx0 * (Off)sizeof(cx<T>);
@@ -313,9 +325,13 @@ stencil_pipe_kernel(KArgs<T> a) {
   };
   auto commit = [&](int z) {
     cx<T>* dst = lds + (z & 1) * BUF;
+    const T wz = WGT && waxis == 3 ? centred(z < nz ? z : nz - 1, nz) : (T)1;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       if (PLANE % NT != 0 && sidx[s] < 0) continue;
+      if constexpr (WGT)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) R[s][c] = scl(wgt[s] * wz, R[s][c]);
 #pragma unroll
       for (int c = 0; c < NC; ++c)
         dst[c * PLANE + sidx[s]] = sval[s] ? R[s][c] : mk<T>(0, 0);
@@ -663,6 +679,7 @@ hipError_t launch_t(const StencilLaunch& L, const StencilConsts<double>& c, hipS
   a.stream = entries * (2 * sizeof(T) + 2 * sizeof(TW) +
                         (L.old && L.old != L.out ? 2 * (L.old_fp64 ? 8 : 4) : 0)) > kCacheBytes;
   a.k = cast_consts<T>(c);
+  a.h = L.h;
   const int ty = L.tile_y;
   constexpr unsigned NSP = NC / 3;   // spin waves per row
   auto go = [&](auto kernel, int tx, int rows, int waves) {
@@ -689,6 +706,17 @@ hipError_t launch_t(const StencilLaunch& L, const StencilConsts<double>& c, hipS
     kernel<<<dim3((unsigned)(nwg * a.zsplit)), dim3(64, waves, NSP), 0, s>>>(a);
     return hipGetLastError();
   };
+  constexpr bool can_weight = sizeof(T) == 8 && std::is_same<TO, void>::value && PH == 0 && NC == 6;
+  if constexpr (can_weight) {
+    if (L.weighted) {
+      if (L.nvec != 16 || part || L.batch != 1 || L.work) return hipErrorInvalidValue;
+      if (L.nx > (1 << 22)) return go(stencil_pipe_kernel<T, TO, TW, PH, STR, 64, 1, NC, true>, 64, 1, 1);
+      return L.nx <= 16 ? go(stencil_pipe_kernel<T, TO, TW, PH, STR, 16, 2, NC, true>, 16, 8, 2)
+                        : go(stencil_pipe_kernel<T, TO, TW, PH, STR, 32, 2, NC, true>, 32, 4, 2);
+    }
+  } else if (L.weighted) {
+    return hipErrorInvalidValue;
+  }
   // Row copies or register staging.  FP64 on whole 64-wide tiles copies rows (its step
   // in cache-sized groups: 58 us copied, 61 staged, 2 vectors of 256 x 48 x 48; 14
   // orbitals of 128 x 37 x 37 63 and 68; H X of 40 vectors 1057 and 1081).  FP32 is
