@@ -139,7 +139,7 @@ __global__ void phase_kernel(int nx, int nz, double h, double Bx, double By, dou
 // fastest.  A workgroup converts a 16 x 16 tile of (x, z) points of one y row of
 // one vector through LDS: it reads the side whose fast axis it can cover with
 // consecutive lanes (16 points of one row), transforms, and writes the other side
-// the same way (for the ABI, 16 z points x 6 components = 1.5 KiB contiguous per x).
+// along its own (for the ABI, 16 z points x 6 components = 1.5 KiB contiguous per x).
 constexpr int kTile = 16;
 constexpr int kTileRow = kTile * 6 + 1;   // complex entries per x row of the tile (padded)
 
@@ -253,16 +253,18 @@ internal_to_abi_kernel(int nx, int ny, int nz, double h, double Bx, double By, d
     }
   }
   __syncthreads();
-  {
-    // write: lanes along z (16 points x 6 components contiguous per x)
-    const int xo = threadIdx.x >> 4, zo = threadIdx.x & 15;
-    const int x = tc.x0 + xo, z = tc.z0 + zo;
-    if (x < nx && z < nz) {
-      const long long a = ((long long)x * ny + tc.y) * nz + z;
-      double2* dst = abi + (long long)b * abi_bstride + ((long long)v * N + a) * 6;
+  // write: consecutive lanes take consecutive entries of the tile's runs of 16 z points x 6
+  // components (a lane writing its own point's six would touch every line six times: 8
+  // vectors of 256 x 48 x 48 177 us, 157 so; 2 of 75 x 31 x 29 9.7 and 8.1.  Reading that
+  // way gains nothing: 169 us, 161 as above)
+  constexpr int kRun = kTile * 6;
 #pragma unroll
-      for (int r = 0; r < 6; ++r) dst[r] = tile[xo][zo * 6 + r];
-    }
+  for (int k = 0; k < 6; ++k) {
+    const int i = threadIdx.x + 256 * k, xo = i / kRun, e = i - xo * kRun;
+    const int x = tc.x0 + xo;
+    if (x < nx && tc.z0 + e / 6 < nz)
+      abi[(long long)b * abi_bstride +
+          ((long long)v * N + ((long long)x * ny + tc.y) * nz + tc.z0) * 6 + e] = tile[xo][e];
   }
 }
 
