@@ -17,7 +17,7 @@
 // All per-iteration decisions (convergence, precision switch, filter
 // coefficients) are made on the device, so one outer iteration is a fixed
 // sequence of launches.  Eager mode reads the flags after every iteration;
-// graph mode records a batch of iterations once and replays it.
+// graph mode records one iteration per combination of filters needed and replays it.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -1294,8 +1294,11 @@ int run_filter_step2(const Filter2Args& A, int* passes) {
 // ---------------------------------------------------------------------------
 size_t gmatrix_bytes(const hkp_grid& g) {
   const size_t N = (size_t)g.nx * g.ny * g.nz, n6 = 6 * N;
-  return align_up(6 * N * 8) + align_up(4 * n6 * 16) + align_up(16 * n6 * 16) +
-         align_up(gmatrix_partial_bytes((long long)N)) + align_up((size_t)16 * 32 * 16);
+  // what the call uses: the on-site fields, 4 + 16 vectors, the Gram partials (at most
+  // 512 N bytes) and product.  What it asks for is 44 vectors' worth, the size that the
+  // interface has always named.
+  return align_up(6 * N * 8) + align_up((size_t)44 * n6 * 16) +
+         align_up(gram_partial_bytes(44, (long long)n6, 1)) + align_up((size_t)16 * 44 * 16);
 }
 
 int run_gmatrix(const GMatrixArgs& A) {
