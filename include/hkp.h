@@ -129,11 +129,13 @@ typedef struct {
                                           phase (t_rr), t_resid times the convergence control */
   double lambda_max_bound;  /* upper spectral bound used by the filter (eV) */
   /* stencil launches (filter steps and H X): algorithmic bytes moved -- the
-   * spinor blocks read and written plus the on-site fields once per launch --
-   * and, in eager mode with stats requested, their event-timed durations on
-   * the solver's stream, split by arithmetic precision */
+   * spinor blocks read and written plus the on-site fields once per step --
+   * and, in eager mode with stats requested, event-timed durations on the
+   * solver's stream, split by arithmetic precision.  A filter is timed as one run
+   * of steps (one pair of events) and counts a launch per step, also where its
+   * steps run over several groups of vectors */
   double hx_bytes;                       /* all stencil launches */
-  int64_t n_stencil32, n_stencil64;      /* timed launches */
+  int64_t n_stencil32, n_stencil64;      /* timed launches (steps) */
   double t_stencil32, t_stencil64;       /* summed durations (s) */
   double bytes_stencil32, bytes_stencil64; /* algorithmic bytes of the timed launches */
   /* FP32 passes that perform two recurrence steps each (timed as above; bytes:
@@ -147,9 +149,9 @@ typedef struct {
 
 /* Autotuner result for the stencil (filter step) kernel on one shape. */
 typedef struct {
-  int32_t tile_y;      /* rows of the x-y tile (the tile is 64 x tile_y) */
+  int32_t tile_y;      /* waves of a workgroup per spin: 64 x tile_y columns of the x-y plane */
   int32_t vgroup;      /* vectors of one tile run side by side (1: vector-major) */
-  int32_t dma;         /* 1: halo-tile rows copied global -> LDS directly */
+  int32_t dma;         /* 1: FP64 halo-tile rows may be copied global -> LDS directly */
   int32_t two_step_tx; /* FP32: tile of the two-step pass (two recurrence steps per */
   int32_t two_step_ty; /* pass) if it beats two one-step passes, else 0 x 0 */
   int32_t reserved;
@@ -270,16 +272,16 @@ int hkp_solve(const hkp_grid* grid, const hkp_material* mat, const hkp_opts* opt
  * [batch][nev][nx][ny][nz][6] ([batch][nb]... with HKP_FLAG_PSI_BLOCK),
  * resid_eV [batch][nev]; batch <= 65535.
  * Every kernel of an outer iteration covers the whole batch in one launch;
- * with HKP_FLAG_GRAPH the iterations are recorded once as a hipGraph and
- * replayed, converged members turning into no-ops on the device. */
+ * with HKP_FLAG_GRAPH an iteration is recorded once per combination of filters
+ * that its members need (FP32, FP64, both) as a hipGraph and replayed,
+ * converged members turning into no-ops on the device. */
 int hkp_solve_batch(const hkp_grid* grid, const hkp_material* mat, const hkp_opts* opts,
                     int32_t batch, const double* V_eV, const double* strain,
                     const double B_T[3], const void* X0, double* eig_eV, void* psi,
                     double* resid_eV, void* workspace, size_t ws_bytes, void* hip_stream,
                     hkp_stats* stats);
 
-/* Progress of an eigensolve after an outer iteration (after each replayed chunk
- * of iterations with HKP_FLAG_GRAPH).  Arrays are host memory owned by the
+/* Progress of an eigensolve after an outer iteration.  Arrays are host memory owned by the
  * library and valid during the call only; values are those of the last
  * Rayleigh-Ritz step (Sec. II.B), per batch member. */
 typedef struct {
