@@ -118,7 +118,7 @@ __global__ void phase_kernel(int nx, int nz, double h, double Bx, double By, dou
         s(ne, mul(wv, ep)), s(ne, mul(wv, em)), s(-ne, mul(wvc, em)), s(-ne, mul(wvc, ep)),
         s(n8, add(wm, w0)), s(-n8, add(wp, w0)), s(n8, add(vm, v0)), s(-n8, add(vp, v0))};
     for (int i = 0; i < kFoldRow; ++i) {
-      const size_t o = 2 * ((size_t)t * kFoldRow + i);
+      const size_t o = fold_offset(t) + 2 * i;
       p64[o] = row[i].x;
       p64[o + 1] = row[i].y;
       if (p32) {

@@ -20,6 +20,7 @@
 #include <string>
 
 #include "hkp.h"
+#include "launch_rules.h"
 
 namespace hkp {
 
@@ -170,8 +171,7 @@ hipError_t launch_onsite(const hkp_material& m, int nx, int ny, int nz, int batc
 // link phases folded with the stencil coefficients, kFoldRow complex entries per plane
 // (order of sten::Fold, without the y-links' phase along x), and that phase u [nx]
 // (1 where Bz = 0); p32 may be null
-constexpr int kFoldRow = 12;
-inline size_t phase_table_bytes(int nz, size_t real) { return (size_t)nz * kFoldRow * 2 * real; }
+inline size_t phase_table_bytes(int nz, size_t real) { return fold_offset(nz) * real; }
 hipError_t launch_phase_tables(int nx, int nz, double h, const double B[3],
                                const StencilConsts<double>& c, double* p64, double* u64,
                                float* p32, hipStream_t s);

@@ -226,7 +226,7 @@ stencil_pipe_kernel(KArgs<T> a) {
   const int nx = a.nx, ny = a.ny, nz = a.nz;
   const int tx0 = (pl.tile % a.tiles_x) * TX, ty0 = (pl.tile / a.tiles_x) * RH;
   // output planes [o0, o1) of this range; input planes p0..p1 feed them
-  const int o0 = (pl.zc * nz) / pl.zs, o1 = ((pl.zc + 1) * nz) / pl.zs;
+  const int o0 = range_begin(pl.zc, nz, pl.zs), o1 = range_begin(pl.zc + 1, nz, pl.zs);
   const int p0 = o0 > 0 ? o0 - 1 : 0, p1 = o1 < nz ? o1 : nz - 1;
   const unsigned nxy = (unsigned)nx * (unsigned)ny;
   const unsigned N = nxy * (unsigned)nz;   // 6 N < 2^31 (checked on the host)
@@ -462,7 +462,7 @@ stencil_kernel(KArgs<T> a) {
 
   const int nx = a.nx, ny = a.ny, nz = a.nz;
   // output planes [o0, o1) of this range; input planes p0..p1 feed them
-  const int o0 = (zc * nz) / zs, o1 = ((zc + 1) * nz) / zs;
+  const int o0 = range_begin(zc, nz, zs), o1 = range_begin(zc + 1, nz, zs);
   const int p0 = o0 > 0 ? o0 - 1 : 0, p1 = o1 < nz ? o1 : nz - 1;
   const unsigned nxy = (unsigned)nx * (unsigned)ny;
   const unsigned N = nxy * (unsigned)nz;   // 6 N < 2^31 (checked on the host)

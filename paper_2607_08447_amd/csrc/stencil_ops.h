@@ -155,7 +155,7 @@ __device__ __forceinline__ Fold<T> load_fold(const T* ptab, const double* ptab64
                                              cx<double> u) {
   Fold<T> f;
   if constexpr (PH != 0) {
-    Const<T>* t = (Const<T>*)ptab + 2 * kFoldRow * z;
+    Const<T>* t = (Const<T>*)ptab + fold_offset(z);
     auto at = [&](int i) { return mk<T>(t[2 * i], t[2 * i + 1]); };
     f.xo = at(0);
     f.xa = at(1);
@@ -170,7 +170,7 @@ __device__ __forceinline__ Fold<T> load_fold(const T* ptab, const double* ptab64
     f.du = at(10);
     f.dd = at(11);
     if constexpr (PH == 2) {
-      Const<double>* t64 = (Const<double>*)ptab64 + 2 * kFoldRow * z;
+      Const<double>* t64 = (Const<double>*)ptab64 + fold_offset(z);
       auto by = [&](cx<double> ph, int i) {
         const cx<double> r = mul(ph, mk<double>(t64[2 * i], t64[2 * i + 1]));
         return mk<T>((T)r.r, (T)r.i);
