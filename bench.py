@@ -55,12 +55,16 @@ def log(msg):
 
 
 TRAFFIC_JSON = os.path.join(ROOT, "profiles", "stencil_fp32_dqd_256x48x48_traffic.json")
-STENCIL_SRC = os.path.join(ROOT, "paper_2607_08447_amd", "csrc", "stencil.hip")
+STENCIL_SRC = [os.path.join(ROOT, "paper_2607_08447_amd", "csrc", f)
+               for f in ("stencil.hip", "stencil_ops.h", "launch_rules.h")]
 
 
 def _src_hash():
-    with open(STENCIL_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    h = hashlib.sha256()
+    for path in STENCIL_SRC:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def _shape_key(tune, nb):
@@ -68,7 +72,7 @@ def _shape_key(tune, nb):
 
 
 def _traffic_for(kernel_src_hash, shape, alg_bytes_per_launch):
-    """HBM bytes per launch of the dominant kernel from the committed rocprofv3
+    """HBM bytes per step of the dominant kernel from the committed rocprofv3
     counter summary, if it was taken on the current kernel source with the
     launch shape (tile height, vector group, row DMA) and block size this run
     uses, over launches of the same average size (algorithmic bytes per launch
@@ -89,26 +93,41 @@ def _traffic_for(kernel_src_hash, shape, alg_bytes_per_launch):
     return entry.get("hbm_bytes_per_launch")
 
 
-def _bench_alg_bytes(log):
-    """Algorithmic bytes per FP32 stencil launch printed by a benchmark run."""
+def _bench_steps(log):
+    """(algorithmic bytes per FP32 filter step, FP32 filter steps of the whole process) of
+    a benchmark run, from the line it printed: every solve, timed or not, takes the same
+    steps."""
     with open(log) as f:
         for line in f:
             if line.startswith("{") and '"roofline"' in line:
-                return json.loads(line)["roofline"]["algorithmic_bytes_per_launch"]
+                d = json.loads(line)
+                r = d["roofline"]
+                return (r["algorithmic_bytes_per_launch"],
+                        r["launches"] * (d["steps"] + d["warmup"]) // d["steps"])
     raise SystemExit(f"{log}: no benchmark line")
 
 
+# kernels of a filter step (a grid of whole 64-wide tiles may copy its rows in FP64)
+STEP_KERNELS = {"fp32": ("stencil_pipe_kernel<float",),
+                "fp64": ("stencil_pipe_kernel<double", "stencil_kernel<double")}
+
+
+def _recurrence_step(name, precision):
+    """Whether a kernel of this name is a step of the recurrence (the benchmark's headline
+    filter); launches without an old block (product-form steps, H X) are the `void`
+    variants."""
+    return any(k in name and (k + ", void") not in name for k in STEP_KERNELS[precision])
+
+
 def traffic_from(fetch_csv, write_csv, stencil, nb, precision="fp32", bench_log=None):
-    """HBM bytes per launch of the FP32 (or FP64) stencil from rocprofv3
+    """HBM bytes per filter step of the FP32 (or FP64) stencil from rocprofv3
     FETCH_SIZE and WRITE_SIZE (KiB per dispatch) collection files.  Each
     counter is scaled by what it reads for the 1 GiB device copy the profiled
-    run makes first (1 GiB read + 1 GiB written).  FP32 entries go to the JSON
-    the benchmark reads, with the algorithmic bytes per launch the profiled
-    benchmark run printed (bench_log, its stdout); FP64 ones are printed only."""
+    run makes first (1 GiB read + 1 GiB written).  A step is one dispatch per group of
+    vectors, so the FP32 sums are divided by the steps that the profiled benchmark run
+    (bench_log, its stdout) took; they go to the JSON the benchmark reads.  FP64 ones are
+    printed only, per dispatch."""
     import csv
-    # the recurrence's steps (the benchmark's headline filter); launches without
-    # an old block (product-form steps, H X) are the `void` variants
-    tag = "stencil_kernel<float" if precision == "fp32" else "stencil_kernel<double"
 
     def per_kernel(path, counter):
         copy, sten = [], []
@@ -120,7 +139,7 @@ def traffic_from(fetch_csv, write_csv, stencil, nb, precision="fp32", bench_log=
                 name = r["Kernel_Name"]
                 if "copyBuffer" in name and not copy:
                     copy.append(v)
-                elif tag in name and (tag + ", void") not in name:
+                elif _recurrence_step(name, precision):
                     sten.append(v)
         if not copy or not sten:
             raise SystemExit(f"{path}: no copy calibration or no {precision} stencil dispatches")
@@ -132,33 +151,37 @@ def traffic_from(fetch_csv, write_csv, stencil, nb, precision="fp32", bench_log=
         raise SystemExit("FETCH and WRITE runs saw different dispatch counts")
     gib = float(1 << 30)
     kf, kw = gib / cf, gib / cw
-    per_launch = [kf * a + kw * b for a, b in zip(sf, sw)]
+    fetched, written = kf * sum(sf), kw * sum(sw)
     if precision != "fp32":
-        print(json.dumps({"kernel": tag, "dispatches": len(per_launch),
-                          "hbm_bytes_per_launch": sum(per_launch) / len(per_launch),
-                          "fetch_bytes_per_launch": kf * sum(sf) / len(sf),
-                          "write_bytes_per_launch": kw * sum(sw) / len(sw),
+        n = len(sf)
+        print(json.dumps({"kernel": " and ".join(STEP_KERNELS[precision]), "dispatches": n,
+                          "hbm_bytes_per_dispatch": (fetched + written) / n,
+                          "fetch_bytes_per_dispatch": fetched / n,
+                          "write_bytes_per_dispatch": written / n,
                           "copy_calibration": {"fetch_factor": kf, "write_factor": kw}}, indent=1))
         return
+    if bench_log is None:
+        raise SystemExit("FP32 traffic needs --bench-log (the profiled run's stdout)")
+    alg, steps = _bench_steps(bench_log)
+    if not 0 < steps <= len(sf):
+        raise SystemExit(f"{len(sf)} stencil dispatches do not make the run's {steps} steps")
     d = {}
     if os.path.exists(TRAFFIC_JSON):
         with open(TRAFFIC_JSON) as f:
             d = json.load(f)
     if d.get("stencil_src_sha256") != _src_hash():
         d = {"by_launch": {}}   # counters of an older kernel source are dropped
-    d["kernel"] = ("stencil_kernel<float, ...> (FP32 Chebyshev filter step), dqd_256x48x48; "
-                   "entries keyed by tile height, vector group, row DMA / block size")
+    d["kernel"] = ("stencil_pipe_kernel<float, ...> (FP32 Chebyshev filter step), dqd_256x48x48; "
+                   "entries keyed by waves per spin, vector group, row DMA / block size")
     d["stencil_src_sha256"] = _src_hash()
-    if bench_log is None:
-        raise SystemExit("FP32 traffic needs --bench-log (the profiled run's stdout)")
-    alg = _bench_alg_bytes(bench_log)
     d["by_launch"][f"{stencil}/nb{nb}"] = {
-        "dispatches": len(per_launch),
+        "dispatches": len(sf),
+        "steps": steps,
         "algorithmic_bytes_per_launch": alg,
-        "ratio": sum(per_launch) / len(per_launch) / alg,
-        "hbm_bytes_per_launch": sum(per_launch) / len(per_launch),
-        "fetch_bytes_per_launch": kf * sum(sf) / len(sf),
-        "write_bytes_per_launch": kw * sum(sw) / len(sw),
+        "ratio": (fetched + written) / steps / alg,
+        "hbm_bytes_per_launch": (fetched + written) / steps,
+        "fetch_bytes_per_launch": fetched / steps,
+        "write_bytes_per_launch": written / steps,
         "copy_calibration": {"fetch_factor": kf, "write_factor": kw,
                              "note": "1 GiB device copy: counter bytes x factor = true bytes"},
         "made_by": [f"rocprofv3 --pmc FETCH_SIZE -- python3 bench.py --copy-calibration --no-cpu "
@@ -948,7 +971,7 @@ def main():
         "iters_mixed": stats[-1]["iters"],
         "iters_fp64": r64.stats["iters"],
         "roofline": {
-            "bound": "hbm", "kernel": "stencil_kernel<float> (FP32 Chebyshev filter step)",
+            "bound": "hbm", "kernel": "stencil_pipe_kernel<float> (FP32 Chebyshev filter step)",
             "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBPS, 4),
             "traffic": traffic,
