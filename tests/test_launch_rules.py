@@ -20,15 +20,9 @@ using namespace hkp;
 int main() {
   char what[32];
   long long a, b, c;
-  const float c0[3] = {2.0f, 2.2f, 2.6f};   // the kernels' kinds
   while (std::scanf("%31s %lld %lld %lld", what, &a, &b, &c) == 4) {
     if (!std::strcmp(what, "range")) std::printf("%d\n", range_begin((int)a, (int)b, (int)c));
     if (!std::strcmp(what, "fold")) std::printf("%zu\n", fold_offset((int)a));
-    if (!std::strcmp(what, "room")) std::printf("%d\n", z_split(a, (int)b, c != 0, c0[1]).room);
-    if (!std::strcmp(what, "fixed")) std::printf("%d\n", z_split(a, (int)b, c != 0, c0[1]).fixed);
-    for (int k = 0; k < 3; ++k)   // ranges of `c` live workgroups in a launch over `a`
-      if (!std::strcmp(what, "live"))
-        std::printf("%d\n", z_ranges((int)c, (int)b, z_split(a, (int)b, true, c0[k]).room, c0[k]));
   }
 }
 """
@@ -61,23 +55,3 @@ def test_z_ranges_tile_every_column(rules):
 def test_phase_rows_beyond_32_bits(rules):
     z = [0, 1, 47, (1 << 31) // 24 - 1, (1 << 31) // 24 + 1, 178956971, NZ_MAX - 1]
     assert rules([("fold", v, 0, 0) for v in z]) == [24 * v for v in z]
-
-
-def test_few_live_members_of_a_large_batch_are_split(rules):
-    """64 members of 16 vectors in 30 tiles each: with few vectors left the launch has to
-    spread over the CUs; with all of them alive it is not split."""
-    all_ = 64 * 16 * 30
-    for left in (1, 2, 4, 8):
-        assert all(z >= 2 for z in rules([("live", all_, 40, left * 30)])), left
-    assert rules([("live", all_, 40, all_)]) == [1, 1, 1]
-
-
-def test_room_for_z_ranges(rules):
-    """A split decided on the host is the one that the grid holds; one decided on the
-    device has room for two ranges wherever the grid's size allows them."""
-    sizes = [(n, nz) for n in (1, 30, 480, 4095, 4096, 30720, 1 << 30) for nz in (1, 5, 48)]
-    host = [("room", n, nz, 0) for n, nz in sizes], [("fixed", n, nz, 0) for n, nz in sizes]
-    assert rules(host[0]) == rules(host[1])
-    assert all(r >= 2 for (n, _), r in zip(sizes, rules([("room", n, nz, 1) for n, nz in sizes]))
-               if n * 2 < 1 << 31)
-    assert rules([("room", (1 << 31) - 1, 48, 1), ("fixed", (1 << 31) - 1, 48, 1)]) == [1, 1]
