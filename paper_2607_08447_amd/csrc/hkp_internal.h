@@ -45,8 +45,6 @@ __device__ __forceinline__ unsigned udiv(unsigned n, unsigned d, double inv) {
   return q;
 }
 
-constexpr int kCUs = 256;   // compute units of the GPU
-
 // unit constants from CODATA 2018 (h, e exact; m0 = 9.1093837015e-31 kg),
 // ten significant digits
 constexpr double kE0 = 0.03809982116;         // hbar^2/(2 m0), eV nm^2
@@ -103,6 +101,8 @@ struct StencilLaunch {
                          // (vector lock[b] + i of member b is virtual vector work[b] + i);
                          // the grid covers nvec * batch vectors and only the first
                          // work[batch] are live, spread evenly over the XCDs. Or null.
+  long long vlive = -1;  // with a work table: its total where the host knows it,
+  long long vmost = 0;   // else a bound of it (0: nvec * batch); the grid is made for that many
   int vfirst = 0;        // one Hamiltonian without a work table: only the vectors
   int vcount = 0;        // [vfirst, vfirst + vcount) (0: all)
   int tile_y;            // 1, 2, 4: waves of a workgroup per spin

@@ -20,4 +20,63 @@ constexpr int range_begin(int zc, int nz, int zs) {
   return zc * q + zc * r / zs;
 }
 
+constexpr int kCUs = 256;   // compute units of the GPU
+
+// z-ranges for nlw workgroups of nz planes, at most zmax: the fewest planes marched on
+// the CU that gets the most workgroups.  A workgroup marches nz / zs + 2 planes, a CU
+// gets ceil(nlw zs / 256) of them, and c0 workgroups together take no longer per
+// plane than one alone (a plane's latency against its share of the CU).  Measured for
+// 480 FP32 recurrence workgroups (12 vectors of 128 x 40 x 40): 63 us in one range, 68
+// in two; 384 (4 vectors of 256 x 48 x 48): 81 in one, 64 in four; 144 FP64 product
+// ones (6 vectors of 96 x 32 x 32): 53 in one, 35 in two, 28 in three, 30 in four.
+constexpr int kMaxSplit = 12;
+constexpr int z_ranges(int nlw, int nz, int zmax, float c0) {
+  constexpr float inv[kMaxSplit] = {1.0f,     1.0f / 2, 1.0f / 3, 1.0f / 4,  1.0f / 5,  1.0f / 6,
+                                    1.0f / 7, 1.0f / 8, 1.0f / 9, 1.0f / 10, 1.0f / 11, 1.0f / 12};
+  int best = 1;
+  float cost = 1e30f;
+#pragma unroll
+  for (int zs = 1; zs <= kMaxSplit; ++zs) {
+    const float per_cu = (float)(((unsigned)nlw * zs + kCUs - 1) / kCUs);
+    const float c = (per_cu > c0 ? per_cu : c0) * ((float)nz * inv[zs - 1] + 2.0f);
+    if (c < cost && zs <= zmax && zs <= nz) {
+      best = zs;
+      cost = c;
+    }
+  }
+  return best;
+}
+
+// Vectors that a launch with a work table is made for, of all members' `all`: the live
+// ones where the host knows them (live >= 0; it reads the flags after every iteration), in
+// a recorded launch at most those of the members still active when it was recorded
+// (most; 0: all).
+constexpr long long table_vectors(long long all, long long live, long long most) {
+  return live >= 0 ? live : (most > 0 && most < all ? most : all);
+}
+
+// Split of a launch of nwg workgroups: the ranges that its grid leaves room for, and the
+// ranges of every vector where the host decides them (0: the device does, from its live
+// vectors; then with room for twice the split that suits all).  16 workgroups per CU need
+// none; room for it in every launch would double the grid of large ones, half of it empty.
+// The end of a large batch is split because its launches are made for what is left: 64
+// members of 192 x 40 x 40 of which four are slow, mixed 0.690 -> 0.665 s launch by
+// launch and 0.676 -> 0.664 s recorded.
+struct ZSplit {
+  int room, fixed;
+};
+constexpr ZSplit z_split(long long nwg, int nz, bool on_device, float c0) {
+  const int zs = nwg < 16 * kCUs ? z_ranges((int)nwg, nz, 8, c0) : 1;
+  if (!on_device || nwg >= 16 * kCUs) return ZSplit{zs, zs};
+  return ZSplit{2 * zs < kMaxSplit ? 2 * zs : kMaxSplit, 0};
+}
+
+// Whether an iteration recorded for `recorded` active members is recorded anew for the
+// `active` that are left: its launches were too large to be split (member_wgs: workgroups
+// of one member's vectors), and a quarter of them would fill the chip less well.  (A
+// recording takes a millisecond or two, such an iteration a hundred.)
+constexpr bool record_anew(int recorded, int active, long long member_wgs) {
+  return active > 0 && 4LL * active <= recorded && recorded * member_wgs >= 16 * kCUs;
+}
+
 }  // namespace hkp

@@ -216,9 +216,10 @@ double step_bytes(const StencilLaunch& a, long long N, int active_members, doubl
 struct Ctx {
   StencilStats* ss = nullptr;
   int active_members = 1;   // host view of unconverged Hamiltonians (byte accounting)
-  // host view of the vectors that the FP32 and the FP64 filter process (-1: unknown, at
-  // most all)
+  // host view of the vectors that the FP32 and the FP64 filter process (-1: unknown, a
+  // recorded iteration, for at most most_members members)
   int live32 = -1, live64 = -1;
+  int most_members = 0;
   // One Hamiltonian, launched as it goes: the host knows which vectors are live, [locked,
   // nb), so launches need no work table (a workgroup's walk through it is 2-3 us of
   // dependent loads before its first plane) and a filter can go through them in groups.
@@ -289,6 +290,8 @@ void apply_block(const Ctx& c, size_t x_off, size_t w_off, const int* active) {
   if (!c.direct) {
     a.active = active;
     a.work = c.work(2);
+    a.vmost = (long long)c.most_members * c.p.nb;
+    if (c.most_members == 0) a.vlive = (long long)c.active_members * c.p.nb;
   }
   c.ss->begin(c.s);
   HKP_CHECK(launch_stencil(a, c.consts, c.s));
@@ -319,6 +322,8 @@ void cover(const Ctx& c, StencilLaunch& a, const int* active, const int* work, i
     a.active = active;
     a.lock = c.at<int>(c.L.lock);
     a.work = work;
+    a.vmost = (long long)c.most_members * c.p.nb;
+    a.vlive = a.fp64 ? c.live64 : c.live32;
   }
 }
 // vectors counted in the byte accounting of a filter
@@ -992,16 +997,24 @@ int run_solve(const SolveArgs& A, hkp_stats* stats) {
       hipGraph_t graph = nullptr;
       hipGraphExec_t exec = nullptr;
       double bytes = 0;
-      ~Recorded() {
+      int members = 0;   // active when it was recorded
+      void reset() {
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
+        exec = nullptr;
+        graph = nullptr;
       }
+      ~Recorded() { reset(); }
     } rec[4];
+    const long long member_wgs =
+        (long long)p.nb * (((long long)p.nx * p.ny + 64 * p.st.tile_y - 1) / (64 * p.st.tile_y));
     auto record = [&](int need, Recorded& r) {
       // byte accounting of a replay: every member active and no vector locked (an upper
       // estimate; the kernels skip on the device)
       const double bytes_before = sst.hx_bytes;
       const int members = c.active_members;
+      r.reset();
+      r.members = c.most_members = members;
       c.active_members = p.batch;
       c.live32 = c.live64 = -1;
       c.direct = false;
@@ -1023,7 +1036,8 @@ int run_solve(const SolveArgs& A, hkp_stats* stats) {
     while (iters < A.max_iter && !all_done() && !user_stop) {
       count_work();
       const int need = (c.live32 > 0 ? 1 : 0) | (c.live64 > 0 ? 2 : 0);
-      if (!rec[need].exec) record(need, rec[need]);
+      if (!rec[need].exec || record_anew(rec[need].members, c.active_members, member_wgs))
+        record(need, rec[need]);
       sst.hx_bytes += rec[need].bytes;
       HKP_CHECK(hipGraphLaunch(rec[need].exec, c.s));
       ++n_graph;

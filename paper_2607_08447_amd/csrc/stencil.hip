@@ -79,35 +79,10 @@ struct KArgs {
 // and groups) split every (vector, tile) into zs z-ranges so that more workgroups
 // share the chip evenly; a range recomputes one plane on each side.  The grid holds
 // zsplit x the unsplit count; the split is decided from the live count, uniformly
-// for the whole launch (z_ranges below).
+// for the whole launch (z_ranges).
 struct Place {
   int b, vec, tile, zs, zc;
 };
-
-// z-ranges for nlw workgroups of nz planes, at most zmax: the fewest planes marched on
-// the CU that gets the most workgroups.  A workgroup marches nz / zs + 2 planes, a CU
-// gets ceil(nlw zs / 256) of them, and c0 workgroups together take no longer per
-// plane than one alone (a plane's latency against its share of the CU).  Measured for
-// 480 FP32 recurrence workgroups (12 vectors of 128 x 40 x 40): 63 us in one range, 68
-// in two; 384 (4 vectors of 256 x 48 x 48): 81 in one, 64 in four; 144 FP64 product
-// ones (6 vectors of 96 x 32 x 32): 53 in one, 35 in two, 28 in three, 30 in four.
-constexpr int kMaxSplit = 12;
-__host__ __device__ inline int z_ranges(int nlw, int nz, int zmax, float c0) {
-  constexpr float inv[kMaxSplit] = {1.0f,     1.0f / 2, 1.0f / 3, 1.0f / 4,  1.0f / 5,  1.0f / 6,
-                                    1.0f / 7, 1.0f / 8, 1.0f / 9, 1.0f / 10, 1.0f / 11, 1.0f / 12};
-  int best = 1;
-  float cost = 1e30f;
-#pragma unroll
-  for (int zs = 1; zs <= kMaxSplit; ++zs) {
-    const float per_cu = (float)((nlw * zs + kCUs - 1) / kCUs);
-    const float c = (per_cu > c0 ? per_cu : c0) * ((float)nz * inv[zs - 1] + 2.0f);
-    if (c < cost && zs <= zmax && zs <= nz) {
-      best = zs;
-      cost = c;
-    }
-  }
-  return best;
-}
 
 template <typename T>
 __device__ __forceinline__ bool find_place(const KArgs<T>& a, Place* p) {
@@ -669,7 +644,8 @@ hipError_t launch_t(const StencilLaunch& L, const StencilConsts<double>& c, hipS
   a.nvec = part ? L.vcount : L.nvec;
   a.vgroup = L.vgroup < 1 ? 1 : (L.vgroup > a.nvec ? a.nvec : L.vgroup);
   a.vfirst = part ? L.vfirst : 0;
-  const long long vectors = (long long)a.nvec * L.batch;
+  long long vectors = (long long)a.nvec * L.batch;
+  if (L.work) vectors = table_vectors(vectors, L.vlive, L.vmost);
   // The old block (read for the last time) and the output pass the caches by where the
   // launch's blocks exceed the memory-side cache: they would only push out what is
   // read again (on-site fields, halo rows; a 40-vector FP32 step of 256 x 48 x 48: 711
@@ -687,20 +663,16 @@ hipError_t launch_t(const StencilLaunch& L, const StencilConsts<double>& c, hipS
     a.tiles_y = (L.ny + rows - 1) / rows;
     const long long nwg = (long long)a.tiles_x * a.tiles_y * vectors;
     if (nwg <= 0) return hipSuccess;
-    // z split: 0 never, 1 as balances the launch, 2 always in two (tests).  Where the
-    // live count is only known on the device the grid leaves room for twice the split
-    // that suits all vectors.
+    // z split: 0 never, 1 as balances the launch (z_split), 2 always in two (tests)
     a.c0 = sizeof(T) == 8 ? 2.2f : (std::is_same<TO, void>::value ? 2.6f : 2.0f);
     a.zsplit = a.zfixed = 1;
     if (L.zsplit >= 2) {
       a.zsplit = 2;
       a.zfixed = L.nz >= 8 ? 2 : 1;
-    } else if (L.zsplit == 1 && nwg < 16 * kCUs) {
-      a.zfixed = a.zsplit = z_ranges((int)nwg, L.nz, 8, a.c0);
-      if (L.work) {
-        a.zsplit = std::min(kMaxSplit, 2 * a.zsplit);
-        a.zfixed = 0;
-      }
+    } else if (L.zsplit == 1) {
+      const ZSplit z = z_split(nwg, L.nz, L.work && L.vlive < 0, a.c0);
+      a.zsplit = z.room;
+      a.zfixed = z.fixed;
     }
     if (nwg * a.zsplit > 0x7fffffffLL) return hipErrorInvalidValue;
     kernel<<<dim3((unsigned)(nwg * a.zsplit)), dim3(64, waves, NSP), 0, s>>>(a);

@@ -20,9 +20,17 @@ using namespace hkp;
 int main() {
   char what[32];
   long long a, b, c;
+  const float c0[3] = {2.0f, 2.2f, 2.6f};   // the kernels' kinds
   while (std::scanf("%31s %lld %lld %lld", what, &a, &b, &c) == 4) {
     if (!std::strcmp(what, "range")) std::printf("%d\n", range_begin((int)a, (int)b, (int)c));
     if (!std::strcmp(what, "fold")) std::printf("%zu\n", fold_offset((int)a));
+    if (!std::strcmp(what, "room")) std::printf("%d\n", z_split(a, (int)b, c != 0, c0[1]).room);
+    if (!std::strcmp(what, "fixed")) std::printf("%d\n", z_split(a, (int)b, c != 0, c0[1]).fixed);
+    if (!std::strcmp(what, "vectors")) std::printf("%lld\n", table_vectors(a, b, c));
+    if (!std::strcmp(what, "anew")) std::printf("%d\n", record_anew((int)a, (int)b, c) ? 1 : 0);
+    for (int k = 0; k < 3; ++k)   // ranges of `c` live workgroups in a launch over `a`
+      if (!std::strcmp(what, "live"))
+        std::printf("%d\n", z_ranges((int)c, (int)b, z_split(a, (int)b, true, c0[k]).room, c0[k]));
   }
 }
 """
@@ -55,3 +63,40 @@ def test_z_ranges_tile_every_column(rules):
 def test_phase_rows_beyond_32_bits(rules):
     z = [0, 1, 47, (1 << 31) // 24 - 1, (1 << 31) // 24 + 1, 178956971, NZ_MAX - 1]
     assert rules([("fold", v, 0, 0) for v in z]) == [24 * v for v in z]
+
+
+def test_few_live_members_of_a_large_batch_are_split(rules):
+    """64 members of 16 vectors in 30 tiles each: with few vectors left the launch has to
+    spread over the CUs, whether the host counts them or a recorded launch is made for the
+    members left; with all of them alive it is not split."""
+    tiles, nb, batch = 30, 16, 64
+    all_ = batch * nb
+    for left in (1, 2, 4, 8):
+        n = rules([("vectors", all_, left, 0)])[0]
+        assert n == left
+        assert rules([("fixed", n * tiles, 40, 0)])[0] >= 2, left
+    for members in (1, 3):
+        n = rules([("vectors", all_, -1, members * nb)])[0]
+        assert n == members * nb
+        assert all(z >= 2 for z in rules([("live", n * tiles, 40, 4 * tiles)]))
+    assert rules([("vectors", all_, -1, 0), ("fixed", all_ * tiles, 40, 0)]) == [all_, 1]
+
+
+def test_recorded_iterations_follow_the_members_left(rules):
+    """64 -> 16 -> 4 -> 1 where the launches are large; never for small ones, whose
+    recording costs more than it gives."""
+    wgs = 16 * 30
+    at = [a for a in range(64, 0, -1) if rules([("anew", 64, a, wgs)])[0]]
+    assert at == list(range(16, 0, -1))
+    assert rules([("anew", 8, 2, 4096 // 8 - 1), ("anew", 8, 2, 4096 // 8), ("anew", 8, 0, 1 << 20)]) == [0, 1, 0]
+
+
+def test_room_for_z_ranges(rules):
+    """A split decided on the host is the one that the grid holds; one decided on the
+    device has room for two ranges, unless the launch is too large to be split."""
+    sizes = [(n, nz) for n in (1, 30, 480, 4095, 4096, 30720, (1 << 31) - 1) for nz in (1, 5, 48)]
+    host = [("room", n, nz, 0) for n, nz in sizes], [("fixed", n, nz, 0) for n, nz in sizes]
+    assert rules(host[0]) == rules(host[1])
+    room = rules([("room", n, nz, 1) for n, nz in sizes])
+    assert all((r >= 2) == (n < 4096) for (n, _), r in zip(sizes, room))
+    assert all(n * r < 1 << 31 for (n, _), r in zip(sizes, room))
