@@ -336,19 +336,26 @@ int run_autotune(const hkp_grid& g, int nb, bool mixed, bool strain, int field, 
   double best_us = 1e300;
   const char* dbg = std::getenv("HKP_TUNE_TRACE");
   const int group = filter_group(nb, (size_t)n6 * esz);
-  std::vector<int> groups;   // 1 (vector-major), 2, 4, nb (tile-major)
-  for (int vg : {1, 2, 4, nb})
-    if (vg <= nb && std::find(groups.begin(), groups.end(), vg) == groups.end()) groups.push_back(vg);
-  for (int dma = 0; dma < 2; ++dma)
-  for (int vg : groups)
-  for (int ty : {1, 2, 4}) {
-    if (ty > 1 && ty > 2 * g.ny) continue;
-    if (dma && g.nx % 64 != 0) continue;
+  const int ngroups = (nb + group - 1) / group;
+  // steps timed per group: enough that its first, from HBM, and the two events count little
+  const int reps = std::max(12, 48 / ngroups);
+  auto elapsed = [&](auto run) {   // us; < 0: a launch failed
+    if (hipEventRecord(e0, s) != hipSuccess) return -1.0;
+    const bool ok = run();
+    float ms = 0;
+    if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess || !ok ||
+        hipEventElapsedTime(&ms, e0, e1) != hipSuccess)
+      return -1.0;
+    return 1e3 * ms;
+  };
+  TuneShape shapes[kMaxTuneShapes];
+  const int nshapes = tune_shapes(g.nx, g.ny, nb, !mixed, shapes);
+  for (int i = 0; i < nshapes; ++i) {
+    const TuneShape& t = shapes[i];
     StencilLaunch a{};
     a.nx = g.nx;
     a.ny = g.ny;
     a.nz = g.nz;
-    a.nvec = nb;
     a.batch = 1;
     a.old_fp64 = !mixed;
     a.out_fp64 = !mixed;
@@ -361,42 +368,41 @@ int run_autotune(const hkp_grid& g, int nb, bool mixed, bool strain, int field, 
     a.coef.alpha = 1.0;
     a.coef.shift = 0.5;
     a.coef.beta = -1.0;
-    a.tile_y = ty;
-    a.vgroup = vg;
-    a.dma = dma;
+    a.tile_y = t.tile_y;
+    a.vgroup = t.vgroup;
+    a.dma = t.dma;
+    a.zsplit = t.zsplit;
     a.fp64 = !mixed;
-    // as a filter runs: all steps on one group of vectors, its two blocks taking turns
-    const int reps = 5;
-    double us = 0;
-    bool ok = true;
-    for (int v0 = 0; v0 < nb && ok; v0 += group) {
-      const size_t off_v = (size_t)v0 * n6 * esz;
-      char *in = (char*)X + off_v, *out = (char*)O + off_v;
-      a.nvec = std::min(group, nb - v0);
-      auto step = [&]() {
-        a.in = in;
-        a.old = a.out = out;
-        std::swap(in, out);
-        return launch_stencil(a, c, s) == hipSuccess;
-      };
-      ok = step() && step();   // warm-up
-      if (!ok) break;
-      (void)hipEventRecord(e0, s);
-      for (int r = 0; r < reps; ++r) (void)step();
-      (void)hipEventRecord(e1, s);
-      (void)hipEventSynchronize(e1);
-      float ms = 0;
-      (void)hipEventElapsedTime(&ms, e0, e1);
-      us += 1e3 * ms / reps;
-    }
-    if (!ok) continue;
+    // as a filter runs: all steps on one group of vectors, its two blocks taking turns,
+    // then the next group, without a wait between (40 FP64 vectors of 256 x 48 x 48: 1239
+    // us a step; timed group by group without z ranges 1730, which made staged rows win
+    // over copied ones, 752 against 720 ms a solve)
+    auto filter = [&](int steps) {
+      for (int v0 = 0; v0 < nb; v0 += group) {
+        const size_t off_v = (size_t)v0 * n6 * esz;
+        char *in = (char*)X + off_v, *out = (char*)O + off_v;
+        a.nvec = std::min(group, nb - v0);
+        for (int k = 0; k < steps; ++k) {
+          a.in = in;
+          a.old = a.out = out;
+          if (launch_stencil(a, c, s) != hipSuccess) return false;
+          std::swap(in, out);
+        }
+      }
+      return true;
+    };
+    if (!filter(1)) continue;   // warm-up
+    const double us = elapsed([&]() { return filter(reps); }) / reps;
+    if (us < 0) continue;
     if (dbg && dbg[0] == '1')
-      std::fprintf(stderr, "[hkp tune] ty %d vgroup %d dma %d: %.1f us\n", ty, vg, dma, us);
+      std::fprintf(stderr, "[hkp tune] ty %d vgroup %d dma %d: %.1f us\n", t.tile_y, t.vgroup,
+                   t.dma, us);
     if (us < best_us) {
       best_us = us;
-      best.tile_y = ty;
-      best.vgroup = vg;
-      best.dma = dma;
+      best.tile_y = t.tile_y;
+      best.vgroup = t.vgroup;
+      best.dma = t.dma;
+      best.zsplit = t.zsplit;
     }
   }
   // two-step passes (FP32 filter): faster than two one-step passes of the best shape?
@@ -431,14 +437,12 @@ int run_autotune(const hkp_grid& g, int nb, bool mixed, bool strain, int field, 
         a.vgroup = best.vgroup;
         if (!stencil2_supported(a)) continue;
         if (launch_stencil2(a, c, s) != hipSuccess) continue;   // warm-up
-        const int reps = 5;
-        (void)hipEventRecord(e0, s);
-        for (int r = 0; r < reps; ++r) (void)launch_stencil2(a, c, s);
-        (void)hipEventRecord(e1, s);
-        (void)hipEventSynchronize(e1);
-        float ms = 0;
-        (void)hipEventElapsedTime(&ms, e0, e1);
-        const double us = 1e3 * ms / reps;
+        const double us = elapsed([&]() {
+          bool ok = true;
+          for (int r = 0; r < 12; ++r) ok = ok && launch_stencil2(a, c, s) == hipSuccess;
+          return ok;
+        }) / 12;
+        if (us < 0) continue;
         if (dbg && dbg[0] == '1')
           std::fprintf(stderr, "[hkp tune] two-step %d x %d: %.1f us (one-step pair %.1f us)\n",
                        tx, ty, us, 2.0 * best_us);

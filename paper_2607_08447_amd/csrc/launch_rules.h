@@ -79,4 +79,26 @@ constexpr bool record_anew(int recorded, int active, long long member_wgs) {
   return active > 0 && 4LL * active <= recorded && recorded * member_wgs >= 16 * kCUs;
 }
 
+// Launch shapes that the tuner times for a filter step: waves per spin, vectors side by
+// side, whether rows may be copied, and the z split that the solver's launches use.  Row
+// copies are timed where they exist, in FP64 on whole 64-wide tiles; in FP32 there is
+// nothing to time, and the FP64 launches of a mixed solve take them wherever they can (58
+// us a step against 61 staged, 2 vectors of 256 x 48 x 48).
+struct TuneShape {
+  int tile_y, vgroup, dma, zsplit;
+};
+constexpr int kMaxTuneShapes = 24;
+constexpr int tune_shapes(int nx, int ny, int nb, bool fp64, TuneShape (&out)[kMaxTuneShapes]) {
+  const int whole = nx % 64 == 0 ? 1 : 0;
+  int n = 0;
+  for (int dma = fp64 ? 0 : whole; dma <= whole; ++dma)
+    for (int g = 0; g < 4; ++g) {
+      const int vg = g == 3 ? nb : 1 << g;   // 1 (vector-major), 2, 4, nb (tile-major)
+      if (vg > nb || (g == 3 && nb <= 4 && nb != 3)) continue;   // (once each)
+      for (int ty = 1; ty <= 4; ty *= 2)
+        if (ty <= 2 || ty <= 2 * ny) out[n++] = TuneShape{ty, vg, dma, 1};
+    }
+  return n;
+}
+
 }  // namespace hkp

@@ -19,9 +19,15 @@ PROGRAM = r"""
 using namespace hkp;
 int main() {
   char what[32];
-  long long a, b, c;
+  long long a, b, c, d;
   const float c0[3] = {2.0f, 2.2f, 2.6f};   // the kernels' kinds
-  while (std::scanf("%31s %lld %lld %lld", what, &a, &b, &c) == 4) {
+  while (std::scanf("%31s %lld %lld %lld %lld", what, &a, &b, &c, &d) == 5) {
+    if (!std::strcmp(what, "tune")) {
+      TuneShape t[kMaxTuneShapes];
+      const int n = tune_shapes((int)a, (int)b, (int)c, d != 0, t);
+      for (int i = 0; i < n; ++i)
+        std::printf("%d %d %d %d\n", t[i].tile_y, t[i].vgroup, t[i].dma, t[i].zsplit);
+    }
     if (!std::strcmp(what, "range")) std::printf("%d\n", range_begin((int)a, (int)b, (int)c));
     if (!std::strcmp(what, "fold")) std::printf("%zu\n", fold_offset((int)a));
     if (!std::strcmp(what, "room")) std::printf("%d\n", z_split(a, (int)b, c != 0, c0[1]).room);
@@ -46,7 +52,7 @@ def rules(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(src), "-o", str(exe)], check=True)
 
     def ask(lines):
-        r = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, q)) for q in lines),
+        r = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, (q + (0, 0, 0))[:5])) for q in lines),
                            capture_output=True, text=True, check=True)
         return [int(v) for v in r.stdout.split()]
 
@@ -100,3 +106,18 @@ def test_room_for_z_ranges(rules):
     room = rules([("room", n, nz, 1) for n, nz in sizes])
     assert all((r >= 2) == (n < 4096) for (n, _), r in zip(sizes, room))
     assert all(n * r < 1 << 31 for (n, _), r in zip(sizes, room))
+
+
+@pytest.mark.parametrize("nb", [1, 2, 3, 4, 5, 24])
+@pytest.mark.parametrize("ny", [1, 2, 40])
+@pytest.mark.parametrize("nx", [64, 75, 192])
+@pytest.mark.parametrize("fp64", [0, 1])
+def test_tuner_times_the_launches_that_a_filter_makes(rules, nx, ny, nb, fp64):
+    """Every shape once, with the z split of the solver's launches; row copies (dma) are a
+    choice only where both forms exist, and otherwise the form that the launch takes."""
+    v = rules([("tune", nx, ny, nb, fp64)])
+    shapes = [tuple(v[i:i + 4]) for i in range(0, len(v), 4)]
+    dmas = [0] if nx % 64 else ([0, 1] if fp64 else [1])
+    want = [(ty, vg, dma, 1) for dma in dmas for vg in sorted({1, 2, 4, nb}) if vg <= nb
+            for ty in (1, 2, 4) if ty <= 2 or ty <= 2 * ny]
+    assert sorted(shapes) == sorted(want)
