@@ -76,11 +76,11 @@ __device__ __forceinline__ void block_sums(double (&v)[NV], double* out) {
 
 // block sums of NV values for each of a group's NR systems (v[s * NV + k]), the rows
 // of the running ones written to partial[(system gridDim.x + blockIdx.x) NV + k]
-template <int NR, int NV>
+template <int NR, int NT, int NV>
 __device__ __forceinline__ void group_sums(double (&v)[NR * NV], const bool (&on)[NR],
                                            double* partial) {
   __shared__ double out[NR * NV];
-  block_sums<NR * NV>(v, out);
+  block_sums<NR * NV, NT>(v, out);
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int s = 0; s < NR; ++s)
@@ -393,8 +393,8 @@ cg_start_kernel(const double* partial, int nblk, double tol, CGState* st) {
 
 // p_new = z + beta p_old (at the node and its neighbours: the old direction is
 // not overwritten, p_new goes to the other buffer); q = L p_new; partial p.q
-template <int NR>
-__global__ void __launch_bounds__(kThreads)
+template <int NR, int NT>
+__global__ void __launch_bounds__(NT)
 cg_matvec_kernel(long long NP, PairGeo g, const double* __restrict__ cx,
                  const double* __restrict__ cy, const double* __restrict__ cz,
                   const uint8_t* __restrict__ dir, const double* __restrict__ zv,
@@ -405,8 +405,8 @@ cg_matvec_kernel(long long NP, PairGeo g, const double* __restrict__ cx,
   double acc[NR];
 #pragma unroll
   for (int s = 0; s < NR; ++s) acc[s] = 0.0;
-  for (unsigned t = xcd_remap(blockIdx.x, gridDim.x) * kThreads + threadIdx.x; t < g.pairs;
-       t += gridDim.x * kThreads) {
+  for (unsigned t = xcd_remap(blockIdx.x, gridDim.x) * NT + threadIdx.x; t < g.pairs;
+       t += gridDim.x * NT) {
     int x, y, z;
     const unsigned i = pair_at(t, g, x, y, z);
     const PairHood h = pair_hood<64>(i, x, y, z, g.nx, g.ny, g.nz);
@@ -438,7 +438,7 @@ cg_matvec_kernel(long long NP, PairGeo g, const double* __restrict__ cx,
       acc[s] += pi.x * qi.x + pi.y * qi.y;
     }
   }
-  group_sums<NR, 1>(acc, G.on, partial);
+  group_sums<NR, NT, 1>(acc, G.on, partial);
 }
 
 __global__ void __launch_bounds__(kRedThreads)
@@ -638,8 +638,8 @@ struct MGLevelArgs {
 // formed wherever it is needed (at the node, and at its neighbours from their old b
 // and q) and stored to r_new, another buffer, with partial sums (0, r_new.r_new) per
 // workgroup -- and the restriction takes the new residual as its right-hand side.
-template <bool UPD, int NR>
-__global__ void __launch_bounds__(kThreads)
+template <bool UPD, int NR, int NT>
+__global__ void __launch_bounds__(NT)
 mg_restrict_kernel(MGLevelArgs L, MGGeo c, double w, const double* __restrict__ b,
                     long long b_stride, double* bc, long long bc_stride, const CGState* st,
                     int nrhs, const double* __restrict__ p, const double* __restrict__ q,
@@ -654,9 +654,9 @@ mg_restrict_kernel(MGLevelArgs L, MGGeo c, double w, const double* __restrict__ 
   const unsigned lane = threadIdx.x & 63;
   const unsigned cx = lane >> 5, cy = (lane >> 4) & 1;
   // the four lanes of a coarse node run or leave together
-  for (unsigned t = xcd_remap(blockIdx.x, gridDim.x) * (kThreads / 4) + (threadIdx.x >> 6) * 16 +
+  for (unsigned t = xcd_remap(blockIdx.x, gridDim.x) * (NT / 4) + (threadIdx.x >> 6) * 16 +
                     (lane & 15);
-       t < NC; t += gridDim.x * (kThreads / 4)) {
+       t < NC; t += gridDim.x * (NT / 4)) {
     int X, Y, Z;
     mg_coords(t, c, X, Y, Z);
     const int x = 2 * X + (int)cx, y = 2 * Y + (int)cy, z = 2 * Z;
@@ -706,7 +706,7 @@ mg_restrict_kernel(MGLevelArgs L, MGGeo c, double w, const double* __restrict__ 
       if (lane < 16 && G.on[s]) bc[G.sys[s] * bc_stride + t] = sum;
     }
   }
-  if (UPD) group_sums<NR, 2>(acc, G.on, partial);
+  if (UPD) group_sums<NR, NT, 2>(acc, G.on, partial);
 }
 
 // The coarse tail of the V-cycle: levels t .. t + nt - 1 (the last one the
@@ -859,8 +859,8 @@ mg_tail_kernel(MGTailArgs T, double w, int sweeps, const double* __restrict__ bt
 // then one damped-Jacobi sweep: out = u' + w D^-1 (b - A u').  On level 0, out is
 // the CG's z and the partial sums of r.z go to partial_rz.  A pair's two nodes lie in one
 // aggregate, as do those of each neighbour pair.
-template <bool FINEST, int NR>
-__global__ void __launch_bounds__(kThreads)
+template <bool FINEST, int NR, int NT>
+__global__ void __launch_bounds__(NT)
 mg_correct_kernel(MGLevelArgs L, PairGeo g, MGGeo c, double w, double alpha,
                   const double* __restrict__ b,
                    long long b_stride, const double* __restrict__ e, long long e_stride,
@@ -872,8 +872,8 @@ mg_correct_kernel(MGLevelArgs L, PairGeo g, MGGeo c, double w, double alpha,
 #pragma unroll
   for (int s = 0; s < NR; ++s) acc[s] = 0.0;
   const unsigned sxc = (unsigned)c.ny * c.nz, syc = (unsigned)c.nz;
-  for (unsigned t = xcd_remap(blockIdx.x, gridDim.x) * kThreads + threadIdx.x; t < g.pairs;
-       t += gridDim.x * kThreads) {
+  for (unsigned t = xcd_remap(blockIdx.x, gridDim.x) * NT + threadIdx.x; t < g.pairs;
+       t += gridDim.x * NT) {
     int x, y, z;
     const unsigned j = pair_at(t, g, x, y, z);
     const PairHood h = pair_hood<64>(j, x, y, z, g.nx, g.ny, g.nz);
@@ -918,7 +918,7 @@ mg_correct_kernel(MGLevelArgs L, PairGeo g, MGGeo c, double w, double alpha,
       if (FINEST) acc[s] += r.o.x * o.x + (h.two ? r.o.y * o.y : 0.0);
     }
   }
-  if (FINEST) group_sums<NR, 1>(acc, G.on, partial_rz);
+  if (FINEST) group_sums<NR, NT, 1>(acc, G.on, partial_rz);
 }
 
 // ---------------------------------------------------------------------------
@@ -1353,17 +1353,34 @@ template <int NR>
 unsigned groups(int nrhs) {
   return (unsigned)((nrhs + NR - 1) / NR);
 }
-// f(integral_constant NR) for a kernel of `threads` threads per system: NR systems per
-// workgroup.  Four share each load of the coefficients (20 systems of 272 x 64 x 88: 61.0
-// ms; 63.7 in twos), where that still leaves four workgroups for every CU; else one each,
-// so that small boxes keep their parallelism and two systems are not read as four (2 of
-// 114 x 26 x 69: 3.4 ms, in fours 4.5).
-template <typename F>
-void for_group(long long threads, int nrhs, F f) {
+// How a node-streaming kernel of `threads` threads per system is launched.
+// nr: systems per workgroup.  Four share each load of the coefficients (20 systems of 272
+// x 64 x 88: 61.0 ms; 63.7 in twos), where that still leaves four workgroups for every CU;
+// else one each, so that small boxes keep their parallelism and two systems are not read
+// as four (2 of 114 x 26 x 69: 3.4 ms, in fours 4.5).
+// nt: threads per workgroup, one wave where 256 would leave CUs without a workgroup (a
+// solve on 30 x 22 x 20 nodes 1.16 -> 1.10 ms, on 38 x 22 x 36 1.34 -> 1.28, on 96 x 48 x 56,
+// whose coarse levels it concerns, 2.46 -> 2.35; at most 0.7 % from one node per thread
+// on the smallest boxes, where pairs in workgroups of 256 were 3-4 % slower).
+struct Share {
+  int nr, nt, blocks;   // blocks: workgroups per system (or group of systems)
+};
+Share share(long long threads, int nrhs) {
   if (nrhs > 2 && threads * groups<4>(nrhs) >= 4LL * kCUs * kThreads)
-    f(std::integral_constant<int, 4>{});
-  else
-    f(std::integral_constant<int, 1>{});
+    return Share{4, kThreads, sp_blocks(threads)};
+  if (threads * nrhs < (long long)kCUs * kThreads)
+    return Share{1, 64, (int)((threads + 63) / 64)};
+  return Share{1, kThreads, sp_blocks(threads)};
+}
+// f(grid, NR, NT) with that share as integral constants
+template <typename F>
+void shared_launch(long long threads, int nrhs, F f) {
+  using std::integral_constant;
+  const Share h = share(threads, nrhs);
+  const dim3 grid((unsigned)h.blocks, h.nr == 4 ? groups<4>(nrhs) : (unsigned)nrhs);
+  if (h.nr == 4) f(grid, integral_constant<int, 4>{}, integral_constant<int, kThreads>{});
+  else if (h.nt == 64) f(grid, integral_constant<int, 1>{}, integral_constant<int, 64>{});
+  else f(grid, integral_constant<int, 1>{}, integral_constant<int, kThreads>{});
 }
 PairGeo pair_geo(int nx, int ny, int nz) {
   const unsigned row = (unsigned)(nz + 1) / 2;
@@ -1386,11 +1403,11 @@ hipError_t launch_cg_iter(const PGeom& g, const double* cx, const double* cy, co
                           double* r, double* partial, int max_iter, CGState* st,
                           hipStream_t s, int nrhs, const MGData* mg) {
   const PairGeo pg = pair_geo(g.px, g.py, g.pz);
-  const int nb = sp_blocks(pg.pairs);
-  for_group(pg.pairs, nrhs, [&](auto nr) {
-    constexpr int NR = decltype(nr)::value;
-    cg_matvec_kernel<NR><<<dim3(nb, groups<NR>(nrhs)), kThreads, 0, s>>>(
-        g.NP, pg, cx, cy, cz, dir, z, p_old, p_new, q, partial, st, nrhs);
+  const int nb = share(pg.pairs, nrhs).blocks;
+  shared_launch(pg.pairs, nrhs, [&](dim3 grid, auto nr, auto nt) {
+    constexpr int NR = decltype(nr)::value, NT = decltype(nt)::value;
+    cg_matvec_kernel<NR, NT><<<grid, NT, 0, s>>>(g.NP, pg, cx, cy, cz, dir, z, p_old, p_new, q,
+                                                 partial, st, nrhs);
   });
   cg_alpha_kernel<<<dim3(1, nrhs), kRedThreads, 0, s>>>(partial, nb, st);
   if (!mg) {
@@ -1404,16 +1421,16 @@ hipError_t launch_cg_iter(const PGeom& g, const double* cx, const double* cy, co
   // spent once p_new is formed) and the V-cycle's z to r's, so the caller swaps the
   // two buffers from one iteration to the next
   const MGPlan& P = mg->plan;
-  const unsigned nbu = (unsigned)sp_blocks(4 * P.lv[1].N);
-  for_group(4 * P.lv[1].N, nrhs, [&](auto nr) {
-    constexpr int NR = decltype(nr)::value;
-    mg_restrict_kernel<true, NR><<<dim3(nbu, groups<NR>(nrhs)), kThreads, 0, s>>>(
+  const int nbu = share(4 * P.lv[1].N, nrhs).blocks;
+  shared_launch(4 * P.lv[1].N, nrhs, [&](dim3 grid, auto nr, auto nt) {
+    constexpr int NR = decltype(nr)::value, NT = decltype(nt)::value;
+    mg_restrict_kernel<true, NR, NT><<<grid, NT, 0, s>>>(
         mg_args(*mg, 0), mg_geo(P.lv[1]), kMGOmega, r, g.NP, mg->b + P.lv[1].voff, P.vtotal, st,
         nrhs, p_new, q, phi, z, partial);
   });
   const hipError_t e = launch_mg_vcycle(g, *mg, z, r, st, nrhs, s, false);
   if (e != hipSuccess) return e;
-  cg_beta_mg_kernel<<<dim3(1, nrhs), kRedThreads, 0, s>>>(partial, (int)nbu, mg->partial_rz, nb,
+  cg_beta_mg_kernel<<<dim3(1, nrhs), kRedThreads, 0, s>>>(partial, nbu, mg->partial_rz, nb,
                                                           max_iter, st);
   return hipGetLastError();
 }
@@ -1483,12 +1500,11 @@ hipError_t launch_mg_vcycle(const PGeom& g, const MGData& m, const double* r, do
   auto bvec = [&](int k) { return k == 0 ? r : m.b + P.lv[k].voff; };
   for (int k = restrict0 ? 0 : 1; k < t; ++k) {
     const MGLevel& C = P.lv[k + 1];
-    for_group(4 * C.N, nrhs, [&](auto nr) {
-      constexpr int NR = decltype(nr)::value;
-      mg_restrict_kernel<false, NR>
-          <<<dim3(mg_blocks(4 * C.N), groups<NR>(nrhs)), kThreads, 0, s>>>(
-              margs(m, k), mgeo(C), kMGOmega, bvec(k), k == 0 ? g.NP : vs, m.b + C.voff, vs, st,
-              nrhs, nullptr, nullptr, nullptr, nullptr, nullptr);
+    shared_launch(4 * C.N, nrhs, [&](dim3 grid, auto nr, auto nt) {
+      constexpr int NR = decltype(nr)::value, NT = decltype(nt)::value;
+      mg_restrict_kernel<false, NR, NT><<<grid, NT, 0, s>>>(
+          margs(m, k), mgeo(C), kMGOmega, bvec(k), k == 0 ? g.NP : vs, m.b + C.voff, vs, st, nrhs,
+          nullptr, nullptr, nullptr, nullptr, nullptr);
     });
   }
   MGTailArgs T{};
@@ -1502,18 +1518,18 @@ hipError_t launch_mg_vcycle(const PGeom& g, const MGData& m, const double* r, do
   for (int k = t - 1; k >= 1; --k) {
     const MGLevel &F = P.lv[k], &C = P.lv[k + 1];
     const PairGeo pg = pair_geo(F.nx, F.ny, F.nz);
-    for_group(pg.pairs, nrhs, [&](auto nr) {
-      constexpr int NR = decltype(nr)::value;
-      mg_correct_kernel<false, NR><<<dim3(mg_blocks(pg.pairs), groups<NR>(nrhs)), kThreads, 0, s>>>(
+    shared_launch(pg.pairs, nrhs, [&](dim3 grid, auto nr, auto nt) {
+      constexpr int NR = decltype(nr)::value, NT = decltype(nt)::value;
+      mg_correct_kernel<false, NR, NT><<<grid, NT, 0, s>>>(
           margs(m, k), pg, mgeo(C), kMGOmega, 1.0, m.b + F.voff, vs, m.u + C.voff, vs, m.u + F.voff,
           vs, nullptr, st, nrhs);
     });
   }
   const MGLevel& C1 = P.lv[1];
   const PairGeo pg = pair_geo(g.px, g.py, g.pz);
-  for_group(pg.pairs, nrhs, [&](auto nr) {
-    constexpr int NR = decltype(nr)::value;
-    mg_correct_kernel<true, NR><<<dim3(mg_blocks(pg.pairs), groups<NR>(nrhs)), kThreads, 0, s>>>(
+  shared_launch(pg.pairs, nrhs, [&](dim3 grid, auto nr, auto nt) {
+    constexpr int NR = decltype(nr)::value, NT = decltype(nt)::value;
+    mg_correct_kernel<true, NR, NT><<<grid, NT, 0, s>>>(
         margs(m, 0), pg, mgeo(C1), kMGOmega, kMGAlpha, r, g.NP, m.u + C1.voff, vs, z, g.NP,
         m.partial_rz, st, nrhs);
   });
@@ -1525,7 +1541,7 @@ hipError_t launch_mg_start(const PGeom& g, const MGData& m, const double* r, dou
   const hipError_t e = launch_mg_vcycle(g, m, r, z, st, nrhs, s, true);
   if (e != hipSuccess) return e;
   cg_rz_kernel<<<dim3(1, nrhs), kRedThreads, 0, s>>>(
-      m.partial_rz, sp_blocks(pair_geo(g.px, g.py, g.pz).pairs), st);
+      m.partial_rz, share(pair_geo(g.px, g.py, g.pz).pairs, nrhs).blocks, st);
   return hipGetLastError();
 }
 
