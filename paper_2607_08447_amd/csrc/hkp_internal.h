@@ -45,6 +45,9 @@ __device__ __forceinline__ unsigned udiv(unsigned n, unsigned d, double inv) {
   return q;
 }
 
+// compute units of the current device (256 if it cannot be asked)
+int device_cus();
+
 // unit constants from CODATA 2018 (h, e exact; m0 = 9.1093837015e-31 kg),
 // ten significant digits
 constexpr double kE0 = 0.03809982116;         // hbar^2/(2 m0), eV nm^2

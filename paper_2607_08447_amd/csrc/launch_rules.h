@@ -20,24 +20,26 @@ constexpr int range_begin(int zc, int nz, int zs) {
   return zc * q + zc * r / zs;
 }
 
-constexpr int kCUs = 256;   // compute units of the GPU
+constexpr int kCUs = 256;   // compute units of the whole GPU (a partition of it has fewer)
 
 // z-ranges for nlw workgroups of nz planes, at most zmax: the fewest planes marched on
 // the CU that gets the most workgroups.  A workgroup marches nz / zs + 2 planes, a CU
-// gets ceil(nlw zs / 256) of them, and c0 workgroups together take no longer per
+// gets ceil(nlw zs / cus) of them, and c0 workgroups together take no longer per
 // plane than one alone (a plane's latency against its share of the CU).  Measured for
 // 480 FP32 recurrence workgroups (12 vectors of 128 x 40 x 40): 63 us in one range, 68
 // in two; 384 (4 vectors of 256 x 48 x 48): 81 in one, 64 in four; 144 FP64 product
 // ones (6 vectors of 96 x 32 x 32): 53 in one, 35 in two, 28 in three, 30 in four.
 constexpr int kMaxSplit = 12;
-constexpr int z_ranges(int nlw, int nz, int zmax, float c0) {
+constexpr int z_ranges(int nlw, int nz, int zmax, float c0, int cus) {
   constexpr float inv[kMaxSplit] = {1.0f,     1.0f / 2, 1.0f / 3, 1.0f / 4,  1.0f / 5,  1.0f / 6,
                                     1.0f / 7, 1.0f / 8, 1.0f / 9, 1.0f / 10, 1.0f / 11, 1.0f / 12};
   int best = 1;
   float cost = 1e30f;
+  const float icus = 1.0f / (float)cus;
 #pragma unroll
   for (int zs = 1; zs <= kMaxSplit; ++zs) {
-    const float per_cu = (float)(((unsigned)nlw * zs + kCUs - 1) / kCUs);
+    // the ceiling, by the reciprocal (half a workgroup's margin against its rounding)
+    const float per_cu = (float)(int)(((float)nlw * (float)zs + (float)cus - 0.5f) * icus);
     const float c = (per_cu > c0 ? per_cu : c0) * ((float)nz * inv[zs - 1] + 2.0f);
     if (c < cost && zs <= zmax && zs <= nz) {
       best = zs;
@@ -65,9 +67,9 @@ constexpr long long table_vectors(long long all, long long live, long long most)
 struct ZSplit {
   int room, fixed;
 };
-constexpr ZSplit z_split(long long nwg, int nz, bool on_device, float c0) {
-  const int zs = nwg < 16 * kCUs ? z_ranges((int)nwg, nz, 8, c0) : 1;
-  if (!on_device || nwg >= 16 * kCUs) return ZSplit{zs, zs};
+constexpr ZSplit z_split(long long nwg, int nz, bool on_device, float c0, int cus) {
+  const int zs = nwg < 16 * cus ? z_ranges((int)nwg, nz, 8, c0, cus) : 1;
+  if (!on_device || nwg >= 16 * cus) return ZSplit{zs, zs};
   return ZSplit{2 * zs < kMaxSplit ? 2 * zs : kMaxSplit, 0};
 }
 
@@ -75,8 +77,8 @@ constexpr ZSplit z_split(long long nwg, int nz, bool on_device, float c0) {
 // `active` that are left: its launches were too large to be split (member_wgs: workgroups
 // of one member's vectors), and a quarter of them would fill the chip less well.  (A
 // recording takes a millisecond or two, such an iteration a hundred.)
-constexpr bool record_anew(int recorded, int active, long long member_wgs) {
-  return active > 0 && 4LL * active <= recorded && recorded * member_wgs >= 16 * kCUs;
+constexpr bool record_anew(int recorded, int active, long long member_wgs, int cus) {
+  return active > 0 && 4LL * active <= recorded && recorded * member_wgs >= 16 * cus;
 }
 
 // Launch shapes that the tuner times for a filter step: waves per spin, vectors side by

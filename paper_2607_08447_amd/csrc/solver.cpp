@@ -1036,7 +1036,7 @@ int run_solve(const SolveArgs& A, hkp_stats* stats) {
     while (iters < A.max_iter && !all_done() && !user_stop) {
       count_work();
       const int need = (c.live32 > 0 ? 1 : 0) | (c.live64 > 0 ? 2 : 0);
-      if (!rec[need].exec || record_anew(rec[need].members, c.active_members, member_wgs))
+      if (!rec[need].exec || record_anew(rec[need].members, c.active_members, member_wgs, device_cus()))
         record(need, rec[need]);
       sst.hx_bytes += rec[need].bytes;
       HKP_CHECK(hipGraphLaunch(rec[need].exec, c.s));

@@ -1366,9 +1366,10 @@ struct Share {
   int nr, nt, blocks;   // blocks: workgroups per system (or group of systems)
 };
 Share share(long long threads, int nrhs) {
-  if (nrhs > 2 && threads * groups<4>(nrhs) >= 4LL * kCUs * kThreads)
+  const long long cus = device_cus();
+  if (nrhs > 2 && threads * groups<4>(nrhs) >= 4 * cus * kThreads)
     return Share{4, kThreads, sp_blocks(threads)};
-  if (threads * nrhs < (long long)kCUs * kThreads)
+  if (threads * nrhs < cus * kThreads)
     return Share{1, 64, (int)((threads + 63) / 64)};
   return Share{1, kThreads, sp_blocks(threads)};
 }

@@ -25,6 +25,7 @@
 // vectors of one tile share an L2.  Two ways of staging a plane: copies of whole rows
 // (stencil_kernel) and through registers (stencil_pipe_kernel); launch_t chooses.
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 #include "hkp_internal.h"
@@ -60,6 +61,7 @@ struct KArgs {
   int zsplit;   // z-ranges that the grid leaves room for
   int zfixed;   // z-ranges of the launch, or 0: from the live count
   float c0;
+  int cus;      // compute units of the device
   int stream;   // blocks beyond the cache: the old block and the output pass it by
   int nx, ny, nz, nvec;
   int tiles_x, tiles_y;
@@ -92,7 +94,7 @@ __device__ __forceinline__ bool find_place(const KArgs<T>& a, Place* p) {
   int zs = 1;
   if (a.zsplit > 1) {
     zs = a.zfixed;
-    if (zs == 0) zs = z_ranges(nlw, a.nz, a.zsplit, a.c0);
+    if (zs == 0) zs = z_ranges(nlw, a.nz, a.zsplit, a.c0, a.cus);
   }
   const int nlive = nlw * zs;
   if (nlive <= 0 || (int)blockIdx.x >= nlive) return false;
@@ -665,12 +667,13 @@ hipError_t launch_t(const StencilLaunch& L, const StencilConsts<double>& c, hipS
     if (nwg <= 0) return hipSuccess;
     // z split: 0 never, 1 as balances the launch (z_split), 2 always in two (tests)
     a.c0 = sizeof(T) == 8 ? 2.2f : (std::is_same<TO, void>::value ? 2.6f : 2.0f);
+    a.cus = device_cus();
     a.zsplit = a.zfixed = 1;
     if (L.zsplit >= 2) {
       a.zsplit = 2;
       a.zfixed = L.nz >= 8 ? 2 : 1;
     } else if (L.zsplit == 1) {
-      const ZSplit z = z_split(nwg, L.nz, L.work && L.vlive < 0, a.c0);
+      const ZSplit z = z_split(nwg, L.nz, L.work && L.vlive < 0, a.c0, a.cus);
       a.zsplit = z.room;
       a.zfixed = z.fixed;
     }
@@ -738,6 +741,23 @@ hipError_t launch_ph(const StencilLaunch& L, const StencilConsts<double>& c, hip
 }
 
 }  // namespace
+
+int device_cus() {
+  static std::atomic<int> known[64];   // per device, 0: not asked yet
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) {
+    (void)hipGetLastError();
+    return kCUs;
+  }
+  int n = known[dev].load(std::memory_order_relaxed);
+  if (n > 0) return n;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) {
+    (void)hipGetLastError();
+    return kCUs;
+  }
+  known[dev].store(n, std::memory_order_relaxed);
+  return n;
+}
 
 StencilConsts<double> make_consts(const hkp_material& m, double h, const double B[3]) {
   const double L = m.gamma1 + 4.0 * m.gamma2, M = m.gamma1 - 2.0 * m.gamma2;

@@ -30,13 +30,15 @@ int main() {
     }
     if (!std::strcmp(what, "range")) std::printf("%d\n", range_begin((int)a, (int)b, (int)c));
     if (!std::strcmp(what, "fold")) std::printf("%zu\n", fold_offset((int)a));
-    if (!std::strcmp(what, "room")) std::printf("%d\n", z_split(a, (int)b, c != 0, c0[1]).room);
-    if (!std::strcmp(what, "fixed")) std::printf("%d\n", z_split(a, (int)b, c != 0, c0[1]).fixed);
+    if (!std::strcmp(what, "room")) std::printf("%d\n", z_split(a, (int)b, c != 0, c0[1], d ? (int)d : kCUs).room);
+    if (!std::strcmp(what, "fixed")) std::printf("%d\n", z_split(a, (int)b, c != 0, c0[1], d ? (int)d : kCUs).fixed);
+    if (!std::strcmp(what, "ranges"))   // a live workgroups, b planes, at most c ranges, d CUs
+      std::printf("%d\n", z_ranges((int)a, (int)b, (int)c, c0[1], (int)d));
     if (!std::strcmp(what, "vectors")) std::printf("%lld\n", table_vectors(a, b, c));
-    if (!std::strcmp(what, "anew")) std::printf("%d\n", record_anew((int)a, (int)b, c) ? 1 : 0);
+    if (!std::strcmp(what, "anew")) std::printf("%d\n", record_anew((int)a, (int)b, c, kCUs) ? 1 : 0);
     for (int k = 0; k < 3; ++k)   // ranges of `c` live workgroups in a launch over `a`
       if (!std::strcmp(what, "live"))
-        std::printf("%d\n", z_ranges((int)c, (int)b, z_split(a, (int)b, true, c0[k]).room, c0[k]));
+        std::printf("%d\n", z_ranges((int)c, (int)b, z_split(a, (int)b, true, c0[k], kCUs).room, c0[k], kCUs));
   }
 }
 """
@@ -106,6 +108,22 @@ def test_room_for_z_ranges(rules):
     room = rules([("room", n, nz, 1) for n, nz in sizes])
     assert all((r >= 2) == (n < 4096) for (n, _), r in zip(sizes, room))
     assert all(n * r < 1 << 31 for (n, _), r in zip(sizes, room))
+
+
+@pytest.mark.parametrize("cus", [32, 64, 256, 304])
+def test_launches_are_balanced_for_the_device(rules, cus):
+    """The split minimises planes on the fullest CU of the device's count, whole or a
+    partition: against the rule in exact integers."""
+    def cost(n, nz, zs):
+        return max(-(-n * zs // cus), 2.2) * (nz / zs + 2)
+    q = [(n, nz) for n in (1, 7, 30, 31, 32, 33, 100, 255, 256, 257, 480, 511, 513, 2000, 4095)
+         for nz in (1, 5, 40, 48)]
+    for (n, nz), zs in zip(q, rules([("ranges", n, nz, 8, cus) for n, nz in q])):
+        best = min(cost(n, nz, z) for z in range(1, min(8, nz) + 1))
+        assert 1 <= zs <= min(8, nz) and cost(n, nz, zs) <= best * (1 + 1e-5), (n, nz, zs)
+    # a launch that fills a partition is not split there, but is on the whole GPU
+    assert rules([("fixed", 16 * 32, 48, 0, 32)]) == [1]
+    assert rules([("fixed", 100, 48, 0, 256)])[0] > 1
 
 
 @pytest.mark.parametrize("nb", [1, 2, 3, 4, 5, 24])
