@@ -13,11 +13,20 @@ constexpr int kFoldRow = 12;
 // first real of plane z in that table (beyond 32 bits from 9e7 planes)
 constexpr std::size_t fold_offset(int z) { return (std::size_t)z * (2 * kFoldRow); }
 
-// first of nz planes in range zc of zs: floor(zc nz / zs), without the product (zc nz
-// exceeds 32 bits for long columns; a 64-bit division costs far more than these)
-constexpr int range_begin(int zc, int nz, int zs) {
-  const int q = nz / zs, r = nz - q * zs;
-  return zc * q + zc * r / zs;
+// nz planes in zs <= kMaxSplit ranges, range zc from floor(zc nz / zs): without the product
+// zc nz, which exceeds 32 bits for long columns, and without a division once nz is cut
+// (the host does it for the launches that it splits)
+constexpr int kMaxSplit = 12;
+struct ZCut {
+  int q, r;      // nz = q zs + r
+  unsigned m;    // (n m) >> 16 = floor(n / zs) for n < zs kMaxSplit
+};
+constexpr ZCut z_cut(int nz, int zs) {
+  const int q = nz / zs;
+  return ZCut{q, nz - q * zs, 65536u / (unsigned)zs + 1u};
+}
+constexpr int range_begin(int zc, const ZCut& c) {
+  return zc * c.q + (int)(((unsigned)(zc * c.r) * c.m) >> 16);
 }
 
 constexpr int kCUs = 256;   // compute units of the whole GPU (a partition of it has fewer)
@@ -29,7 +38,6 @@ constexpr int kCUs = 256;   // compute units of the whole GPU (a partition of it
 // 480 FP32 recurrence workgroups (12 vectors of 128 x 40 x 40): 63 us in one range, 68
 // in two; 384 (4 vectors of 256 x 48 x 48): 81 in one, 64 in four; 144 FP64 product
 // ones (6 vectors of 96 x 32 x 32): 53 in one, 35 in two, 28 in three, 30 in four.
-constexpr int kMaxSplit = 12;
 constexpr int z_ranges(int nlw, int nz, int zmax, float c0, int cus) {
   constexpr float inv[kMaxSplit] = {1.0f,     1.0f / 2, 1.0f / 3, 1.0f / 4,  1.0f / 5,  1.0f / 6,
                                     1.0f / 7, 1.0f / 8, 1.0f / 9, 1.0f / 10, 1.0f / 11, 1.0f / 12};

@@ -60,6 +60,7 @@ struct KArgs {
   int vfirst;
   int zsplit;   // z-ranges that the grid leaves room for
   int zfixed;   // z-ranges of the launch, or 0: from the live count
+  ZCut cut;     // the planes in zfixed ranges
   float c0;
   int cus;      // compute units of the device
   int stream;   // blocks beyond the cache: the old block and the output pass it by
@@ -203,7 +204,8 @@ stencil_pipe_kernel(KArgs<T> a) {
   const int nx = a.nx, ny = a.ny, nz = a.nz;
   const int tx0 = (pl.tile % a.tiles_x) * TX, ty0 = (pl.tile / a.tiles_x) * RH;
   // output planes [o0, o1) of this range; input planes p0..p1 feed them
-  const int o0 = range_begin(pl.zc, nz, pl.zs), o1 = range_begin(pl.zc + 1, nz, pl.zs);
+  const ZCut cut = a.zfixed ? a.cut : z_cut(nz, pl.zs);
+  const int o0 = range_begin(pl.zc, cut), o1 = range_begin(pl.zc + 1, cut);
   const int p0 = o0 > 0 ? o0 - 1 : 0, p1 = o1 < nz ? o1 : nz - 1;
   const unsigned nxy = (unsigned)nx * (unsigned)ny;
   const unsigned N = nxy * (unsigned)nz;   // 6 N < 2^31 (checked on the host)
@@ -433,13 +435,14 @@ stencil_kernel(KArgs<T> a) {
 
   Place pl;
   if (!place_workgroup(a, &pl)) return;
-  const int b = pl.b, vec = pl.vec, tile = pl.tile, zs = pl.zs, zc = pl.zc;
+  const int b = pl.b, vec = pl.vec, tile = pl.tile, zc = pl.zc;
   const int tx0 = (tile % a.tiles_x) * 64;
   const int ty0 = (tile / a.tiles_x) * TY;
 
   const int nx = a.nx, ny = a.ny, nz = a.nz;
   // output planes [o0, o1) of this range; input planes p0..p1 feed them
-  const int o0 = range_begin(zc, nz, zs), o1 = range_begin(zc + 1, nz, zs);
+  const ZCut cut = a.zfixed ? a.cut : z_cut(nz, pl.zs);
+  const int o0 = range_begin(zc, cut), o1 = range_begin(zc + 1, cut);
   const int p0 = o0 > 0 ? o0 - 1 : 0, p1 = o1 < nz ? o1 : nz - 1;
   const unsigned nxy = (unsigned)nx * (unsigned)ny;
   const unsigned N = nxy * (unsigned)nz;   // 6 N < 2^31 (checked on the host)
@@ -677,6 +680,7 @@ hipError_t launch_t(const StencilLaunch& L, const StencilConsts<double>& c, hipS
       a.zsplit = z.room;
       a.zfixed = z.fixed;
     }
+    a.cut = z_cut(L.nz, a.zfixed ? a.zfixed : 1);
     if (nwg * a.zsplit > 0x7fffffffLL) return hipErrorInvalidValue;
     kernel<<<dim3((unsigned)(nwg * a.zsplit)), dim3(64, waves, NSP), 0, s>>>(a);
     return hipGetLastError();
