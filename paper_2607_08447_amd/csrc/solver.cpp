@@ -1309,10 +1309,12 @@ int run_filter_step2(const Filter2Args& A, int* passes) {
 size_t gmatrix_bytes(const hkp_grid& g) {
   const size_t N = (size_t)g.nx * g.ny * g.nz, n6 = 6 * N;
   // what the call uses: the on-site fields, 4 + 16 vectors, the Gram partials (at most
-  // 512 N bytes) and product.  What it asks for is 44 vectors' worth, the size that the
-  // interface has always named.
+  // 512 (N + 15) bytes) and product.  What it asks for is the size that the interface has
+  // always named: 44 vectors, their Gram partials in chunks of 1024 entries (at most 2048)
+  // and the product.
+  const size_t chunks = std::min<size_t>(2048, (n6 + 1023) / 1024);
   return align_up(6 * N * 8) + align_up((size_t)44 * n6 * 16) +
-         align_up(gram_partial_bytes(44, (long long)n6, 1)) + align_up((size_t)16 * 44 * 16);
+         align_up(chunks * 44 * 44 * 16) + align_up((size_t)16 * 44 * 16);
 }
 
 int run_gmatrix(const GMatrixArgs& A) {
