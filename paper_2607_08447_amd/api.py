@@ -66,10 +66,9 @@ def _private_stream():
 @contextlib.contextmanager
 def _iter_callback(callback):
     """While the block runs, the eigensolves of this thread report to callback
-    (None: nothing) after every outer iteration (every replayed chunk in graph
-    mode): a dict with iter, batch, nb, nev and numpy arrays nconv [batch],
-    fp64 [batch], ritz_eV and resid_eV [batch, nb].  A true return value ends the
-    solve (status 1 unless every state converged); an exception raised by the
+    (None: nothing) after every outer iteration: a dict with iter, batch, nb, nev and
+    numpy arrays nconv [batch], fp64 [batch], ritz_eV and resid_eV [batch, nb].  A true
+    return value ends the solve (status 1 unless every state converged); an exception raised by the
     callback ends it too and is raised again after the call."""
     if callback is None:
         yield

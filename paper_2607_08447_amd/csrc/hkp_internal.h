@@ -460,13 +460,10 @@ hipError_t launch_anderson(const PGeom& g, int k, int m, int slot, double mixing
                            const double* F, double* histX, double* histF, double* G,
                            double* dots, double* gamma, double* partial, hipStream_t s);
 
-// g-matrices: an internal block of 44 spinors (LS, B = 0) whose slots 0-3 hold the
-// four states; slots 4 (a + 1) + v <- r_a psi_v (r about the box centre),
-// slots 32 + 4 b + v <- Z_b psi_v (Zeeman matrix per tesla); the post kernel turns
-// the 16 x 44 Gram product of slots 0-15 against 0-43 (slots 16-31 = H_0 of 0-15)
-// into an hkp_gmatrix_result
-// G [16][32] = {psi, r psi}^H [H_0 {psi, r psi}, psi, Z psi] from psi (4 vectors) and img = H_0
-// {psi, r psi} (16), internal layout; partial: gmatrix_partial_bytes(N)
+// g-matrices: G [16][32] = L^H [H_0 L, psi, Z psi], L = {psi, r psi} (row 4 c + i: r_c
+// psi_i, c = 0 psi itself; r about the box centre, Z_b the Zeeman matrix per tesla), from psi
+// (4 vectors, LS, B = 0) and img = H_0 L (16), both in the internal layout; the post kernel
+// turns it into an hkp_gmatrix_result.  partial: gmatrix_partial_bytes(N)
 size_t gmatrix_partial_bytes(long long N);
 hipError_t launch_gmatrix_gram(int nx, int ny, int nz, double h, double kappa, const double* psi,
                                const double* img, double* partial, double* G, hipStream_t s);

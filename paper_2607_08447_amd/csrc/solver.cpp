@@ -2,12 +2,13 @@
 // Rayleigh-Chebyshev method named in the paper, Sec. II.B):
 //
 //   bounds   k-step Lanczos -> upper spectral bound b
-//   init     random block, SVQB, Rayleigh-Ritz
+//   init     random block, orthonormalised, Rayleigh-Ritz
 //   repeat   filter:  Y = p_m(H) X, scaled three-term Chebyshev recurrence on
 //                     [a_cut, b] (a_cut = largest Ritz value of the block,
 //                     normalised at the lowest Ritz value) -- m fused stencil
 //                     steps, FP64 or FP32 (mixed precision)
-//            orth:    SVQB twice (Gram, Jacobi eig, rotate), FP64
+//            orth:    Gram matrix, its Cholesky factor (or SVQB's, twice, where it is
+//                     ill conditioned), applied by the Rayleigh-Ritz step, FP64
 //            RR:      W = H X (FP64), X^H W, Jacobi eig; one pass over X and W
 //                     gives X <- X Q, ||(W Q)_j - theta_j (X Q)_j|| and the next
 //                     filter's first step alpha (W Q - c X Q) (W Q is not stored)
@@ -531,9 +532,10 @@ void filter32(const Ctx& c, const int* active, int m) {
   while (k < m) single();
 }
 
-// SVQB factor of X: S = D U diag(lambda)^-1/2 from X^H X (X S orthonormal) into
-// `out`; `again` (optional) receives the per-member need for a second pass
-void svqb_factor(const Ctx& c, const int* active, size_t out, int* again = nullptr) {
+// orthonormalising factor S of X (X S orthonormal) from X^H X into `out`: the inverse
+// Cholesky factor where X^H X is provably well conditioned, else SVQB's D U
+// diag(lambda)^-1/2; `again` (optional) receives the per-member need for a second pass
+void orth_factor(const Ctx& c, const int* active, size_t out, int* again = nullptr) {
   BlockDesc X = c.blk(c.L.X, c.p.nb);
   HKP_CHECK(launch_gram(X, X, 1, c.p.batch, c.at<double>(c.L.gram), c.at<double>(c.L.mat1),
                         active, c.s));
@@ -542,7 +544,7 @@ void svqb_factor(const Ctx& c, const int* active, size_t out, int* again = nullp
                         active, c.s, again));
 }
 
-// orthonormalise X by SVQB: its factor S goes to mat3 and is applied by the
+// orthonormalise X: the factor S goes to mat3 and is applied by the
 // Rayleigh-Ritz rotation (X S Q in one pass over the block).  Members whose Gram
 // matrix was ill conditioned (one pass would leave an orthogonality error
 // ~ eps kappa) are rotated now and take a second pass; their mat3 is I.
@@ -550,14 +552,14 @@ void orthonormalise(const Ctx& c, const int* active) {
   int* again = c.at<int>(c.L.again);
   const long long ms = (long long)c.p.nb * c.p.nb;
   BlockDesc X = c.blk(c.L.X, c.p.nb);
-  svqb_factor(c, active, c.L.mat3, again);
+  orth_factor(c, active, c.L.mat3, again);
   HKP_CHECK(launch_rotate(X, X, c.p.nb, c.p.nb, c.at<double>(c.L.mat3), c.p.batch, again, c.s));
-  svqb_factor(c, again, c.L.mat2);
+  orth_factor(c, again, c.L.mat2);
   HKP_CHECK(launch_rotate(X, X, c.p.nb, c.p.nb, c.at<double>(c.L.mat2), c.p.batch, again, c.s));
   HKP_CHECK(launch_set_identity(c.at<double>(c.L.mat3), c.p.nb, c.p.batch, ms, again, c.s));
 }
 
-// Rayleigh-Ritz on the span of X S (S in mat3, the SVQB factor or I): W = H X,
+// Rayleigh-Ritz on the span of X S (S in mat3, the orthonormalising factor or I): W = H X,
 // the projection S^H (X^H W) S, its eigenpairs (theta, Q), T = S Q; then one
 // pass over X and W gives X <- X T, the residual norms ||(W T)_j - theta_j
 // (X T)_j|| and the next filter's first step alpha (W T - c X T) (FP32 for
@@ -797,7 +799,7 @@ int run_solve(const SolveArgs& A, hkp_stats* stats) {
     ++n_sync;
   }
 
-  // ---- initial block: caller's X0 or random; SVQB; Rayleigh-Ritz
+  // ---- initial block: caller's X0 or random; orthonormalised; Rayleigh-Ritz
   const bool spin_free = (A.flags & HKP_FLAG_SPIN_FREE) != 0;
   if (spin_free) {
     // three-component orbital blocks
@@ -1302,9 +1304,8 @@ int run_filter_step2(const Filter2Args& A, int* passes) {
 }
 
 // ---------------------------------------------------------------------------
-// g-matrices: psi, r_a psi (16 vectors) -> H_0 of them, Z_b psi -> one Gram product
-// L^H [L, H_0 L, Z psi] (16 x 44; L, the first 16 vectors of the block, is read twice
-// by the same workgroup, the second time from cache).
+// g-matrices: H_0 of L = {psi, r_a psi} (16 vectors, formed from psi as they are read),
+// then one Gram product L^H [H_0 L, psi, Z_b psi] (16 x 32), which reads psi and the images
 // ---------------------------------------------------------------------------
 size_t gmatrix_bytes(const hkp_grid& g) {
   const size_t N = (size_t)g.nx * g.ny * g.nz, n6 = 6 * N;
