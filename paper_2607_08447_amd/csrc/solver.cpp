@@ -960,12 +960,7 @@ int run_solve(const SolveArgs& A, hkp_stats* stats) {
       ++iters;
       m_cur = degree_at(iters);
       count_work();
-      if (p.batch == 1) {
-        const bool f32 = p.mixed && !hflags[1];
-        iteration(iters, true, f32, degree_at(iters + 1));
-      } else {
-        iteration(iters, false, false, degree_at(iters + 1));
-      }
+      iteration(iters, c.live32 == 0 || c.live64 == 0, c.live32 > 0, degree_at(iters + 1));
       read_flags();
       report(iters);
       if (trace) {

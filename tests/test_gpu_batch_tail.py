@@ -52,3 +52,20 @@ def test_last_members_of_a_batch(batch, degree, precision, tol, product, graph):
     done = [int((n == NEV).sum()) for n in counts]
     print("members done after each iteration", done, flush=True)
     assert MEMBERS - 15 <= done[-2] < MEMBERS   # the end was a few members' alone
+
+
+def test_steps_counted_are_steps_run(batch):
+    """The FP32 filter's timed steps are those of the iterations in which a member was
+    filtered in FP32; once all are in FP64 there are none."""
+    import torch
+    import paper_2607_08447_amd as hkp
+    w, Vs, S, X0, _ = batch
+    print("batch tail counted steps", flush=True)
+    rows = []
+    r = hkp.solve_batch(torch.from_numpy(Vs), w.h, NEV, strain=S, B=w.B, nb=NB, tol=1e-9, X0=X0,
+                        precision="mixed", graph=False, degree=24, max_iter=100,
+                        callback=lambda i: rows.append((i["nconv"], i["fp64"])))
+    assert r.status == 0
+    in32 = [bool(((n < NEV) & (f == 0)).any()) for n, f in rows]   # before the next iteration
+    assert not all(in32[:-1])
+    assert 0 < r.stats["n_stencil32"] <= 23 * (1 + sum(in32))
