@@ -11,19 +11,25 @@ namespace hkp {
 // complex entries per plane of the folded link-phase table
 constexpr int kFoldRow = 12;
 // first real of plane z in that table (beyond 32 bits from 9e7 planes)
-constexpr std::size_t fold_offset(int z) { return (std::size_t)z * (2 * kFoldRow); }
+constexpr std::size_t fold_offset(int z) {
+  return (std::size_t)((unsigned long long)(unsigned)z * (unsigned)(2 * kFoldRow));
+}
 
 // nz planes in zs <= kMaxSplit ranges, range zc from floor(zc nz / zs): without the product
 // zc nz, which exceeds 32 bits for long columns, and without a division once nz is cut
 // (the host does it for the launches that it splits)
 constexpr int kMaxSplit = 12;
+struct ZRanges {
+  int zs;
+  float inv;     // 1 / zs
+};
 struct ZCut {
   int q, r;      // nz = q zs + r
-  unsigned m;    // (n m) >> 16 = floor(n / zs) for n < zs kMaxSplit
+  unsigned m;    // floor(65536 / zs) + 1: (n m) >> 16 = floor(n / zs) for n < zs kMaxSplit
 };
-constexpr ZCut z_cut(int nz, int zs) {
-  const int q = nz / zs;
-  return ZCut{q, nz - q * zs, 65536u / (unsigned)zs + 1u};
+constexpr ZCut z_cut(int nz, const ZRanges& z) {
+  const int q = nz / z.zs;
+  return ZCut{q, nz - q * z.zs, (unsigned)(65536.0f * z.inv) + 1u};
 }
 constexpr int range_begin(int zc, const ZCut& c) {
   return zc * c.q + (int)(((unsigned)(zc * c.r) * c.m) >> 16);
@@ -38,19 +44,20 @@ constexpr int kCUs = 256;   // compute units of the whole GPU (a partition of it
 // 480 FP32 recurrence workgroups (12 vectors of 128 x 40 x 40): 63 us in one range, 68
 // in two; 384 (4 vectors of 256 x 48 x 48): 81 in one, 64 in four; 144 FP64 product
 // ones (6 vectors of 96 x 32 x 32): 53 in one, 35 in two, 28 in three, 30 in four.
-constexpr int z_ranges(int nlw, int nz, int zmax, float c0, int cus) {
+// (icus: 1 / cus.  No division: a launch whose live count is only known on the device
+// evaluates this in every workgroup, before its first plane)
+constexpr ZRanges z_ranges(int nlw, int nz, int zmax, float c0, float cus, float icus) {
   constexpr float inv[kMaxSplit] = {1.0f,     1.0f / 2, 1.0f / 3, 1.0f / 4,  1.0f / 5,  1.0f / 6,
                                     1.0f / 7, 1.0f / 8, 1.0f / 9, 1.0f / 10, 1.0f / 11, 1.0f / 12};
-  int best = 1;
+  ZRanges best{1, 1.0f};
   float cost = 1e30f;
-  const float icus = 1.0f / (float)cus;
 #pragma unroll
   for (int zs = 1; zs <= kMaxSplit; ++zs) {
     // the ceiling, by the reciprocal (half a workgroup's margin against its rounding)
-    const float per_cu = (float)(int)(((float)nlw * (float)zs + (float)cus - 0.5f) * icus);
+    const float per_cu = (float)(int)(((float)nlw * (float)zs + cus - 0.5f) * icus);
     const float c = (per_cu > c0 ? per_cu : c0) * ((float)nz * inv[zs - 1] + 2.0f);
     if (c < cost && zs <= zmax && zs <= nz) {
-      best = zs;
+      best = ZRanges{zs, inv[zs - 1]};
       cost = c;
     }
   }
@@ -73,12 +80,15 @@ constexpr long long table_vectors(long long all, long long live, long long most)
 // members of 192 x 40 x 40 of which four are slow, mixed 0.690 -> 0.665 s launch by
 // launch and 0.676 -> 0.664 s recorded.
 struct ZSplit {
-  int room, fixed;
+  int room;
+  ZRanges fixed;
 };
 constexpr ZSplit z_split(long long nwg, int nz, bool on_device, float c0, int cus) {
-  const int zs = nwg < 16 * cus ? z_ranges((int)nwg, nz, 8, c0, cus) : 1;
-  if (!on_device || nwg >= 16 * cus) return ZSplit{zs, zs};
-  return ZSplit{2 * zs < kMaxSplit ? 2 * zs : kMaxSplit, 0};
+  const ZRanges z = nwg < 16 * cus
+                        ? z_ranges((int)nwg, nz, 8, c0, (float)cus, 1.0f / (float)cus)
+                        : ZRanges{1, 1.0f};
+  if (!on_device || nwg >= 16 * cus) return ZSplit{z.zs, z};
+  return ZSplit{2 * z.zs < kMaxSplit ? 2 * z.zs : kMaxSplit, ZRanges{0, 0.0f}};
 }
 
 // Whether an iteration recorded for `recorded` active members is recorded anew for the

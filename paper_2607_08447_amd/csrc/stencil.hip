@@ -62,7 +62,7 @@ struct KArgs {
   int zfixed;   // z-ranges of the launch, or 0: from the live count
   ZCut cut;     // the planes in zfixed ranges
   float c0;
-  int cus;      // compute units of the device
+  float cus, icus;   // compute units of the device, and their reciprocal
   int stream;   // blocks beyond the cache: the old block and the output pass it by
   int nx, ny, nz, nvec;
   int tiles_x, tiles_y;
@@ -84,7 +84,8 @@ struct KArgs {
 // zsplit x the unsplit count; the split is decided from the live count, uniformly
 // for the whole launch (z_ranges).
 struct Place {
-  int b, vec, tile, zs, zc;
+  int b, vec, tile, zc;
+  ZCut cut;
 };
 
 template <typename T>
@@ -93,14 +94,21 @@ __device__ __forceinline__ bool find_place(const KArgs<T>& a, Place* p) {
   const int nv = a.work ? a.work[a.batch] : 0;   // live vectors
   const int nlw = a.work ? nv * ntiles : (int)gridDim.x / a.zsplit;
   int zs = 1;
+  p->cut = a.cut;
   if (a.zsplit > 1) {
     zs = a.zfixed;
-    if (zs == 0) zs = z_ranges(nlw, a.nz, a.zsplit, a.c0, a.cus);
+    if (zs == 0) {
+      const ZRanges z = z_ranges(nlw, a.nz, a.zsplit, a.c0, a.cus, a.icus);
+      zs = __builtin_amdgcn_readfirstlane(z.zs);
+      const ZCut c = z_cut(a.nz, z);
+      p->cut.q = __builtin_amdgcn_readfirstlane(c.q);
+      p->cut.r = __builtin_amdgcn_readfirstlane(c.r);
+      p->cut.m = (unsigned)__builtin_amdgcn_readfirstlane((int)c.m);
+    }
   }
   const int nlive = nlw * zs;
   if (nlive <= 0 || (int)blockIdx.x >= nlive) return false;
   int logical = xcd_remap(blockIdx.x, nlive);
-  p->zs = zs;
   p->zc = logical / nlw;   // z range outermost: one range of all tiles per XCD run
   logical -= p->zc * nlw;
   if (a.work) {
@@ -134,7 +142,6 @@ __device__ __forceinline__ bool place_workgroup(const KArgs<T>& a, Place* p) {
   p->b = __builtin_amdgcn_readfirstlane(p->b);
   p->vec = __builtin_amdgcn_readfirstlane(p->vec);
   p->tile = __builtin_amdgcn_readfirstlane(p->tile);
-  p->zs = __builtin_amdgcn_readfirstlane(p->zs);
   p->zc = __builtin_amdgcn_readfirstlane(p->zc);
   return true;
 }
@@ -204,8 +211,7 @@ stencil_pipe_kernel(KArgs<T> a) {
   const int nx = a.nx, ny = a.ny, nz = a.nz;
   const int tx0 = (pl.tile % a.tiles_x) * TX, ty0 = (pl.tile / a.tiles_x) * RH;
   // output planes [o0, o1) of this range; input planes p0..p1 feed them
-  const ZCut cut = a.zfixed ? a.cut : z_cut(nz, pl.zs);
-  const int o0 = range_begin(pl.zc, cut), o1 = range_begin(pl.zc + 1, cut);
+  const int o0 = range_begin(pl.zc, pl.cut), o1 = range_begin(pl.zc + 1, pl.cut);
   const int p0 = o0 > 0 ? o0 - 1 : 0, p1 = o1 < nz ? o1 : nz - 1;
   const unsigned nxy = (unsigned)nx * (unsigned)ny;
   const unsigned N = nxy * (unsigned)nz;   // 6 N < 2^31 (checked on the host)
@@ -281,6 +287,9 @@ stencil_pipe_kernel(KArgs<T> a) {
   const int lb = (ly + 1) * W + (lx + 1);   // this thread's centre in an LDS plane
   cx<double> ux = mk<double>(1, 0);
   if constexpr (PH == 2) ux = ld(a.utab64 + 2 * (gx < nx ? gx : nx - 1));
+  // the folded phases' rows, from plane p0 on (advanced: a product per plane costs more)
+  const T* frow = a.ptab + (PH != 0 ? fold_offset(p0) : 0);
+  const double* frow64 = a.ptab64 + (PH == 2 ? fold_offset(p0) : 0);
 
   const bool stream = a.stream != 0;
 
@@ -360,7 +369,9 @@ stencil_pipe_kernel(KArgs<T> a) {
     fetch(z + 2 < p1 ? z + 2 : p1);
     load_fields(z + 1 < nz ? z + 1 : z, nxt);
     load_old(z < o1 ? (z > o0 ? z : o0) : o1 - 1, nxt);
-    const Fold<T> f = load_fold<T, PH>(a.ptab, a.ptab64, z, ux);
+    const Fold<T> f = load_fold<T, PH>(frow, frow64, ux);
+    if constexpr (PH != 0) frow += fold_offset(1);
+    if constexpr (PH == 2) frow64 += fold_offset(1);
     const T d00 = cur.d[0], d11 = cur.d[STR ? 1 : 0], d22 = cur.d[STR ? 2 : 0];
     const T d12 = STR ? cur.d[STR ? 3 : 0] : (T)0;
     const T d02 = STR ? cur.d[STR ? 4 : 0] : (T)0;
@@ -441,8 +452,7 @@ stencil_kernel(KArgs<T> a) {
 
   const int nx = a.nx, ny = a.ny, nz = a.nz;
   // output planes [o0, o1) of this range; input planes p0..p1 feed them
-  const ZCut cut = a.zfixed ? a.cut : z_cut(nz, pl.zs);
-  const int o0 = range_begin(zc, cut), o1 = range_begin(zc + 1, cut);
+  const int o0 = range_begin(zc, pl.cut), o1 = range_begin(zc + 1, pl.cut);
   const int p0 = o0 > 0 ? o0 - 1 : 0, p1 = o1 < nz ? o1 : nz - 1;
   const unsigned nxy = (unsigned)nx * (unsigned)ny;
   const unsigned N = nxy * (unsigned)nz;   // 6 N < 2^31 (checked on the host)
@@ -544,6 +554,8 @@ stencil_kernel(KArgs<T> a) {
 
   cx<double> ux = mk<double>(1, 0);
   if constexpr (PH == 2) ux = ld(a.utab64 + 2 * gxc);
+  const T* frow = a.ptab + (PH != 0 ? fold_offset(p0) : 0);   // as in the staged march
+  const double* frow64 = a.ptab64 + (PH == 2 ? fold_offset(p0) : 0);
 
   // on-site fields of this column, loaded one plane ahead (d00 d11 d22 d12 d02 d01;
   // without strain only the first)
@@ -578,7 +590,9 @@ stencil_kernel(KArgs<T> a) {
     const T d01 = STR ? cd[STR ? 5 : 0] : (T)0;
     const cx<T>* L = bufp(IC<cur>{}) + lb;
     cx<T> acc2[3];
-    const Fold<T> f = load_fold<T, PH>(a.ptab, a.ptab64, z, ux);
+    const Fold<T> f = load_fold<T, PH>(frow, frow64, ux);
+    if constexpr (PH != 0) frow += fold_offset(1);
+    if constexpr (PH == 2) frow64 += fold_offset(1);
     push_plane<T, PH, STR, NC, PLANE, W>(L, X, F, k, dgs, ax, ay, az, sd3, sby, shift, f, d00,
                                          d11, d22, d12, d02, d01, acc0, acc1, acc2);
 
@@ -670,17 +684,21 @@ hipError_t launch_t(const StencilLaunch& L, const StencilConsts<double>& c, hipS
     if (nwg <= 0) return hipSuccess;
     // z split: 0 never, 1 as balances the launch (z_split), 2 always in two (tests)
     a.c0 = sizeof(T) == 8 ? 2.2f : (std::is_same<TO, void>::value ? 2.6f : 2.0f);
-    a.cus = device_cus();
-    a.zsplit = a.zfixed = 1;
+    const int cus = device_cus();
+    a.cus = (float)cus;
+    a.icus = 1.0f / (float)cus;
+    a.zsplit = 1;
+    ZRanges fixed{1, 1.0f};
     if (L.zsplit >= 2) {
       a.zsplit = 2;
-      a.zfixed = L.nz >= 8 ? 2 : 1;
+      if (L.nz >= 8) fixed = ZRanges{2, 0.5f};
     } else if (L.zsplit == 1) {
-      const ZSplit z = z_split(nwg, L.nz, L.work && L.vlive < 0, a.c0, a.cus);
+      const ZSplit z = z_split(nwg, L.nz, L.work && L.vlive < 0, a.c0, cus);
       a.zsplit = z.room;
-      a.zfixed = z.fixed;
+      fixed = z.fixed;
     }
-    a.cut = z_cut(L.nz, a.zfixed ? a.zfixed : 1);
+    a.zfixed = fixed.zs;
+    a.cut = z_cut(L.nz, fixed.zs > 0 ? fixed : ZRanges{1, 1.0f});
     if (nwg * a.zsplit > 0x7fffffffLL) return hipErrorInvalidValue;
     kernel<<<dim3((unsigned)(nwg * a.zsplit)), dim3(64, waves, NSP), 0, s>>>(a);
     return hipGetLastError();

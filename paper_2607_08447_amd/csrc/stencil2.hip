@@ -261,7 +261,7 @@ stencil2_kernel(K2Args a) {
       const T d02 = STR ? d1[STR ? 4 : 0] : (T)0;
       const T d01 = STR ? d1[STR ? 5 : 0] : (T)0;
       push_plane<T, PH, STR, 6, IPL, IW>(L, X, F, k, dgs, ax, ay, az, sd3, sby, shift1,
-                                         (load_fold<T, PH>(a.ptab, nullptr, z, one)), d00, d11, d22, d12, d02, d01, acc0,
+                                         (load_fold<T, PH>(a.ptab + fold_offset(z), nullptr, one)), d00, d11, d22, d12, d02, d01, acc0,
                                          acc1, acc2);
     }
     // this thread's tile column of Y0 plane z (own spin), for Y2's beta term
@@ -280,7 +280,7 @@ stencil2_kernel(K2Args a) {
       const T d02 = STR ? d2[STR ? 4 : 0] : (T)0;
       const T d01 = STR ? d2[STR ? 5 : 0] : (T)0;
       push_plane<T, PH, STR, 6, EPL, EW>(L, X, F, k, dgs, ax, ay, az, sd3, sby, shift2,
-                                         (load_fold<T, PH>(a.ptab, nullptr, z - 2, one)), d00, d11, d22, d12, d02, d01, bcc0,
+                                         (load_fold<T, PH>(a.ptab + fold_offset(z - 2), nullptr, one)), d00, d11, d22, d12, d02, d01, bcc0,
                                          bcc1, bcc2);
     }
     // both steps' arithmetic is done before the stores below: their wait for the

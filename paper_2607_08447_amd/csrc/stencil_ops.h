@@ -150,12 +150,12 @@ using Const = const __attribute__((address_space(4))) T;   // uniform tables: sc
 // phase along x: those products are formed in double from the double table, so an
 // FP32 constant is rounded once.  One scalar load per plane in place of about 40 vector operations
 // per wave and plane to fold them (a sixth of the plane's arithmetic).
+// (row, row64: the plane's rows of the two tables)
 template <typename T, int PH>
-__device__ __forceinline__ Fold<T> load_fold(const T* ptab, const double* ptab64, int z,
-                                             cx<double> u) {
+__device__ __forceinline__ Fold<T> load_fold(const T* row, const double* row64, cx<double> u) {
   Fold<T> f;
   if constexpr (PH != 0) {
-    Const<T>* t = (Const<T>*)ptab + fold_offset(z);
+    Const<T>* t = (Const<T>*)row;
     auto at = [&](int i) { return mk<T>(t[2 * i], t[2 * i + 1]); };
     f.xo = at(0);
     f.xa = at(1);
@@ -170,7 +170,7 @@ __device__ __forceinline__ Fold<T> load_fold(const T* ptab, const double* ptab64
     f.du = at(10);
     f.dd = at(11);
     if constexpr (PH == 2) {
-      Const<double>* t64 = (Const<double>*)ptab64 + fold_offset(z);
+      Const<double>* t64 = (Const<double>*)row64;
       auto by = [&](cx<double> ph, int i) {
         const cx<double> r = mul(ph, mk<double>(t64[2 * i], t64[2 * i + 1]));
         return mk<T>((T)r.r, (T)r.i);

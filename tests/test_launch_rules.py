@@ -28,17 +28,18 @@ int main() {
       for (int i = 0; i < n; ++i)
         std::printf("%d %d %d %d\n", t[i].tile_y, t[i].vgroup, t[i].dma, t[i].zsplit);
     }
-    if (!std::strcmp(what, "range")) std::printf("%d\n", range_begin((int)a, z_cut((int)b, (int)c)));
+    if (!std::strcmp(what, "range")) std::printf("%d\n", range_begin((int)a, z_cut((int)b, ZRanges{(int)c, 1.0f / (float)c})));
     if (!std::strcmp(what, "fold")) std::printf("%zu\n", fold_offset((int)a));
     if (!std::strcmp(what, "room")) std::printf("%d\n", z_split(a, (int)b, c != 0, c0[1], d ? (int)d : kCUs).room);
-    if (!std::strcmp(what, "fixed")) std::printf("%d\n", z_split(a, (int)b, c != 0, c0[1], d ? (int)d : kCUs).fixed);
+    if (!std::strcmp(what, "fixed")) std::printf("%d\n", z_split(a, (int)b, c != 0, c0[1], d ? (int)d : kCUs).fixed.zs);
     if (!std::strcmp(what, "ranges"))   // a live workgroups, b planes, at most c ranges, d CUs
-      std::printf("%d\n", z_ranges((int)a, (int)b, (int)c, c0[1], (int)d));
+      std::printf("%d\n", z_ranges((int)a, (int)b, (int)c, c0[1], (float)d, 1.0f / (float)d).zs);
     if (!std::strcmp(what, "vectors")) std::printf("%lld\n", table_vectors(a, b, c));
     if (!std::strcmp(what, "anew")) std::printf("%d\n", record_anew((int)a, (int)b, c, kCUs) ? 1 : 0);
     for (int k = 0; k < 3; ++k)   // ranges of `c` live workgroups in a launch over `a`
       if (!std::strcmp(what, "live"))
-        std::printf("%d\n", z_ranges((int)c, (int)b, z_split(a, (int)b, true, c0[k], kCUs).room, c0[k], kCUs));
+        std::printf("%d\n", z_ranges((int)c, (int)b, z_split(a, (int)b, true, c0[k], kCUs).room, c0[k],
+                                     kCUs, 1.0f / kCUs).zs);
   }
 }
 """
