@@ -274,7 +274,8 @@ int hkp_solve(const hkp_grid* grid, const hkp_material* mat, const hkp_opts* opt
  * Every kernel of an outer iteration covers the whole batch in one launch;
  * with HKP_FLAG_GRAPH an iteration is recorded once per combination of filters
  * that its members need (FP32, FP64, both) as a hipGraph and replayed,
- * converged members turning into no-ops on the device. */
+ * converged members turning into no-ops on the device; large batches record it
+ * anew when a quarter of the members is left. */
 int hkp_solve_batch(const hkp_grid* grid, const hkp_material* mat, const hkp_opts* opts,
                     int32_t batch, const double* V_eV, const double* strain,
                     const double B_T[3], const void* X0, double* eig_eV, void* psi,
